@@ -72,8 +72,9 @@ typedef enum {
     SINET_LOOKUP_LEARNED_MLP = 5  /* 1-16-1 ReLU MLP + bounded search        */
 } sinet_lookup;
 
-/* OR-ed into the kind argument of sinet_table_create: do not build the
- * in/out index, so label-only queries also run the kind's own search. */
+/* OR-ed into the kind argument of sinet_table_create: build neither the
+ * in/out index nor the institution index, so label-only and institution
+ * queries also run the kind's own search. */
 #define SINET_TABLE_NO_INOUT_INDEX 0x100u
 /* OR-ed into the kind argument: a BSEARCH table searches the boundaries in
  * global memory from the first probe (no LDS copy of sampled boundaries),
@@ -194,7 +195,9 @@ const char* sinet_version(void);
  * index when it fits in LDS (a 2-bit state per /16 block plus the sorted
  * 16-bit offsets of the boundaries of the union of all prefixes inside the
  * /16 blocks that such a boundary cuts); label-only queries are answered from
- * it, the kind's search serves institution ids and positions.  kind may be
+ * it.  Every table also gets an institution index (the /16 blocks that any
+ * prefix touches, and small sorted groups of the boundaries inside them), which
+ * answers institution ids; the kind's search serves positions.  kind may be
  * OR-ed with SINET_TABLE_NO_INOUT_INDEX.  base: IPv4
  * address, host bits allowed (they are masked off as Algorithm 1 masks the
  * CIDR base); len: prefix length Z in 0..32; inst: institution id of the row

@@ -9,6 +9,7 @@
 
 #include "sinet.h"
 #include "inout_index.h"
+#include "inst_index.h"
 #include "sinet_internal.h"
 
 namespace sinet {
@@ -159,10 +160,12 @@ static uint32_t pla_lds_words(const DevTable& t, uint32_t S, bool window) {
 static void build_filter(const std::vector<uint32_t>& B, const std::vector<uint32_t>& owner,
                          std::vector<uint32_t>& filter) {
     filter.assign(kFilterWords, 0);
+    size_t j1 = 0;  // the interval of the block's last address, one sweep over B
     for (uint64_t k = 0; k < 65536; ++k) {
         const uint32_t lo = (uint32_t)(k << 16), hi = lo | 0xFFFFu;
-        const uint32_t j0 = (uint32_t)(std::upper_bound(B.begin(), B.end(), lo) - B.begin()) - 1;
-        const uint32_t j1 = (uint32_t)(std::upper_bound(B.begin(), B.end(), hi) - B.begin()) - 1;
+        while (j1 + 1 < B.size() && B[j1 + 1] <= lo) ++j1;
+        const size_t j0 = j1;  // that of its first
+        while (j1 + 1 < B.size() && B[j1 + 1] <= hi) ++j1;
         const uint32_t st = j0 != j1 ? 2u : (owner[j0] ? 1u : 0u);
         filter[k >> 4] |= st << ((k & 15) * 2);
     }
@@ -345,6 +348,8 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
     bool io_ok = interval_kind && want_io && build_inout(t->B, t->owner, io, iod) &&
                  io.size() + kLdsReserveWords <= lds_words;
     if (!io_ok) io.clear();
+    InstIndex ix;
+    if (want_io) build_inst_index(t->B, t->owner, id.data(), ix);
     std::vector<uint32_t> trie;
     if (kind == SINET_LOOKUP_TRIE) build_trie(t->B, trie);
     const bool learned = kind == SINET_LOOKUP_LEARNED_PLA || kind == SINET_LOOKUP_LEARNED_MLP;
@@ -359,7 +364,10 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
                  oTop = take(4ull * n_top), oTrie = take(4 * trie.size()),
                  oKnot = take(4ull * smax), oC = take(4ull * smax), oG = take(4ull * smax),
                  oMlp = take(4 * SINET_MLP_PARAMS), oFb = take(8), oRadix = take(4ull * rw),
-                 oFilter = take(4ull * filter.size()), oIo = take(4ull * io.size());
+                 oFilter = take(4ull * filter.size()), oIo = take(4ull * io.size()),
+                 oIg = take(4ull * ix.groups.size()), oIf = take(4ull * ix.first.size()),
+                 oIs = take(2ull * ix.sample.size()), oIl = take(4ull * ix.leaves.size()),
+                 oIi = take(4ull * ix.MI.size());
     void* arena = nullptr;
     hipError_t e = hipMalloc(&arena, off);
     if (e != hipSuccess) {
@@ -377,6 +385,11 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
     if (r == hipSuccess) r = up(oB, Bpad.data(), 4ull * (m_pad + kBTail));
     if (r == hipSuccess) r = up(oFilter, filter.data(), 4ull * filter.size());
     if (r == hipSuccess) r = up(oIo, io.data(), 4ull * io.size());
+    if (r == hipSuccess) r = up(oIg, ix.groups.data(), 4ull * ix.groups.size());
+    if (r == hipSuccess) r = up(oIf, ix.first.data(), 4ull * ix.first.size());
+    if (r == hipSuccess) r = up(oIs, ix.sample.data(), 2ull * ix.sample.size());
+    if (r == hipSuccess) r = up(oIl, ix.leaves.data(), 4ull * ix.leaves.size());
+    if (r == hipSuccess) r = up(oIi, ix.MI.data(), 4ull * ix.MI.size());
     if (r == hipSuccess) r = up(oOwn, t->owner.data(), 4ull * m);
     if (r == hipSuccess) r = up(oMem, member.data(), 4ull * mw);
     if (r == hipSuccess) r = up(oInst, id.data(), 4 * P);
@@ -422,6 +435,18 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
         d.io_words = iod.io_words;
         d.io_slot = iod.io_slot;
         d.io_list = iod.io_list;
+    }
+    t->inst = InstDev{};
+    if (want_io) {
+        t->inst.groups = (const uint32_t*)(a + oIg);
+        t->inst.first = (const uint32_t*)(a + oIf);
+        t->inst.sample = (const uint16_t*)(a + oIs);
+        t->inst.leaves = (const uint32_t*)(a + oIl);
+        t->inst.MI = (const uint32_t*)(a + oIi);
+        t->inst.n_first = (uint32_t)ix.first.size();
+        t->inst.n_sample = (uint32_t)ix.sample.size();
+        t->inst.steps = ix.steps;
+        t->inst.n_dict = ix.coded ? (uint32_t)ix.MI.size() : 0u;
     }
     d.m_f = (float)m;
     d.fallbacks = (unsigned long long*)(a + oFb);
@@ -600,6 +625,8 @@ sinet_status sinet_discriminate(const sinet_table* t, const uint32_t* src, const
     if (n == 0) return SINET_OK;
     if (!src || !dst) return fail(SINET_ERR_INVALID_ARG, "src or dst is NULL");
     if (!label && !src_inst && !dst_inst) return SINET_OK;
+    if ((src_inst || dst_inst) && t->inst.groups)
+        return run_inst(t->inst, src, dst, n, label, src_inst, dst_inst, stream);
     PassParams p;
     memset(&p, 0, sizeof(p));
     p.t = label_view(t, !src_inst && !dst_inst);

@@ -2196,7 +2196,7 @@ uint32_t device_cu_count() {
     return cus;
 }
 
-static int blocks_per_cu(const void* fn, int block, size_t lds) {
+int blocks_per_cu(const void* fn, int block, size_t lds) {
     static std::mutex mu;
     static std::map<std::tuple<const void*, int, size_t, int>, int> cache;
     int dev = 0;

@@ -184,6 +184,18 @@ struct BatchArgs {
     uint32_t queue_words;       // lookup pass: LDS words per wave for the window PLA's queue
 };
 
+// Device arrays of a table's institution index (inst_index.h); groups is
+// nullptr when the table has none.
+struct InstDev {
+    const uint32_t* groups;
+    const uint32_t* first;
+    const uint16_t* sample;
+    const uint32_t* leaves;
+    const uint32_t* MI;
+    uint32_t n_first, n_sample, steps;
+    uint32_t n_dict;            // coded leaves: dictionary words in MI, else 0
+};
+
 struct ZeroJob {
     unsigned long long* p;
     uint64_t n;                 // 64-bit words
@@ -193,6 +205,7 @@ struct ZeroJob {
 
 struct sinet_table {
     sinet::DevTable dev;
+    sinet::InstDev inst;
     sinet_lookup kind;
     uint64_t n_prefix;
     void* arena;                // one device allocation holding every array
@@ -260,7 +273,12 @@ sinet_status parse_sessions(const uint8_t* text, uint64_t len, int64_t origin, c
 sinet_status ws_alloc(void** ptr, size_t bytes, hipStream_t s);
 sinet_status ws_free(void* ptr, hipStream_t s);
 uint32_t device_cu_count();
+int blocks_per_cu(const void* fn, int block, size_t lds);
 uint64_t div_magic(uint32_t width);
+
+// Institution ids (and labels) through the institution index (inst.hip).
+sinet_status run_inst(const InstDev& x, const uint32_t* src, const uint32_t* dst, uint64_t n,
+                      uint8_t* label, uint32_t* src_inst, uint32_t* dst_inst, hipStream_t s);
 
 // sliding-window histogram (window.hip)
 uint32_t win_pieces(uint64_t n);
