@@ -195,7 +195,7 @@ const char* sinet_version(void);
  * index when it fits in LDS (a 2-bit state per /16 block plus the sorted
  * 16-bit offsets of the boundaries of the union of all prefixes inside the
  * /16 blocks that such a boundary cuts); label-only queries are answered from
- * it.  Every table also gets an institution index (the /16 blocks that any
+ * it (a SCAN table's by a search over that union's boundaries).  Every table also gets an institution index (the /16 blocks that any
  * prefix touches, and small sorted groups of the boundaries inside them), which
  * answers institution ids; the kind's search serves positions.  kind may be
  * OR-ed with SINET_TABLE_NO_INOUT_INDEX.  base: IPv4
@@ -454,7 +454,10 @@ sinet_status sinet_pipeline_noalloc(const sinet_table* t, const sinet_columns* c
  *   index_ms      segment scan, directory fill   k_window_bounds: pieces' bins
  *   stage2_ms     k_stage2: block reduction      k_window_fixup: boundary spills
  *   far_ms        far pass (global atomics)      k_window_far (global atomics)
- * For n_bins <= 2048 stage1_ms is the single private-histogram pass. */
+ * Coarse bins (the local reduce, see sinet_set_reduce): stage1_ms is its one
+ * pass, lookup_ms the lookup pass when the lookup is not fused into it; where a
+ * probe decides, stage1_ms and stage1_launches count both reduces, of which one
+ * returns at once. */
 typedef struct {
     double lookup_ms;
     double stage1_ms;
@@ -462,7 +465,7 @@ typedef struct {
     double stage2_ms;
     double far_ms;
     uint64_t calls;     /* timed sinet_histogram / sinet_pipeline calls */
-    uint64_t stage1_launches;  /* stage-1 (or private-pass, or window) launches among them */
+    uint64_t stage1_launches;  /* stage-1 (or local, or window) launches among them */
     uint64_t window_calls;     /* calls (pieces of calls) reduced by the sliding window */
 } sinet_timing;
 
@@ -477,9 +480,10 @@ sinet_status sinet_timing_enable(int on);
 sinet_status sinet_timing_read(sinet_timing* out);
 
 /* Reduce used by sinet_histogram / sinet_pipeline (and the streamer) when
- * the histogram has more than 2048 bins (smaller ones are always reduced in
- * LDS per workgroup).  Both reduces give bit-identical results for any
- * input; they differ in speed and workspace:
+ * the histogram has more than 2048 bins.  Smaller ones always take the local
+ * reduce: a workgroup adds a contiguous range of sessions into the bins they
+ * touch in LDS and adds those to the output.  All reduces give bit-identical
+ * results for any input; they differ in speed and workspace:
  *   RECORDS  the two-stage map-reduce of the sections "Two-stage Map-Reduce
  *            with tiling pattern" and "Reduce": stage 1 writes one 4-byte
  *            record per session grouped by 1024-bin block, stage 2 reduces
@@ -490,8 +494,10 @@ sinet_status sinet_timing_read(sinet_timing* out);
  *            sessions with the bins it touches in LDS and writes every bin
  *            once (labels are stored by a lookup pass first; about 1 byte
  *            of workspace per session plus 330 MB);
- *   AUTO     WINDOW from 2^28 sessions on, else RECORDS (the default; the
- *            measured crossover of the two on a day of 1-ms bins).
+ *   AUTO     (the default) the local reduce from 16 sessions per bin on, for
+ *            bins narrower than 48 ms only if a probe of the sessions' order
+ *            on the device allows it; else WINDOW from 2^28 sessions on, else
+ *            RECORDS (the measured crossover of the two on a day of 1-ms bins).
  * Process-wide; takes effect for calls made after it returns.
  * Errors: INVALID_ARG (unknown mode). */
 typedef enum {

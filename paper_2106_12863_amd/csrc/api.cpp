@@ -113,18 +113,24 @@ static void build_trie(const std::vector<uint32_t>& B, std::vector<uint32_t>& tr
     }
 }
 
-// In/out index of the union of the prefixes (layout in inout_index.h).
-static bool build_inout(const std::vector<uint32_t>& B, const std::vector<uint32_t>& owner,
-                        std::vector<uint32_t>& io, DevTable& d) {
-    std::vector<uint32_t> U;  // where membership of the union changes
+// Where membership in the union of the prefixes changes (outside before 0).
+static std::vector<uint32_t> union_boundaries(const std::vector<uint32_t>& B,
+                                              const std::vector<uint32_t>& owner) {
+    std::vector<uint32_t> U;
     bool prev = false;
     for (size_t j = 0; j < B.size(); ++j) {
         const bool in = owner[j] != 0;
         if (in != prev) U.push_back(B[j]);
         prev = in;
     }
+    return U;
+}
+
+// In/out index of the union of the prefixes (layout in inout_index.h).
+static bool build_inout(const std::vector<uint32_t>& B, const std::vector<uint32_t>& owner,
+                        std::vector<uint32_t>& io, DevTable& d) {
     IoLayout lay{};
-    if (!build_inout_index(U, io, lay)) return false;
+    if (!build_inout_index(union_boundaries(B, owner), io, lay)) return false;
     d.io_words = lay.words;
     d.io_slot = lay.slot;
     d.io_list = lay.list;
@@ -187,12 +193,16 @@ sinet_status check_usable(const sinet_table* t) {
 }
 
 // The device view a pass uses: label-only passes of a table with an in/out
-// index run the index kind (LDS holds the index alone).
+// index (a scan table: its union's boundaries) run the index kind (LDS holds
+// the index alone).
 DevTable label_view(const sinet_table* t, bool label_only) {
     DevTable d = t->dev;
     if (label_only && d.io) {
         d.kind = kInoutKind;
         d.lds_bytes = 4u * d.io_words;
+    } else if (label_only && d.un) {
+        d.kind = kUnionKind;
+        d.lds_bytes = 4u << d.un_steps;
     }
     return d;
 }
@@ -226,14 +236,9 @@ sinet_status pipeline_prepare(const sinet_table* t, const sinet_columns* cols, c
     if (!out || !out->count || !out->bytes) return fail(SINET_ERR_INVALID_ARG, "histogram output is NULL");
     if (cols->n && (!cols->ts || !cols->src || !cols->dst || !cols->bytes))
         return fail(SINET_ERR_INVALID_ARG, "column is NULL");
-    if (!accumulate && (cols->n == 0 || out->dropped)) {
-        st = cols->n == 0 ? clear_hist(win, out, stream)
-                          : launch_zero((unsigned long long*)out->dropped, 8, stream);
-        if (st != SINET_OK) return st;
-    }
-    if (cols->n == 0) {
+    if (cols->n == 0) {  // otherwise the reduce clears its outputs
         *done = true;
-        return SINET_OK;
+        return accumulate ? SINET_OK : clear_hist(win, out, stream);
     }
     PassParams& p = *pp;
     memset(&p, 0, sizeof(p));
@@ -348,6 +353,19 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
     bool io_ok = interval_kind && want_io && build_inout(t->B, t->owner, io, iod) &&
                  io.size() + kLdsReserveWords <= lds_words;
     if (!io_ok) io.clear();
+    // a scan table's label-only queries search its union's boundaries
+    std::vector<uint32_t> un;
+    uint32_t un_steps = 0, un_in0 = 0;
+    if (!interval_kind && want_io) {
+        un = union_boundaries(t->B, t->owner);
+        if (!un.empty() && un[0] == 0) {
+            un_in0 = 1;
+            un.erase(un.begin());
+        }
+        for (uint32_t& b : un) --b;
+        while ((1u << un_steps) <= un.size()) ++un_steps;
+        un.resize((size_t)1 << un_steps, 0xFFFFFFFFu);
+    }
     InstIndex ix;
     if (want_io) build_inst_index(t->B, t->owner, id.data(), ix);
     std::vector<uint32_t> trie;
@@ -365,7 +383,7 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
                  oKnot = take(4ull * smax), oC = take(4ull * smax), oG = take(4ull * smax),
                  oMlp = take(4 * SINET_MLP_PARAMS), oFb = take(8), oRadix = take(4ull * rw),
                  oFilter = take(4ull * filter.size()), oIo = take(4ull * io.size()),
-                 oIg = take(4ull * ix.groups.size()), oIf = take(4ull * ix.first.size()),
+                 oUn = take(4ull * un.size()), oIg = take(4ull * ix.groups.size()), oIf = take(4ull * ix.first.size()),
                  oIs = take(2ull * ix.sample.size()), oIl = take(4ull * ix.leaves.size()),
                  oIi = take(4ull * ix.MI.size());
     void* arena = nullptr;
@@ -377,29 +395,29 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
     t->arena = arena;
     t->arena_bytes = off;
     char* a = (char*)arena;
-    auto up = [&](size_t o, const void* src, size_t bytes) -> hipError_t {
-        if (!bytes) return hipSuccess;
-        return hipMemcpyAsync(a + o, src, bytes, hipMemcpyHostToDevice, stream);
+    // one image of the arena, one copy
+    std::vector<char> image(off, 0);
+    auto up = [&](size_t o, const void* src, size_t bytes) {
+        if (bytes) memcpy(image.data() + o, src, bytes);
     };
-    hipError_t r = hipSuccess;
-    if (r == hipSuccess) r = up(oB, Bpad.data(), 4ull * (m_pad + kBTail));
-    if (r == hipSuccess) r = up(oFilter, filter.data(), 4ull * filter.size());
-    if (r == hipSuccess) r = up(oIo, io.data(), 4ull * io.size());
-    if (r == hipSuccess) r = up(oIg, ix.groups.data(), 4ull * ix.groups.size());
-    if (r == hipSuccess) r = up(oIf, ix.first.data(), 4ull * ix.first.size());
-    if (r == hipSuccess) r = up(oIs, ix.sample.data(), 2ull * ix.sample.size());
-    if (r == hipSuccess) r = up(oIl, ix.leaves.data(), 4ull * ix.leaves.size());
-    if (r == hipSuccess) r = up(oIi, ix.MI.data(), 4ull * ix.MI.size());
-    if (r == hipSuccess) r = up(oOwn, t->owner.data(), 4ull * m);
-    if (r == hipSuccess) r = up(oMem, member.data(), 4ull * mw);
-    if (r == hipSuccess) r = up(oInst, id.data(), 4 * P);
-    if (r == hipSuccess) r = up(oCb, cb.data(), 4 * P);
-    if (r == hipSuccess) r = up(oMk, mk.data(), 4 * P);
-    if (r == hipSuccess) r = up(oLn, ln.data(), 4 * P);
-    if (r == hipSuccess) r = up(oTop, top.data(), 4ull * n_top);
-    if (r == hipSuccess) r = up(oTrie, trie.data(), 4 * trie.size());
-    const unsigned long long zero = 0;
-    if (r == hipSuccess) r = up(oFb, &zero, 8);
+    up(oB, Bpad.data(), 4ull * (m_pad + kBTail));
+    up(oFilter, filter.data(), 4ull * filter.size());
+    up(oIo, io.data(), 4ull * io.size());
+    up(oUn, un.data(), 4ull * un.size());
+    up(oIg, ix.groups.data(), 4ull * ix.groups.size());
+    up(oIf, ix.first.data(), 4ull * ix.first.size());
+    up(oIs, ix.sample.data(), 2ull * ix.sample.size());
+    up(oIl, ix.leaves.data(), 4ull * ix.leaves.size());
+    up(oIi, ix.MI.data(), 4ull * ix.MI.size());
+    up(oOwn, t->owner.data(), 4ull * m);
+    up(oMem, member.data(), 4ull * mw);
+    up(oInst, id.data(), 4 * P);
+    up(oCb, cb.data(), 4 * P);
+    up(oMk, mk.data(), 4 * P);
+    up(oLn, ln.data(), 4 * P);
+    up(oTop, top.data(), 4ull * n_top);
+    up(oTrie, trie.data(), 4 * trie.size());
+    hipError_t r = hipMemcpyAsync(arena, image.data(), off, hipMemcpyHostToDevice, stream);
     if (r == hipSuccess) r = hipStreamSynchronize(stream);
     if (r != hipSuccess) {
         (void)hipFree(arena);
@@ -435,6 +453,11 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
         d.io_words = iod.io_words;
         d.io_slot = iod.io_slot;
         d.io_list = iod.io_list;
+    }
+    if (!un.empty()) {
+        d.un = (const uint32_t*)(a + oUn);
+        d.un_steps = un_steps;
+        d.un_in0 = un_in0;
     }
     t->inst = InstDev{};
     if (want_io) {
@@ -646,12 +669,7 @@ sinet_status sinet_histogram(const uint32_t* ts, const uint64_t* bytes, const ui
     if (st != SINET_OK) return st;
     if (!out || !out->count || !out->bytes) return fail(SINET_ERR_INVALID_ARG, "histogram output is NULL");
     if (n && (!ts || !bytes || !label)) return fail(SINET_ERR_INVALID_ARG, "column is NULL");
-    if (!accumulate && (n == 0 || out->dropped)) {
-        st = n == 0 ? clear_hist(win, out, stream)
-                    : launch_zero((unsigned long long*)out->dropped, 8, stream);
-        if (st != SINET_OK) return st;
-    }
-    if (n == 0) return SINET_OK;
+    if (n == 0) return accumulate ? SINET_OK : clear_hist(win, out, stream);
     PassParams p;
     memset(&p, 0, sizeof(p));
     p.ts = ts;

@@ -51,9 +51,11 @@ enum KernelKind : uint32_t {
     KK_PLA = SINET_LOOKUP_LEARNED_PLA,
     KK_MLP = SINET_LOOKUP_LEARNED_MLP,
     KK_INOUT = kInoutKind,  // label-only lookups through the in/out index
+    KK_UNION = kUnionKind,  // label-only lookups of a scan table: its union's boundaries
     KK_LABEL_IN = 100       // histogram of given labels
 };
-static_assert(KK_LABEL_IN == kLabelInKind && KK_INOUT == kInoutKind, "internal kinds");
+static_assert(KK_LABEL_IN == kLabelInKind && KK_INOUT == kInoutKind && KK_UNION == kUnionKind,
+              "internal kinds");
 
 constexpr int kXcds = 8;
 constexpr int kMaxBlock = 1024;
@@ -75,7 +77,7 @@ constexpr uint64_t kMaxPiece = 1ull << 31;  // sessions per partitioned pass (32
 
 // Per-workgroup LDS view of the table.
 struct LdsView {
-    const uint32_t* io;      // in/out index
+    const uint32_t* io;      // in/out index, or the union's boundaries
     const uint32_t* filter;  // 2-bit state of every /16 block (interval kinds)
     const uint32_t* top;     // BSEARCH
     const uint32_t* member;  // all interval kinds (or global)
@@ -549,6 +551,28 @@ __device__ __forceinline__ uint32_t scan_owner(const DevTable& t, const LdsView&
     return best;
 }
 
+// Membership of each address in the union of a scan table's prefixes: the
+// parity of the number of its boundaries (in0: an odd start) at or below the
+// address, found by a binary search over at most 2^11 of them in LDS, every
+// address in lockstep.  They are stored less one, so that b <= a is b - 1 < a,
+// padded to 2^steps - 1 words with 0xFFFFFFFF.  Algorithm 1's row scan costs a
+// lane 64 x 8 dependent LDS reads for its four sessions against 64 rows, and
+// 21 us for the few workgroups of a 10,000-session call; this is 7 rounds of 8
+// independent ones.
+template <int N>
+__device__ __forceinline__ void union_lookup(const uint32_t* un, uint32_t steps, uint32_t in0,
+                                             const uint32_t* a, uint32_t* in) {
+    uint32_t c[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) c[q] = 0;
+    for (uint32_t h = 1u << steps >> 1; h; h >>= 1) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) c[q] += un[c[q] + h - 1u] < a[q] ? h : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) in[q] = (c[q] ^ in0) & 1u;
+}
+
 // In/out mark (and, when want_code, the owner code row + 1 or 0) of each
 // address.  Label-only lookups first consult the /16 filter: a block that no
 // boundary cuts is entirely in or entirely out, which answers most addresses
@@ -558,6 +582,10 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
                                         bool want_code, uint32_t* in, uint32_t* code) {
     if constexpr (KIND == KK_INOUT) {
         inout_lookup<N>(v.io, t.io_slot, t.io_list, a, in);
+#pragma unroll
+        for (int q = 0; q < N; ++q) code[q] = 0;
+    } else if constexpr (KIND == KK_UNION) {
+        union_lookup<N>(v.io, t.un_steps, t.un_in0, a, in);
 #pragma unroll
         for (int q = 0; q < N; ++q) code[q] = 0;
     } else if constexpr (KIND == KK_SCAN) {
@@ -674,7 +702,7 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
 enum HistMode : int {
     H_NONE = 0,     // labels / institutions / positions only
     H_ATOMIC = 1,   // device-scope atomics into the output bins
-    H_PRIVATE = 2   // whole histogram privatised in LDS per workgroup
+    H_PRIVATE = 2   // whole histogram privatised in LDS per workgroup (batches)
 };
 
 // LDS histogram of the private mode: counts u32 [4][n_bins], bytes u64 [4][n_bins].
@@ -730,7 +758,7 @@ template <uint32_t KIND, int HM>
 __device__ __forceinline__ void one_session(const PassParams& p, const LdsView& v,
                                             const PrivHist& h, uint64_t i, Dropped& d) {
     if (p.pos_out) {
-        if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT) {
+        if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT && KIND != KK_UNION) {
             const uint32_t a = p.src[i];
             uint32_t j;
             intervals<KIND, 1>(p.t, v, &a, &j);
@@ -810,7 +838,7 @@ template <uint32_t KIND, int HM>
 __device__ __forceinline__ void four_sessions(const PassParams& p, const LdsView& v,
                                               const PrivHist& h, uint64_t i, Dropped& d) {
     if (p.pos_out) {
-        if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT) {
+        if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT && KIND != KK_UNION) {
             const uint4 a4 = *reinterpret_cast<const uint4*>(p.src + i);
             const uint32_t a[4] = {a4.x, a4.y, a4.z, a4.w};
             uint32_t j[4];
@@ -846,6 +874,8 @@ __device__ __forceinline__ LdsView stage_lds(const DevTable& t, uint32_t* lds, u
     };
     if constexpr (KIND == KK_INOUT) {
         v.io = copy(t.io, t.io_words);
+    } else if constexpr (KIND == KK_UNION) {
+        v.io = copy(t.un, 1u << t.un_steps);
     } else if constexpr (KIND == KK_SCAN) {
         v.cb = copy(t.cb, t.n_prefix);
         v.mask = copy(t.mask, t.n_prefix);
@@ -875,8 +905,6 @@ __device__ __forceinline__ LdsView stage_lds(const DevTable& t, uint32_t* lds, u
 // ---------------------------------------------------------------------------
 // k_pass: one pass over the sessions.
 //   H_NONE    labels / institutions / positions;
-//   H_PRIVATE the whole (small) histogram lives in LDS per workgroup and is
-//             merged into the output bins with atomics at the end;
 //   H_ATOMIC  with far.list: only the sessions the partitioned path flagged
 //             as far (see k_stage1), merged with device-scope atomics after
 //             the block reduction wrote the bins; without: every session.
@@ -885,21 +913,12 @@ template <uint32_t KIND, int HM, bool VEC>
 __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& far) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     uint32_t used = 0;
+    if (HM == H_ATOMIC && far.list && *glob(far.count) == 0) return;  // before the table is staged
     LdsView v = stage_lds<KIND>(p.t, lds, &used);
     if constexpr (HM == H_NONE && queued_kind(KIND)) {
         if (p.queue_words) v.queue = lds + used + (threadIdx.x >> 6) * p.queue_words;
     }
-    PrivHist h{nullptr, nullptr};
-    if constexpr (HM == H_PRIVATE) {
-        used = (used + 1) & ~1u;
-        h.b = reinterpret_cast<unsigned long long*>(lds + used);
-        h.c = lds + used + 2 * 4 * p.n_bins;
-        for (uint32_t k = threadIdx.x; k < 4 * p.n_bins; k += blockDim.x) {
-            h.b[k] = 0;
-            h.c[k] = 0;
-        }
-        __syncthreads();
-    }
+    const PrivHist h{nullptr, nullptr};
     Dropped d{};
     if (HM == H_ATOMIC && far.list) {
         const uint32_t nfar = *far.count;
@@ -970,17 +989,6 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
         }
     }
     if constexpr (HM != H_NONE) d.flush(p.dropped);
-    if constexpr (HM == H_PRIVATE) {
-        __syncthreads();
-        for (uint32_t k = threadIdx.x; k < 4 * p.n_bins; k += blockDim.x) {
-            if (h.c[k]) {
-                __hip_atomic_fetch_add(p.count + k, (unsigned long long)h.c[k], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(p.hbytes + k, h.b[k], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
 }
 
 template <uint32_t KIND, int HM, bool VEC>
@@ -1202,6 +1210,7 @@ __global__ void __launch_bounds__(kStage1Block, 4) k_stage1(PassParams p, PartWs
     __shared__ Stage1Shared sh[2];
     __shared__ uint4 srec[kChunkSlots / 4];
     __shared__ uint32_t s_run;
+    if (w.gate && !*glob(w.gate)) return;
     uint32_t used = 0;
     const LdsView v = stage_lds<KIND>(p.t, lds, &used);
     Dropped d{};
@@ -1227,6 +1236,160 @@ __global__ void __launch_bounds__(kStage1Block, 4) k_stage1(PassParams p, PartWs
             stage1_chunk<KIND>(p, w, v, sh[iter++ & 1u], srec, c, c, 0u, cur, full(c), d);
             cur = nxt;
         }
+    }
+    d.flush(p.dropped);
+}
+
+// ---------------------------------------------------------------------------
+// k_local: the reduce of coarse bins (many sessions per bin), one pass with the
+// labels computed or given.
+//
+// Session logs are nearly sorted by time, so with many sessions per bin the
+// sessions of a contiguous range touch few bins.  A workgroup takes one range
+// and walks it in runs of at most 2^17 - 1 sessions; during a run it keeps a
+// window of `bins` bins x 4 labels in LDS, one 64-bit word each (count << 47 |
+// byte sum), adds every session with one LDS atomic, and at the run's end adds
+// the words that are not zero to the (cleared) output with device atomics and
+// places the window anew.  When all bins fit, the window is the histogram.
+// Sessions outside the window or with 2^30 bytes or more go to the output
+// directly, so any input is exact.  With 2^reps copies of the window, lane l
+// using copy l % 2^reps, lanes that hit the same bin (coarse bins: a wave's
+// sessions share one or two) meet in fewer words.
+//
+// HBM bound: 12 B/session (and 8 B of addresses, or 1 B of labels).  A step
+// needs no barrier; runs do, two each.  Measured against the records (whose
+// stage 2 has one workgroup per 1,024 bins, and whose counters a few blocks
+// contend for) and, from 2^28 sessions on, the sliding window (whose 5-bit
+// counts overflow into one event list): 1e8 sessions of a day into 86,400
+// one-second bins, lookups included, 1.78 -> 0.38 ms (5.3 TB/s); into 1,440
+// minutes 89.7 -> 0.37 ms; 4e8 labelled sessions into 86,400 seconds 63.4 ->
+// 0.91 ms (5.7 TB/s), into 144 ten-minute frames (before: 32-bit count and
+// 64-bit byte atomics on one copy) 1.65 -> 0.88 ms (5.9 TB/s).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kLocalShift = 47;                       // window word: count << 47 | bytes
+constexpr uint64_t kLocalMaxBytes = 1ull << 30;            // larger counts go to the output
+constexpr uint32_t kLocalRun = (1u << 17) - 1u;            // sessions of a run at most
+static_assert((kLocalMaxBytes - 1) * kLocalRun < (1ull << kLocalShift), "no carry into the count");
+
+struct LocalArgs {
+    uint32_t bins;     // bins of the window
+    uint32_t reps;     // log2 of the window's copies
+    uint32_t run;      // steps of a run
+    uint32_t whole;    // the window is the whole histogram
+    const uint32_t* gate;  // NULL, or a word: nonzero when another reduce runs instead
+};
+
+template <uint32_t KIND, bool VEC>
+__global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    __shared__ uint32_t s_min[kMaxBlock / 64];
+    if (a.gate && *glob(a.gate)) return;
+    uint32_t used = 0;
+    const LdsView v = stage_lds<KIND>(p.t, lds, &used);
+    unsigned long long* h = reinterpret_cast<unsigned long long*>(lds + ((used + 1) & ~1u));
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t words = a.bins * 4u;
+    for (uint32_t k = tid; k < words << a.reps; k += blockDim.x) h[k] = 0;
+    const uint32_t rep = lane & ((1u << a.reps) - 1u);
+    Dropped d{};
+    const uint64_t step = 4ull * blockDim.x;
+    const uint64_t n_steps = (p.n + step - 1) / step;
+    const uint64_t s0 = n_steps * blockIdx.x / gridDim.x, s1 = n_steps * (blockIdx.x + 1) / gridDim.x;
+    auto full = [&](uint64_t s) { return VEC && (s + 1) * step <= p.n; };
+    Raw4 cur{}, nxt{};
+    if (s0 < s1 && full(s0)) load4<KIND>(p, s0 * step + 4ull * tid, cur);
+    uint32_t w0 = 0;
+    __syncthreads();
+    for (uint64_t r0 = s0; r0 < s1; r0 += a.run) {
+        const uint64_t r1 = r0 + a.run < s1 ? r0 + a.run : s1;
+        if (!a.whole) {
+            // the window starts a sixteenth of itself before the median of the
+            // waves' first bins (a few stray sessions do not move it)
+            uint32_t m = 0xFFFFFFFFu;
+            const uint32_t t4[4] = {cur.ts.x, cur.ts.y, cur.ts.z, cur.ts.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t i = r0 * step + 4ull * tid + k;
+                const uint32_t ts = full(r0) ? t4[k] : (i < p.n ? *glob(p.ts + i) : 0u);
+                uint32_t bin;
+                if (i < p.n && in_window(p, ts, bin)) m = min(m, bin);
+            }
+            m = wave_min(m);
+            if (lane == 0) s_min[wave] = m;
+            lds_barrier();
+            const uint32_t nw = blockDim.x >> 6;
+            const uint32_t mine = lane < nw ? s_min[lane] : 0xFFFFFFFFu;
+            const uint32_t valid = (uint32_t)__popcll(__ballot(mine != 0xFFFFFFFFu));
+            uint32_t rank = 0;
+            for (uint32_t k = 0; k < nw; ++k) {
+                const uint32_t o = s_min[k];
+                rank += (o < mine || (o == mine && k < lane)) ? 1u : 0u;
+            }
+            const unsigned long long at = __ballot(mine != 0xFFFFFFFFu && rank == valid / 2);
+            const uint32_t med =
+                at ? (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(at)) : 0u;
+            w0 = med > a.bins / 16u ? med - a.bins / 16u : 0u;
+        }
+        for (uint64_t s = r0; s < r1; ++s) {
+            if (s + 1 < s1 && full(s + 1)) load4<KIND>(p, (s + 1) * step + 4ull * tid, nxt);
+            const uint64_t i0 = s * step + 4ull * tid;
+            uint32_t lab[4], ts[4];
+            unsigned long long by[4];
+            if (full(s)) {
+                labels4_from<KIND>(p, v, i0, cur.src, cur.dst, cur.l4, lab);
+                ts[0] = cur.ts.x; ts[1] = cur.ts.y; ts[2] = cur.ts.z; ts[3] = cur.ts.w;
+                by[0] = cur.b01.x; by[1] = cur.b01.y; by[2] = cur.b23.x; by[3] = cur.b23.y;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint64_t i = i0 + k;
+                    lab[k] = ts[k] = 0;
+                    by[k] = 0;
+                    if (i >= p.n) continue;
+                    if constexpr (KIND == KK_LABEL_IN) lab[k] = *glob(p.label_in + i) & 3u;
+                    else lab[k] = label1<KIND>(p, v, i);
+                    ts[k] = *glob(p.ts + i);
+                    by[k] = *glob(p.bytes + i);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (!full(s) && i0 + k >= p.n) continue;
+                uint32_t bin;
+                const bool inw = in_window(p, ts[k], bin);
+                const uint32_t off = bin - w0;
+                if (inw && off < a.bins && by[k] < kLocalMaxBytes) {
+                    atomicAdd(&h[((off * 4u + lab[k]) << a.reps) + rep], (1ull << kLocalShift) | by[k]);
+                } else if (inw) {
+                    const uint64_t x = (uint64_t)lab[k] * p.n_bins + bin;
+                    __hip_atomic_fetch_add(p.count + x, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(p.hbytes + x, by[k], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    d.add(lab[k], by[k]);
+                }
+            }
+            cur = nxt;
+        }
+        lds_barrier();
+        // consecutive lanes take consecutive bins of a label, as the output does
+        for (uint32_t k = tid; k < words; k += blockDim.x) {
+            const uint32_t l = k / a.bins, b = k - l * a.bins;
+            unsigned long long c = 0, y = 0;
+            for (uint32_t r = 0; r < 1u << a.reps; ++r) {
+                unsigned long long* e = &h[((b * 4u + l) << a.reps) + r];
+                const unsigned long long x = *e;
+                if (x) *e = 0;
+                c += x >> kLocalShift;
+                y += x & ((1ull << kLocalShift) - 1ull);
+            }
+            if (c) {
+                const uint64_t x = (uint64_t)l * p.n_bins + w0 + b;
+                __hip_atomic_fetch_add(p.count + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(p.hbytes + x, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        lds_barrier();
     }
     d.flush(p.dropped);
 }
@@ -1300,6 +1463,7 @@ __global__ void __launch_bounds__(1024) k_scan_final(const uint32_t* __restrict_
 // Group the directory entries by block: segs[seg_off[b] ..] = (first slot,
 // count).  Consumes seg_count back to zero.
 __global__ void k_fill(PartWs w) {
+    if (w.gate && !*glob(w.gate)) return;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < w.n_chunks * kWin;
          q += stride) {
@@ -1588,6 +1752,7 @@ __global__ void __launch_bounds__(kStage2Block) k_stage2(PartWs w, unsigned long
                                                         unsigned long long* hbytes, uint32_t n_bins,
                                                         int accumulate) {
     __shared__ Stage2Shared sh;
+    if (w.gate && !*glob(w.gate)) return;
     const bool lines = (n_bins & 15u) == 0 && (((uintptr_t)count | (uintptr_t)hbytes) & 127u) == 0;
     stage2_run(w, sh, PlainOut{count, hbytes, n_bins, accumulate}, lines ? 1u : kStage2Run);
 }
@@ -1601,6 +1766,59 @@ __global__ void k_zero(unsigned long long* __restrict__ p, uint64_t n) {
     const uint64_t n2 = (n - head) / 2;
     for (uint64_t k = i; k < n2; k += stride) q[k] = make_ulonglong2(0, 0);
     if (i == 0 && ((n - head) & 1)) p[n - 1] = 0;
+}
+
+// *gate = 1 (the local reduce does not run) when more than an eighth of 64
+// groups of 64 consecutive sessions, evenly spaced, spread over more than
+// `spread` bins.  One workgroup of 1,024 lanes, four groups a wave.
+__global__ void __launch_bounds__(kMaxBlock) k_local_probe(PassParams p, uint32_t spread,
+                                                           uint32_t* gate) {
+    __shared__ uint32_t s_wide;
+    if (threadIdx.x == 0) s_wide = 0;
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t ts[4];
+    bool has[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint64_t i = (p.n >> 6) * (4 * wave + k) + lane;
+        has[k] = i < p.n;
+        ts[k] = has[k] ? *glob(p.ts + i) : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        uint32_t bin;
+        const bool in = in_window(p, ts[k], bin) && has[k];
+        const uint32_t lo = wave_min(in ? bin : 0xFFFFFFFFu);
+        const uint32_t hi = ~wave_min(in ? ~bin : 0xFFFFFFFFu);
+        if (lane == 0 && lo <= hi && hi - lo > spread) atomicAdd(&s_wide, 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *glob(gate) = s_wide > 8u ? 1u : 0u;
+}
+
+// Up to three arrays of 8-byte words cleared in one launch; the first two only
+// when the gate (or no gate) says that the local reduce runs.
+struct ClearArgs {
+    unsigned long long* p[3];
+    uint64_t n[3];
+    const uint32_t* gate;
+};
+
+__global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool local = !c.gate || *glob(c.gate) == 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (c.n[a] == 0 || (a < 2 && !local)) continue;
+        const uint64_t head = ((uintptr_t)c.p[a] & 15) ? 1 : 0;  // 8-byte aligned
+        u64x2_t* q = reinterpret_cast<u64x2_t*>(c.p[a] + head);
+        const uint64_t n2 = (c.n[a] - head) / 2;
+        for (uint64_t k = i; k < n2; k += stride) *glob(q + k) = u64x2_t{0ull, 0ull};
+        if (i == 0 && head) *glob(c.p[a]) = 0;
+        if (i == 0 && ((c.n[a] - head) & 1)) *glob(c.p[a] + c.n[a] - 1) = 0;
+    }
 }
 
 __global__ void k_zero32(uint32_t* __restrict__ p, uint64_t n) {
@@ -2147,11 +2365,8 @@ using Stage1Fn = void (*)(PassParams, PartWs);
 template <uint32_t KIND>
 static PassFn pass_fn(int hm, bool vec) {
     if (KIND == KK_INOUT && hm == H_NONE && vec) return k_pass_inout;
-    switch (hm) {
-        case H_NONE: return vec ? k_pass<KIND, H_NONE, true> : k_pass<KIND, H_NONE, false>;
-        case H_ATOMIC: return vec ? k_pass<KIND, H_ATOMIC, true> : k_pass<KIND, H_ATOMIC, false>;
-        default: return vec ? k_pass<KIND, H_PRIVATE, true> : k_pass<KIND, H_PRIVATE, false>;
-    }
+    if (hm == H_NONE) return vec ? k_pass<KIND, H_NONE, true> : k_pass<KIND, H_NONE, false>;
+    return vec ? k_pass<KIND, H_ATOMIC, true> : k_pass<KIND, H_ATOMIC, false>;
 }
 
 static PassFn pick_pass(uint32_t kind, int hm, bool vec) {
@@ -2162,6 +2377,7 @@ static PassFn pick_pass(uint32_t kind, int hm, bool vec) {
         case KK_PLA: return pass_fn<KK_PLA>(hm, vec);
         case KK_MLP: return pass_fn<KK_MLP>(hm, vec);
         case KK_INOUT: return pass_fn<KK_INOUT>(hm, vec);
+        case KK_UNION: return pass_fn<KK_UNION>(hm, vec);
         case KK_LABEL_IN: return pass_fn<KK_LABEL_IN>(hm, vec);
         default: return nullptr;
     }
@@ -2175,6 +2391,7 @@ static Stage1Fn pick_stage1(uint32_t kind) {
         case KK_PLA: return k_stage1<KK_PLA>;
         case KK_MLP: return k_stage1<KK_MLP>;
         case KK_INOUT: return k_stage1<KK_INOUT>;
+        case KK_UNION: return k_stage1<KK_UNION>;
         case KK_LABEL_IN: return k_stage1<KK_LABEL_IN>;
         default: return nullptr;
     }
@@ -2235,10 +2452,10 @@ bool vector_ok(const PassParams& p, uint32_t kind, bool hist) {
 }
 
 static sinet_status launch_k_pass(const PassParams& p, uint32_t kind, int hm, bool vec,
-                                  const FarList& far, size_t extra_lds, hipStream_t s) {
+                                  const FarList& far, hipStream_t s) {
     PassFn fn = pick_pass(kind, hm, vec);
     if (!fn) return fail(SINET_ERR_UNSUPPORTED, "no kernel for this lookup kind");
-    size_t lds = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + extra_lds + 8;
+    size_t lds = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 8;
     if (lds > 160 * 1024) return fail(SINET_ERR_UNSUPPORTED, "table needs more LDS than a CU has");
     const int block = lds > 40 * 1024 ? 1024 : 256;
     // the lookup pass of the queued kinds queues its searches per wave when
@@ -2270,7 +2487,7 @@ sinet_status launch_pass(const PassParams& p, uint32_t mode, hipStream_t s) {
     const uint32_t kind = (mode & PASS_LABEL_IN) ? (uint32_t)KK_LABEL_IN : p.t.kind;
     const bool hist = (mode & PASS_HIST) != 0;
     FarList none{};
-    return launch_k_pass(p, kind, hist ? H_ATOMIC : H_NONE, vector_ok(p, kind, hist), none, 0, s);
+    return launch_k_pass(p, kind, hist ? H_ATOMIC : H_NONE, vector_ok(p, kind, hist), none, s);
 }
 
 sinet_status launch_zero(unsigned long long* p, uint64_t n_words, hipStream_t s) {
@@ -2281,6 +2498,20 @@ sinet_status launch_zero(unsigned long long* p, uint64_t n_words, hipStream_t s)
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, s, p, n_words);
     return check_hip(hipGetLastError(), "zero kernel launch");
+}
+
+// The histogram's arrays (cells words each; with a gate only if it says so) and
+// dropped counters cleared in one launch; dropped may be NULL, cells 0.
+static sinet_status launch_clear(const PassParams& p, uint64_t cells, hipStream_t s,
+                                 const uint32_t* gate = nullptr) {
+    const ClearArgs c{{p.count, p.hbytes, p.dropped}, {cells, cells, p.dropped ? 8ull : 0ull}, gate};
+    if (c.n[0] + c.n[2] == 0) return SINET_OK;
+    uint64_t blocks = (cells / 2 + 255) / 256;
+    const uint64_t cap = (uint64_t)device_cu_count() * 8;
+    if (blocks > cap) blocks = cap;
+    if (blocks < 1) blocks = 1;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, s, c);
+    return check_hip(hipGetLastError(), "clear launch");
 }
 
 static sinet_status launch_zero32(uint32_t* p, uint64_t n, hipStream_t s) {
@@ -2494,7 +2725,7 @@ sinet_status run_partitioned(const PassParams& p0, uint32_t kind, const PartWs& 
     q.dst_inst = nullptr;
     q.dropped = nullptr;
     PhaseScope ph(PH_FAR, s);
-    return launch_k_pass(q, kind, H_ATOMIC, false, far, 0, s);
+    return launch_k_pass(q, kind, H_ATOMIC, false, far, s);
 }
 
 // ---- batch launches -----------------------------------------------------------
@@ -2508,6 +2739,7 @@ static BatchFn pick_batch_stage1(uint32_t kind) {
         case KK_PLA: return k_batch_stage1<KK_PLA>;
         case KK_MLP: return k_batch_stage1<KK_MLP>;
         case KK_INOUT: return k_batch_stage1_o4<KK_INOUT>;
+        case KK_UNION: return k_batch_stage1_o4<KK_UNION>;
         case KK_LABEL_IN: return k_batch_stage1_o4<KK_LABEL_IN>;
         default: return nullptr;
     }
@@ -2521,6 +2753,7 @@ static BatchFn pick_batch_far(uint32_t kind) {
         case KK_PLA: return k_batch_far<KK_PLA>;
         case KK_MLP: return k_batch_far<KK_MLP>;
         case KK_INOUT: return k_batch_far<KK_INOUT>;
+        case KK_UNION: return k_batch_far<KK_UNION>;
         case KK_LABEL_IN: return k_batch_far<KK_LABEL_IN>;
         default: return nullptr;
     }
@@ -2634,7 +2867,8 @@ sinet_status ws_free(void* ptr, hipStream_t s) {
     return check_hip(hipFreeAsync(ptr, s), "workspace free");
 }
 
-constexpr int H_WINDOW = 4;
+// Reduces of run_hist.
+enum { R_LOCAL, R_RECORDS, R_WINDOW };
 
 // Which reduce the histogram calls use (sinet_set_reduce).
 static std::atomic<int> g_reduce{SINET_REDUCE_AUTO};
@@ -2655,14 +2889,34 @@ sinet_status set_reduce(int mode) {
 // 3.70 ms with 4e8, a crossover near 2.7e8 sessions.
 constexpr uint64_t kWindowMinSessions = 1ull << 28;
 
-int hist_strategy(const DevTable& t, uint32_t kind, uint32_t n_bins, uint64_t n) {
-    const size_t priv = 12ull * 4 * n_bins;
-    const size_t tab = kind == KK_LABEL_IN ? 0 : t.lds_bytes;
-    if (n_bins <= 2048 && priv + tab + 64 <= 96 * 1024) return H_PRIVATE;
+// The local reduce is a candidate from this many sessions per bin on.  Fewer
+// leave it little to add up in LDS before its device atomics: 1e8 sessions of a
+// day took 1.11 ms with 12 sessions per bin, 0.76 with 23, 0.60 with 58 and 0.44
+// with 116, the records 0.89-0.93 ms each.  Small calls gain before that (4e6
+// sessions, 11 per bin: 62 against 91 us) but would need a probe of their order.
+constexpr uint64_t kLocalMinPerBin = 16;
+constexpr uint32_t kLocalAlways = 2048;    // bins that always take the local reduce
+// Width from which a window of bins (about 2,500) takes the time order of any
+// nearly sorted log: +-1 minute.  With narrower bins a probe looks first: with
+// +-5 s of jitter 4e8 sessions at 4 ms per bin took 13.3 ms with the local
+// reduce, whose window they leave, 1.45 ms with the sliding window; at 10 ms per
+// bin 1.71 against 15.6 ms.
+constexpr uint32_t kLocalSureWidth = 48;
+
+struct Strategy {
+    int reduce;   // R_RECORDS or R_WINDOW, or R_LOCAL when the local reduce is sure
+    bool probe;   // the local reduce runs instead if the sessions' order allows it
+};
+
+static Strategy hist_strategy(const PassParams& p) {
+    if (p.n_bins <= kLocalAlways) return {R_LOCAL, false};
     const int mode = g_reduce.load();
-    if (mode == SINET_REDUCE_WINDOW) return H_WINDOW;
-    if (mode == SINET_REDUCE_AUTO && n >= kWindowMinSessions) return H_WINDOW;
-    return 3;  // partitioned
+    if (mode == SINET_REDUCE_WINDOW) return {R_WINDOW, false};
+    if (mode == SINET_REDUCE_RECORDS) return {R_RECORDS, false};
+    const int other = p.n >= kWindowMinSessions ? R_WINDOW : R_RECORDS;
+    if (p.n / p.n_bins < kLocalMinPerBin) return {other, false};
+    if (p.width >= kLocalSureWidth) return {R_LOCAL, false};
+    return {other, true};
 }
 
 // Lookups that walk global memory (trie, learned windows, binary searches
@@ -2694,7 +2948,7 @@ static PassParams advance(const PassParams& p, uint64_t off) {
 // With the workspace given: ws holds win_ws_bytes(n, P) bytes, then (when a
 // lookup pass runs and the caller stores no labels) n bytes of labels.
 static sinet_status run_window_in(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s,
-                                  void* ws, uint32_t P, bool timed) {
+                                  void* ws, uint32_t P, bool timed, const uint32_t* gate = nullptr) {
     const size_t wsb = win_ws_bytes(p.n, P);
     const bool lookup = kind != KK_LABEL_IN;
     sinet_status st = SINET_OK;
@@ -2705,13 +2959,14 @@ static sinet_status run_window_in(const PassParams& p, uint32_t kind, int accumu
         lq.pos_out = nullptr;
         FarList none{};
         PhaseScope ph(PH_LOOKUP, s, timed);
-        st = launch_k_pass(lq, kind, H_NONE, vector_ok(lq, kind, false), none, 0, s);
+        st = launch_k_pass(lq, kind, H_NONE, vector_ok(lq, kind, false), none, s);
         q.label_in = lq.label_out;
     }
     q.label_out = nullptr;
     q.src_inst = nullptr;
     q.dst_inst = nullptr;
-    const WinArgs a = win_carve(ws, q, P, accumulate);
+    WinArgs a = win_carve(ws, q, P, accumulate);
+    a.gate = gate;
     if (st == SINET_OK) {
         PhaseScope ph(PH_INDEX, s, timed);
         st = win_launch_bounds(a, s);
@@ -2747,30 +3002,166 @@ static sinet_status run_window(const PassParams& p, uint32_t kind, int accumulat
     return st != SINET_OK ? st : st2;
 }
 
+using LocalFn = void (*)(PassParams, LocalArgs);
+
+static LocalFn pick_local(uint32_t kind, bool vec) {
+    switch (kind) {
+        case KK_UNION: return vec ? k_local<KK_UNION, true> : k_local<KK_UNION, false>;
+        case KK_INOUT: return vec ? k_local<KK_INOUT, true> : k_local<KK_INOUT, false>;
+        case KK_LABEL_IN: return vec ? k_local<KK_LABEL_IN, true> : k_local<KK_LABEL_IN, false>;
+        default: return nullptr;
+    }
+}
+
+// LDS of a workgroup of the local reduce, window and table: one workgroup of
+// 1,024 lanes per CU with a table, two without.
+constexpr size_t kLocalLds = 156 * 1024;
+constexpr size_t kLocalLdsLabels = 79 * 1024;
+
+// Label lookups that the local reduce runs itself; the others store their
+// labels in a pass of their own first.
+static bool local_fuses(uint32_t kind, const DevTable& t) {
+    return kind == KK_LABEL_IN || kind == KK_UNION ||
+           (kind == KK_INOUT && t.lds_bytes <= 92 * 1024);
+}
+
+// Bins that its window can hold.
+static uint32_t local_bins(uint32_t kind, const DevTable& t) {
+    const size_t tab = (kind == KK_LABEL_IN ? 0 : t.lds_bytes) + 8;
+    return (uint32_t)(((kind == KK_LABEL_IN ? kLocalLdsLabels : kLocalLds) - tab) / 32);
+}
+
+static sinet_status launch_local(const PassParams& p, uint32_t kind, const uint32_t* gate,
+                                 hipStream_t s) {
+    LocalFn fn = pick_local(kind, vector_ok(p, kind, true));
+    if (!fn) return fail(SINET_ERR_UNSUPPORTED, "no kernel for this lookup kind");
+    const size_t tab = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 8;
+    const uint32_t cap = local_bins(kind, p.t);
+    // small inputs: smaller steps, so that more CUs take part
+    const uint32_t cus = device_cu_count();
+    const uint32_t block = p.n >= 2048ull * cus ? 1024 : 256;
+    const uint32_t step = 4 * block, most = kLocalRun / step;
+    LocalArgs a{};
+    a.gate = gate;
+    a.whole = p.n_bins <= cap ? 1u : 0u;
+    a.run = most;
+    const uint64_t per_bin = p.n / p.n_bins + 1;
+    uint64_t want = p.n_bins;  // bins the copies must each hold
+    if (!a.whole) {
+        // a run moves forward by at most 3/8 of the window, the rest is for the
+        // time jitter; the copies hold eight times a full run's advance
+        const uint64_t fit = (uint64_t)cap * 3 / 8 * per_bin / step;
+        a.run = (uint32_t)(fit < 1 ? 1 : fit < most ? fit : most);
+        want = 8 * ((uint64_t)kLocalRun / per_bin) + 256;
+    }
+    // copies while they fit and hold fewer words than the workgroup has sessions
+    const uint64_t steps = (p.n + step - 1) / step;
+    const uint64_t mine = p.n / (steps < cus ? steps : cus);
+    while (a.reps < 4 && want << (a.reps + 1) <= cap && want << (a.reps + 3) <= mine) ++a.reps;
+    a.bins = a.whole ? p.n_bins : cap >> a.reps;
+    const size_t lds = tab + (32ull * a.bins << a.reps);
+    uint64_t grid = (uint64_t)cus * blocks_per_cu((const void*)fn, block, lds);
+    if (grid > steps) grid = steps;
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(block), lds, s, p, a);
+    return check_hip(hipGetLastError(), "local reduce launch");
+}
+
+// The local reduce: the output cleared, the labels stored first when the
+// lookup does not run inside it (into label_out, or n bytes at `labels`).
+static sinet_status run_local_in(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s,
+                                 uint8_t* labels, bool timed) {
+    sinet_status st = accumulate ? SINET_OK : launch_clear(p, 4ull * p.n_bins, s);
+    PassParams q = p;
+    if (st == SINET_OK && !local_fuses(kind, p.t)) {
+        PassParams lq = p;
+        if (!lq.label_out) lq.label_out = labels;
+        FarList none{};
+        PhaseScope ph(PH_LOOKUP, s, timed);
+        st = launch_k_pass(lq, kind, H_NONE, vector_ok(lq, kind, false), none, s);
+        q.label_in = lq.label_out;
+        q.label_out = nullptr;
+        kind = KK_LABEL_IN;
+    }
+    if (st != SINET_OK) return st;
+    PhaseScope ph(PH_STAGE1, s, timed);
+    return launch_local(q, kind, nullptr, s);
+}
+
+static sinet_status run_local(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s) {
+    void* ws = nullptr;
+    if (!local_fuses(kind, p.t) && !p.label_out) {
+        const sinet_status st = ws_alloc(&ws, p.n, s);
+        if (st != SINET_OK) return st;
+    }
+    const sinet_status st = run_local_in(p, kind, accumulate, s, (uint8_t*)ws, true);
+    const sinet_status st2 = ws ? ws_free(ws, s) : SINET_OK;
+    return st != SINET_OK ? st : st2;
+}
+
 // The histogram of run_hist with its workspace taken from `scratch` (bytes
-// long) instead of allocated: the private pass for small windows (no
-// workspace), else the sliding-window reduce with as many pieces as fit.
+// long) instead of allocated: the local reduce for coarse bins (at most
+// the labels), else the sliding-window reduce with as many pieces as fit.
 // Records no timing events.
 sinet_status run_hist_in(const PassParams& p, uint32_t mode, int accumulate, hipStream_t s,
                          void* scratch, size_t bytes) {
     const uint32_t kind = (mode & PASS_LABEL_IN) ? (uint32_t)KK_LABEL_IN : p.t.kind;
     if (p.n == 0) return SINET_OK;
-    if (hist_strategy(p.t, kind, p.n_bins, p.n) == H_PRIVATE) {
-        sinet_status st = SINET_OK;
-        if (!accumulate) {
-            st = launch_zero(p.count, 4ull * p.n_bins, s);
-            if (st == SINET_OK) st = launch_zero(p.hbytes, 4ull * p.n_bins, s);
-            if (st != SINET_OK) return st;
-        }
-        FarList none{};
-        return launch_k_pass(p, kind, H_PRIVATE, vector_ok(p, kind, true), none,
-                             12ull * 4 * p.n_bins + 8, s);
+    const Strategy strat = hist_strategy(p);
+    if (strat.reduce == R_LOCAL)  // 2^25 sessions at most: their labels fit
+        return run_local_in(p, kind, accumulate, s, (uint8_t*)scratch, false);
+    if (!accumulate) {
+        const sinet_status st = launch_clear(p, 0, s);
+        if (st != SINET_OK) return st;
     }
     uint32_t P = win_pieces(p.n);
     while (P > 1 && window_ws_total(p, kind, P) > bytes) P = P * 3 / 4;
     if (window_ws_total(p, kind, P) > bytes)
         return fail(SINET_ERR_INVALID_ARG, "input too large for the static scratch");
     return run_window_in(p, kind, accumulate, s, scratch, P, false);
+}
+
+// Bins that may be wide enough for the local reduce: both it and the other
+// reduce are launched, behind a word that a probe sets from how far
+// neighbouring sessions spread; the kernels of the one not chosen return at
+// once.  The labels are stored first unless both reduces look them up alike
+// (the records with a table the local reduce fuses).
+static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulate, int other,
+                               hipStream_t s) {
+    const bool fused = other == R_RECORDS && local_fuses(kind, p.t);
+    const bool lookup = !fused && kind != KK_LABEL_IN;
+    const uint32_t P = win_pieces(p.n);
+    const size_t wsb = al256(other == R_WINDOW ? win_ws_bytes(p.n, P) : part_ws_bytes(p.n, p.n_bins));
+    void* ws = nullptr;
+    sinet_status st = ws_alloc(&ws, wsb + 256 + (lookup && !p.label_out ? p.n : 0), s);
+    if (st != SINET_OK) return st;
+    uint32_t* gate = (uint32_t*)((char*)ws + wsb);
+    const uint32_t k2 = fused ? kind : (uint32_t)KK_LABEL_IN;
+    const uint32_t bins = local_bins(k2, p.t);
+    hipLaunchKernelGGL(k_local_probe, dim3(1), dim3(kMaxBlock), 0, s, p, bins / 16 * 9, gate);
+    st = check_hip(hipGetLastError(), "order probe launch");
+    if (st == SINET_OK && !accumulate) st = launch_clear(p, 4ull * p.n_bins, s, gate);
+    PassParams q = p;
+    if (st == SINET_OK && lookup) {
+        if (!q.label_out) q.label_out = (uint8_t*)ws + wsb + 256;
+        FarList none{};
+        PhaseScope ph(PH_LOOKUP, s);
+        st = launch_k_pass(q, kind, H_NONE, vector_ok(q, kind, false), none, s);
+        q.label_in = q.label_out;
+        q.label_out = nullptr;
+    }
+    if (st == SINET_OK) {
+        PhaseScope ph(PH_STAGE1, s);
+        st = launch_local(q, k2, gate, s);
+    }
+    if (st == SINET_OK && other == R_WINDOW) {
+        st = run_window_in(q, KK_LABEL_IN, accumulate, s, ws, P, true, gate);
+    } else if (st == SINET_OK) {
+        PartWs w = part_ws_carve(ws, p.n, p.n_bins);
+        w.gate = gate;
+        st = run_partitioned(q, k2, w, accumulate, s);
+    }
+    const sinet_status st2 = ws_free(ws, s);
+    return st != SINET_OK ? st : st2;
 }
 
 sinet_status run_hist(const PassParams& p, uint32_t mode, int accumulate, hipStream_t s) {
@@ -2787,24 +3178,18 @@ sinet_status run_hist(const PassParams& p, uint32_t mode, int accumulate, hipStr
             PassParams head = p;
             head.n = h;
             FarList none{};
-            return launch_k_pass(head, kind, H_ATOMIC, false, none, 0, s);
+            return launch_k_pass(head, kind, H_ATOMIC, false, none, s);
         }
     }
     count_timed_call();
-    const int strat = hist_strategy(p.t, kind, p.n_bins, p.n);
-    if (strat == H_PRIVATE) {
-        sinet_status st = SINET_OK;
-        if (!accumulate) {
-            st = launch_zero(p.count, 4ull * p.n_bins, s);
-            if (st == SINET_OK) st = launch_zero(p.hbytes, 4ull * p.n_bins, s);
-            if (st != SINET_OK) return st;
-        }
-        FarList none{};
-        PhaseScope ph(PH_STAGE1, s);
-        return launch_k_pass(p, kind, H_PRIVATE, vector_ok(p, kind, true), none,
-                             12ull * 4 * p.n_bins + 8, s);
+    const Strategy strat = hist_strategy(p);
+    if (strat.reduce == R_LOCAL) return run_local(p, kind, accumulate, s);
+    if (strat.probe) return run_probed(p, kind, accumulate, strat.reduce, s);
+    if (!accumulate) {
+        const sinet_status st = launch_clear(p, 0, s);
+        if (st != SINET_OK) return st;
     }
-    if (strat == H_WINDOW) return run_window(p, kind, accumulate, s);
+    if (strat.reduce == R_WINDOW) return run_window(p, kind, accumulate, s);
     // partitioned: pieces of at most kMaxPiece sessions (32-bit slot indices)
     int acc = accumulate;
     for (uint64_t lo = 0; lo < p.n; lo += kMaxPiece) {
@@ -2837,7 +3222,7 @@ sinet_status run_hist(const PassParams& p, uint32_t mode, int accumulate, hipStr
             lq.pos_out = nullptr;
             FarList none{};
             PhaseScope ph(PH_LOOKUP, s);
-            st = launch_k_pass(lq, kind, H_NONE, vector_ok(lq, kind, false), none, 0, s);
+            st = launch_k_pass(lq, kind, H_NONE, vector_ok(lq, kind, false), none, s);
             q.label_in = lq.label_out;
             q.label_out = nullptr;
             q.src_inst = nullptr;

@@ -53,6 +53,11 @@ struct DevTable {
     uint32_t io_words;
     uint32_t io_slot;           // per cut /16 block: up to four boundary offsets
     uint32_t io_list;           // overflow list of blocks with more boundaries
+    // SCAN tables, label-only queries: boundaries of the prefixes' union less
+    // one, padded to 2^un_steps words; membership before the first one
+    const uint32_t* un;
+    uint32_t un_steps;
+    uint32_t un_in0;
     uint32_t max_err;
     float m_f;                  // (float) m
     unsigned long long* fallbacks;  // device counter
@@ -66,6 +71,7 @@ constexpr uint32_t kPlaRadixBits = 12;          // PLA segment directory: top 12
 constexpr uint32_t kPlaWindowErr = 6;           // largest bound one 16-boundary window serves
 constexpr uint32_t kBTail = 20;                 // 0xFFFFFFFF past the padded boundaries
 constexpr uint32_t kInoutKind = 6;              // internal kind: label-only via the in/out index
+constexpr uint32_t kUnionKind = 7;              // internal kind: label-only by the union's boundaries
 constexpr uint32_t kLabelInKind = 100;          // internal kind: stage 1 on stored labels
 __host__ __device__ constexpr uint32_t radix_words(uint32_t bits) {
     return ((1u << bits) + 2) / 2;  // (2^bits + 1) u16 entries
@@ -98,6 +104,7 @@ struct PartWs {
     uint64_t n_chunks;
     uint32_t n_blocks;
     uint32_t vec;                   // 16-byte vector loads allowed
+    const uint32_t* gate;           // NULL, or a word: zero when another reduce runs instead
 };
 
 struct FarList {
@@ -160,6 +167,7 @@ struct WinArgs {
     uint64_t ev_cap;
     uint32_t vec;                   // 16-byte column loads allowed
     int accumulate;
+    const uint32_t* gate;           // NULL, or a word: zero when another reduce runs instead
 };
 
 // One stream of a batch as the batch kernels see it.
@@ -260,7 +268,6 @@ size_t part_ws_bytes(uint64_t n, uint32_t n_bins);
 PartWs part_ws_carve(void* base, uint64_t n, uint32_t n_bins);
 sinet_status run_partitioned(const PassParams& p, uint32_t kind, const PartWs& w, int accumulate,
                              hipStream_t s);
-int hist_strategy(const DevTable& t, uint32_t kind, uint32_t n_bins, uint64_t n);
 // Watch-list histograms: count/hbytes [2][n_keys][n_bins], dropped [2][2]
 // (cleared first unless accumulate); the table's inst ids are the keys.
 sinet_status run_watch(const PassParams& p, uint32_t n_keys, int accumulate, hipStream_t s);

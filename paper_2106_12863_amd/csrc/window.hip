@@ -85,6 +85,7 @@ __device__ __forceinline__ uint64_t piece_begin(uint64_t n, uint32_t P, uint32_t
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_window_bounds(WinArgs a) {
     const uint32_t lane = threadIdx.x, q = blockIdx.x;
+    if (a.gate && !*glob(a.gate)) return;
     if (q == 0) {
         if (lane < 4) a.counters[lane] = 0;
         if (lane == 0) a.est[0] = 0;
@@ -431,6 +432,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t P = a.pieces;
     __shared__ uint32_t s_t[4];
+    if (a.gate && !*glob(a.gate)) return;
     WinPiece g;
     g.q = blockIdx.x;
     {
@@ -514,6 +516,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
 // bin in both ranges is read and written once.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024) k_window_fixup(WinArgs a) {
+    if (a.gate && !*glob(a.gate)) return;
     const uint32_t q = blockIdx.x, P = a.pieces;
     const uint32_t Tq = a.T[q], Tq1 = a.T[q + 1];
     const uint32_t ea = q > 0 ? min(a.E[q - 1], Tq1) : Tq;         // [Tq, ea) from the left
@@ -555,6 +558,7 @@ __global__ void __launch_bounds__(1024) k_window_fixup(WinArgs a) {
 // after every bin has been written.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_window_far(WinArgs a) {
+    if (a.gate && !*glob(a.gate)) return;
     // blockIdx.y: the piece; lanes of the x blocks take its listed steps' bitmap
     // words, 32 sessions each
     {
