@@ -379,8 +379,9 @@ sinet_status sinet_batch_plan_destroy(sinet_batch_plan* plan);
  * in *n_bad.  *n_lines receives the number of lines.  The kernels read whole
  * aligned 16-byte groups of text and stay inside [text, text + len).
  * Errors: INVALID_ARG (NULL pointer, more lines than out->n: *n_lines then
- * holds the number needed), UNSUPPORTED (text of 2^47 bytes or more),
- * OUT_OF_MEMORY (the line index, 8 bytes per line).  Synchronous. */
+ * holds the number needed, and the columns the first out->n lines),
+ * UNSUPPORTED (text of 2^46 bytes or more), OUT_OF_MEMORY (8 bytes per 31 KB
+ * of text).  Synchronous. */
 sinet_status sinet_parse_sessions(const uint8_t* text, uint64_t len, int32_t origin_days,
                                   sinet_columns* out, uint64_t* n_lines, uint64_t* n_bad,
                                   hipStream_t stream);

@@ -9,167 +9,95 @@
 // origin, an octet above 255 or a byte count above 2^64 - 1 gives
 // ts = 0xFFFFFFFF, src = dst = bytes = 0 and counts as bad.
 //
-// Three passes over the text:
-//   k_count_lines  newlines per 64 KB block (coalesced 16-byte loads);
-//   k_scan_counts  one workgroup: exclusive sums of the block counts;
-//   k_line_starts  every newline's position + 1 written at its line number;
-//   k_parse        a workgroup takes 256 consecutive lines, stages their bytes
-//                  in LDS with coalesced loads (as many whole lines at a time
-//                  as fit in 64 KB), builds a bitmap of the staged commas
-//                  (16 bytes per lane) and each lane finds its line's field
-//                  bounds in the bitmap and parses the fields from LDS (a line
-//                  longer than the staging is read from device memory
-//                  directly).
+// k_parse reads the text once.  A workgroup takes a block of kOwn bytes, in
+// order (a ticket each), and looks at the kWindow - kOwn bytes after it too: 64
+// bytes per lane, classified in registers and staged in LDS.  The positions of
+// the delimiters (',' and '\n') are compacted into LDS by rank, so a line, which
+// starts after a delimiter that is a newline, finds the ends of its fields by
+// index.  A lane per line then parses the four fields with four-byte reads and
+// byte dot products.  A line whose fields leave the window (or a window with
+// more delimiters or lines than the lists hold) is parsed from device memory.
+// The number of newlines before a block comes from the blocks before it: each
+// publishes its own count at once, then the count up to its end, and one wave
+// adds up its predecessors' counts back to the nearest such sum while the
+// others parse.  A block waits only for lower tickets, whose holders publish
+// their counts before they wait, so the lowest unfinished block never waits and
+// every wait ends.
+//
+// Bound by vector issue (620 instructions per 4 KB wave, 1.0 ms of the 1.8),
+// then HBM.  3.9 GB of text, 2e7 lines: 4.22 ms with a counting pass, an index
+// of line starts and a pass over staged lines; 2.41 with a counting pass and
+// this kernel; 2.29 with the byte-permute classification instead of zero-byte
+// arithmetic; 2.10 with the counts found by the kernel itself; 1.84 ms (2.4
+// TB/s) with the search for them beside the parsing.  Persistent workgroups
+// that fetched their next block early took 4.30 ms: a ticket taken early
+// publishes its count late.
+// The block that holds a newline owns the line after it; the first block owns
+// the first line.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "pass_common.h"
 #include "sinet.h"
 #include "sinet_internal.h"
 
 namespace sinet {
 namespace {
 
-constexpr int kParseBlock = 256;
-constexpr uint64_t kScanBytes = 64 * 1024;    // text bytes per counting block
-constexpr uint32_t kStageBytes = 64 * 1024;   // LDS staging of a workgroup's lines
+constexpr int kParseBlock = 512;
+constexpr uint32_t kWindow = 64 * kParseBlock;  // text bytes a workgroup looks at
+constexpr uint32_t kOwn = kWindow - 1024;       // of which it owns the newlines
+constexpr uint32_t kOwnLanes = kOwn / 64;       // lanes whose bytes it owns
+static_assert(kOwn % 64 == 0, "a lane's bytes are owned or not");
+// state of a block: its newlines (its own, or up to its end) and what they are
+constexpr uint64_t kOwnCount = 1ull << 62, kSumCount = 2ull << 62, kCountMask = kOwnCount - 1;
+constexpr uint32_t kDelims = 6144;              // delimiters listed (25 per line of 200 bytes: 4,100)
+constexpr uint32_t kLines = 1024;               // newlines listed
 constexpr uint32_t kBadTs = 0xFFFFFFFFu;
 
-__device__ __forceinline__ uint32_t nl_in(uint4 v) {
-    uint32_t c = 0;
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) c += ((w[k] >> (8 * b)) & 0xFFu) == 10u ? 1u : 0u;
-    return c;
+// The text as whole 16-byte groups: position x (from the aligned address at or
+// below the text) holds text byte x - skew.
+struct Text {
+    const uint8_t* base;  // 16-byte aligned; bytes [skew, end) are the text
+    uint32_t skew;
+    uint64_t end;
+};
+
+// The 16 bytes from position x (a multiple of 16); bytes outside the text are
+// 0 and are not read.
+__device__ __forceinline__ uint4 group16(const Text& t, uint64_t x) {
+    if (x >= t.skew && x + 16 <= t.end) {
+        const u32x4_t v = *glob(reinterpret_cast<const u32x4_t*>(t.base + x));
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    for (uint32_t b = 0; b < 16; ++b)
+        if (x + b >= t.skew && x + b < t.end) w[b >> 2] |= (uint32_t)*glob(t.base + x + b) << (8 * (b & 3u));
+    return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// Newlines of block blockIdx.x ([blk * kScanBytes, +kScanBytes) of the text).
-__global__ void __launch_bounds__(kParseBlock) k_count_lines(const uint8_t* __restrict__ text,
-                                                             uint64_t len, uint64_t* __restrict__ counts,
-                                                             uint32_t vec) {
-    __shared__ uint32_t s_sum;
-    if (threadIdx.x == 0) s_sum = 0;
-    __syncthreads();
-    const uint64_t b0 = (uint64_t)blockIdx.x * kScanBytes;
-    const uint64_t b1 = b0 + kScanBytes < len ? b0 + kScanBytes : len;
-    uint32_t c = 0;
-    if (vec) {
-        for (uint64_t p = b0 + 16 * (uint64_t)threadIdx.x; p < b1; p += 16 * kParseBlock) {
-            if (p + 16 <= b1) {
-                c += nl_in(*reinterpret_cast<const uint4*>(text + p));
-            } else {
-                for (uint64_t q = p; q < b1; ++q) c += text[q] == 10 ? 1u : 0u;
-            }
-        }
-    } else {
-        for (uint64_t p = b0 + threadIdx.x; p < b1; p += kParseBlock) c += text[p] == 10 ? 1u : 0u;
-    }
-    atomicAdd(&s_sum, c);
-    __syncthreads();
-    if (threadIdx.x == 0) counts[blockIdx.x] = s_sum;
+// Per byte of w: 0x00 where it is the character C, else 0xFF.  A byte permute
+// takes its selectors from the text: selector 12 gives 0x00, every other one
+// 0xFF when all the bytes it may select (and their signs) are ones, and the
+// exclusive or moves C to 12.
+template <uint32_t C>
+__device__ __forceinline__ uint32_t not_char(uint32_t w) {
+    return __builtin_amdgcn_perm(0xFFFFFFFFu, 0xFFFFFFFFu, w ^ (0x01010101u * (C ^ 12u)));
 }
 
-// Exclusive sums of n counts in place, total in counts[n] (one workgroup):
-// each 1024-count step scans within waves (shuffles), then adds the totals
-// of the waves before and of the steps before.
-__global__ void __launch_bounds__(1024) k_scan_counts(uint64_t* __restrict__ counts, uint32_t n) {
-    __shared__ uint64_t s_wave[16];
-    __shared__ uint64_t s_carry;
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    for (uint32_t base = 0; base < n; base += 1024) {
-        const uint32_t i = base + threadIdx.x;
-        const uint64_t x = i < n ? counts[i] : 0ull;
-        uint64_t incl = x;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint64_t y = __shfl_up(incl, d);
-            if (lane >= (uint32_t)d) incl += y;
-        }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        uint64_t before = s_carry, total = 0;
-        for (uint32_t w = 0; w < 16; ++w) {
-            if (w < wave) before += s_wave[w];
-            total += s_wave[w];
-        }
-        if (i < n) counts[i] = before + incl - x;
-        __syncthreads();  // every lane has read s_wave and s_carry
-        if (threadIdx.x == 0) s_carry += total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) counts[n] = s_carry;
+// Low eight bits: which of the eight bytes of lo and hi are C.  Flags of 0 and
+// -1 times the weights 1, 2, .. 64, -128 sum to minus the mask of the other
+// bytes (modulo 256); starting from -1 leaves its complement.
+template <uint32_t C>
+__device__ __forceinline__ uint32_t chars8(uint32_t lo, uint32_t hi) {
+    const int m = __builtin_amdgcn_sdot4((int)not_char<C>(lo), 0x08040201, -1, false);
+    return (uint32_t)__builtin_amdgcn_sdot4((int)not_char<C>(hi), (int)0x80402010u, m, false);
 }
 
-// starts[k + 1] = position after the k-th newline (starts[0] = 0).  Each step
-// of a block reads 64 contiguous bytes per lane (four 16-byte loads); a
-// lane's newlines are numbered after the ones of the lanes before it (wave
-// scan, then the waves in order).
-__device__ __forceinline__ uint64_t nl_bits16(uint4 v) {  // bit i: byte i of v is '\n'
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint64_t m = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            m |= (uint64_t)(((w[k] >> (8 * q)) & 0xFFu) == 10u ? 1u : 0u) << (4 * k + q);
-    return m;
-}
-
-__global__ void __launch_bounds__(kParseBlock) k_line_starts(const uint8_t* __restrict__ text,
-                                                             uint64_t len,
-                                                             const uint64_t* __restrict__ first,
-                                                             uint64_t* __restrict__ starts,
-                                                             uint32_t vec) {
-    __shared__ uint32_t s_wave[kParseBlock / 64];
-    __shared__ uint64_t s_base;
-    const uint64_t b0 = (uint64_t)blockIdx.x * kScanBytes;
-    const uint64_t b1 = b0 + kScanBytes < len ? b0 + kScanBytes : len;
-    if (threadIdx.x == 0) {
-        s_base = first[blockIdx.x];
-        if (blockIdx.x == 0) starts[0] = 0;
-    }
-    __syncthreads();
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    for (uint64_t st = b0; st < b1; st += 64 * kParseBlock) {
-        const uint64_t p = st + 64 * (uint64_t)threadIdx.x;
-        uint64_t mask = 0;  // bit q: byte p + q is a newline
-        if (vec && p + 64 <= b1) {
-            const uint4* v = reinterpret_cast<const uint4*>(text + p);
-            const uint4 v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
-            mask = nl_bits16(v0) | nl_bits16(v1) << 16 | nl_bits16(v2) << 32 | nl_bits16(v3) << 48;
-        } else {
-            for (int q = 0; q < 64; ++q)
-                if (p + q < b1 && text[p + q] == 10) mask |= 1ull << q;
-        }
-        const uint32_t c = (uint32_t)__popcll(mask);
-        uint32_t incl = c;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t y = (uint32_t)__shfl_up((int)incl, d);
-            if (lane >= (uint32_t)d) incl += y;
-        }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        uint64_t before = s_base;
-        uint32_t step_total = 0;
-        for (uint32_t w = 0; w < kParseBlock / 64; ++w) {
-            if (w < wave) before += s_wave[w];
-            step_total += s_wave[w];
-        }
-        uint64_t k = before + (incl - c);  // newlines before this lane's first
-        while (mask) {
-            const uint32_t q = (uint32_t)__builtin_ctzll(mask);
-            starts[k + 1] = p + q + 1;
-            ++k;
-            mask &= mask - 1;
-        }
-        __syncthreads();  // every lane has read s_wave and s_base
-        if (threadIdx.x == 0) s_base += step_total;
-        __syncthreads();
-    }
+// Bit i: byte i of the 16 bytes v is C.
+template <uint32_t C>
+__device__ __forceinline__ uint32_t chars16(uint4 v) {
+    return __builtin_amdgcn_perm(chars8<C>(v.z, v.w), chars8<C>(v.x, v.y), 0x0C0C0400u);
 }
 
 // days since 1970-01-01 of a proleptic Gregorian date (H. Hinnant's
@@ -197,14 +125,15 @@ struct LdsLine {
     }
 };
 
-// Byte access to one line in device memory (lines too long for the staging):
+// Byte access to one line in device memory (lines that leave their window):
 // bytes only, never past the line.
 struct GlobalLine {
     const uint8_t* p;
     __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return p[i]; }
     __device__ __forceinline__ uint32_t upto(uint32_t i, uint32_t e) const { return i < e ? p[i] : 0xFFu; }
-    __device__ __forceinline__ uint32_t comma(uint32_t c, uint32_t n) const {
-        while (c < n && p[c] != ',') ++c;
+    // the first ',' or '\n' in [c, n), or n
+    __device__ __forceinline__ uint32_t delim(uint32_t c, uint32_t n) const {
+        while (c < n && p[c] != ',' && p[c] != 10) ++c;
         return c;
     }
 };
@@ -221,6 +150,24 @@ __device__ __forceinline__ bool dec(const Bytes& b, uint32_t at, int n, int32_t&
     return true;
 }
 
+// The date and time of day as milliseconds from the origin day's midnight;
+// false for an impossible one or one outside [0, 2^32 - 1).
+__device__ __forceinline__ bool time_of(int32_t y, int32_t mo, int32_t d, int32_t h, int32_t mi, int32_t se,
+                                        int32_t ms, int64_t origin, uint32_t& ts) {
+    if (mo < 1 || mo > 12 || d < 1) return false;
+    const bool leap = (y % 4 == 0 && y % 100 != 0) || y % 400 == 0;
+    // days in month: 31 except April, June, September, November (30) and February
+    const int32_t dim = mo == 2 ? (leap ? 29 : 28) : ((mo == 4 || mo == 6 || mo == 9 || mo == 11) ? 30 : 31);
+    if (d > dim || h > 23 || mi > 59 || se > 59) return false;
+    // a day before the origin's is negative, the 50th after it past 2^32
+    const int64_t day = (int64_t)days_from_civil(y, mo, d) - origin;
+    if (day < 0 || day > 49) return false;
+    const uint64_t t = (uint64_t)(uint32_t)day * 86400000u + (uint32_t)(h * 3600000 + mi * 60000 + se * 1000 + ms);
+    if (t >= kBadTs) return false;
+    ts = (uint32_t)t;
+    return true;
+}
+
 template <class Bytes>
 __device__ __forceinline__ bool capture_time(const Bytes& b, uint32_t s, uint32_t e, int64_t origin, uint32_t& ts) {
     if (e - s != 23) return false;
@@ -231,16 +178,7 @@ __device__ __forceinline__ bool capture_time(const Bytes& b, uint32_t s, uint32_
     if (!dec(b, s, 4, y) || !dec(b, s + 5, 2, mo) || !dec(b, s + 8, 2, d) || !dec(b, s + 11, 2, h) ||
         !dec(b, s + 14, 2, mi) || !dec(b, s + 17, 2, se) || !dec(b, s + 20, 3, ms))
         return false;
-    if (mo < 1 || mo > 12 || d < 1) return false;
-    const bool leap = (y % 4 == 0 && y % 100 != 0) || y % 400 == 0;
-    // days in month: 31 except April, June, September, November (30) and February
-    const int32_t dim = mo == 2 ? (leap ? 29 : 28) : ((mo == 4 || mo == 6 || mo == 9 || mo == 11) ? 30 : 31);
-    if (d > dim || h > 23 || mi > 59 || se > 59) return false;
-    const int64_t t = ((int64_t)days_from_civil(y, mo, d) - origin) * 86400000 + h * 3600000 +
-                      mi * 60000 + se * 1000 + ms;
-    if (t < 0 || t >= (int64_t)kBadTs) return false;
-    ts = (uint32_t)t;
-    return true;
+    return time_of(y, mo, d, h, mi, se, ms, origin, ts);
 }
 
 template <class Bytes>
@@ -301,224 +239,308 @@ __device__ __forceinline__ bool count_u64(const Bytes& b, uint32_t s, uint32_t e
     return true;
 }
 
-// Parse the line [0, n) of b; false for a bad line.
-template <class Bytes>
-__device__ __forceinline__ bool parse_line(const Bytes& b, uint32_t n, int64_t origin, uint32_t& ts, uint32_t& src,
-                           uint32_t& dst, uint64_t& nbytes) {
+// Parse the line of b that ends at its first newline or at n; false for a bad
+// line.
+__device__ __forceinline__ bool parse_line(const GlobalLine& b, uint32_t n, int64_t origin, uint32_t& ts,
+                                           uint32_t& src, uint32_t& dst, uint64_t& nbytes) {
     uint32_t s = 0;
     for (int f = 1; f <= 21; ++f) {
-        const uint32_t c = b.comma(s, n);
+        // a capture time is 23 bytes: a longer first field is not read on
+        const uint32_t c = b.delim(s, f == 1 ? min(n, 24u) : n);
         // field f is [s, c)
         if (f == 1 && !capture_time(b, s, c, origin, ts)) return false;
         if (f == 5 && !ipv4(b, s, c, src)) return false;
         if (f == 8 && !ipv4(b, s, c, dst)) return false;
         if (f == 21) return count_u64(b, s, c, nbytes);
-        if (c >= n) return false;  // the line ended before field 21
+        if (c >= n || b[c] == 10) return false;  // the line ended before field 21
         s = c + 1;
     }
     return false;
 }
 
-// Bit i of the result: byte i of the 16 bytes v is ','.  The zero-byte test
-// is exact per byte: for x = word ^ 0x2C2C2C2C, bit 7 of each byte of
-// ((x & 0x7F7F7F7F) + 0x7F7F7F7F) | x is set exactly when that byte of x is
-// not zero (the sums stay inside their bytes).  The four words' flags are
-// gathered first (bit 8 b + q: byte b of word q), then packed to 16 bits
-// (bit 4 b + q) and the 4 x 4 bit matrix is transposed (bit 4 q + b).
-__device__ __forceinline__ uint32_t comma_bits16(uint4 v) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t s = 0;
+// One line of the window, parsed from the staged text and its delimiters.
+// Reads of up to three bytes before a field stay inside the line, of up to
+// three after one inside the staging (16 bytes of slack).
+struct Staged {
+    const uint8_t* text;
+    __device__ __forceinline__ uint32_t word(uint32_t at) const {  // any alignment
+        uint32_t w;
+        __builtin_memcpy(&w, text + at, 4);
+        return w;
+    }
+};
+
+// Nonzero when a byte of x (digits less '0' by exclusive or) is above 9.
+__device__ __forceinline__ uint32_t not_digits(uint32_t x) { return (x | (x + 0x76767676u)) & 0x80808080u; }
+
+// Field 1 at s, 23 bytes: same rules as capture_time.
+__device__ __forceinline__ bool staged_time(const Staged& b, uint32_t s, int64_t origin, uint32_t& ts) {
+    constexpr uint32_t z = 0x30303030u;
+    const uint32_t w0 = b.word(s), w1 = b.word(s + 4), w2 = b.word(s + 8), w3 = b.word(s + 12),
+                   w4 = b.word(s + 16), w5 = b.word(s + 20);
+    // "YYYY" "/MM/" "DD h" "h:MM" ":SS." "mmm,"
+    const uint32_t seps = ((w1 ^ 0x2F00002Fu) & 0xFF0000FFu) | ((w2 ^ 0x00200000u) & 0x00FF0000u) |
+                          ((w3 ^ 0x00003A00u) & 0x0000FF00u) | ((w4 ^ 0x2E00003Au) & 0xFF0000FFu);
+    const uint32_t x0 = w0 ^ z, x1 = (w1 ^ z) & 0x00FFFF00u, x2 = (w2 ^ z) & 0xFF00FFFFu,
+                   x3 = (w3 ^ z) & 0xFFFF00FFu, x4 = (w4 ^ z) & 0x00FFFF00u, x5 = (w5 ^ z) & 0x00FFFFFFu;
+    const uint32_t bad = seps | not_digits(x0) | not_digits(x1) | not_digits(x2) | not_digits(x3) |
+                         not_digits(x4) | not_digits(x5);
+    if (bad) return false;
+    auto dot = [](uint32_t x, uint32_t w, uint32_t c) { return __builtin_amdgcn_udot4(x, w, c, false); };
+    const int32_t y = (int32_t)(dot(x0, 0x0000010Au, 0u) * 100u + dot(x0, 0x010A0000u, 0u));
+    const int32_t mo = (int32_t)dot(x1, 0x00010A00u, 0u), d = (int32_t)dot(x2, 0x0000010Au, 0u);
+    const int32_t h = (int32_t)dot(x2, 0x0A000000u, x3 & 0xFFu), mi = (int32_t)dot(x3, 0x010A0000u, 0u);
+    const int32_t se = (int32_t)dot(x4, 0x00010A00u, 0u), ms = (int32_t)dot(x5, 0x00010A64u, 0u);
+    return time_of(y, mo, d, h, mi, se, ms, origin, ts);
+}
+
+// Four digits or fewer that end before `end`: the last k of them (1 to 4).
+__device__ __forceinline__ uint32_t last_digits(const Staged& b, uint32_t end, uint32_t k, uint32_t& bad) {
+    const uint32_t x = (b.word(end - 4) ^ 0x30303030u) & (0xFFFFFFFFu << (8u * (4u - k)));
+    bad |= not_digits(x);
+    return __builtin_amdgcn_udot4(x, 0x0000010Au, 0u, false) * 100u +
+           __builtin_amdgcn_udot4(x, 0x010A0000u, 0u, false);
+}
+
+// A dotted quad in [s, e): same rules as ipv4.
+__device__ __forceinline__ bool staged_ipv4(const Staged& b, uint32_t s, uint32_t e, uint32_t& a) {
+    const uint32_t n = e - s;
+    if (n < 7u || n > 15u) return false;
+    // bit i: byte i of the field is '.'
+    uint32_t m = chars16<'.'>(make_uint4(b.word(s), b.word(s + 4), b.word(s + 8), b.word(s + 12)));
+    m &= (1u << n) - 1u;
+    if (__popc(m) != 3) return false;
+    uint32_t bad = 0, v = 0, at = 0;  // at: the octet's first byte
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t x = w[q] ^ 0x2C2C2C2Cu;
-        const uint32_t t = ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x;  // bit 7 of a byte: not a comma
-        s |= (t >> (7 - q)) & (0x01010101u << q);
+    for (int part = 0; part < 4; ++part) {
+        const uint32_t end = part < 3 ? (uint32_t)__builtin_ctz(m) : n, k = end - at;
+        bad |= k - 1u > 2u ? 1u : 0u;
+        const uint32_t o = last_digits(b, s + end, min(max(k, 1u), 4u), bad);
+        bad |= o > 255u ? 1u : 0u;
+        v = (v << 8) | (o & 255u);
+        at = end + 1;
+        m &= m - 1u;
     }
-    s ^= 0x0F0F0F0Fu;
-    uint32_t y = (s | (s >> 4)) & 0x00FF00FFu;
-    y = (y | (y >> 8)) & 0xFFFFu;
-    uint32_t t = (y ^ (y >> 3)) & 0x0A0Au;
-    y ^= t ^ (t << 3);
-    t = (y ^ (y >> 6)) & 0x00CCu;
-    y ^= t ^ (t << 6);
-    return y;
+    a = v;
+    return bad == 0u;
 }
 
-// Position of the r-th (1-based) set bit of m, r <= popcount(m).
-__device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t r) {
-    uint32_t pos = 0;
-    uint32_t c = (uint32_t)__popc(m & 0xFFFFu);
-    if (r > c) { r -= c; m >>= 16; pos += 16; }
-    c = (uint32_t)__popc(m & 0xFFu);
-    if (r > c) { r -= c; m >>= 8; pos += 8; }
-    c = (uint32_t)__popc(m & 0xFu);
-    if (r > c) { r -= c; m >>= 4; pos += 4; }
-    c = (uint32_t)__popc(m & 0x3u);
-    if (r > c) { r -= c; m >>= 2; pos += 2; }
-    return pos + (r > (m & 1u) ? 1u : 0u);
-}
-
-// parse_line for a line staged in LDS at staging bytes [b0, b1), with the
-// staging's comma bitmap (bit i of word j: staged byte 32 j + i is ',').
-// The line's bitmap words give its comma count and, for commas 1, 4, 7 and
-// 20, the word that holds each and its rank there; commas 5, 8 and 21 are
-// the next set bits after 4, 7 and 20 (comma 21 is the line's end when the
-// line has exactly 20).  Field f is [comma f-1 + 1, comma f).  Same rules as
-// parse_line.
-__device__ __forceinline__ bool parse_line_lds(const uint8_t* stage, const uint32_t* bits, uint32_t b0,
-                                               uint32_t b1, int64_t origin, uint32_t& ts, uint32_t& src,
-                                               uint32_t& dst, uint64_t& nbytes) {
-    if (b1 <= b0) return false;  // an empty line has one field
-    const uint32_t w0 = b0 >> 5, w1 = (b1 - 1) >> 5;
-    const uint32_t lo = 0xFFFFFFFFu << (b0 & 31u);
-    const uint32_t hi = 0xFFFFFFFFu >> (31u - ((b1 - 1) & 31u));
-    auto word = [&](uint32_t w) {  // the line's commas in bitmap word w
-        uint32_t m = bits[w];
-        if (w == w0) m &= lo;
-        if (w == w1) m &= hi;
-        return m;
-    };
-    uint32_t k = 0;  // commas in the words before w
-    uint32_t wa = 0, ra = 0, wb = 0, rb = 0, wc = 0, rc = 0, wd = 0, rd = 0;
-    for (uint32_t w = w0; w <= w1; ++w) {
-        const uint32_t c = (uint32_t)__popc(word(w));
-        // comma t is in word w when k < t <= k + c
-        if (0u - k < c) { wa = w; ra = 1u - k; }
-        if (3u - k < c) { wb = w; rb = 4u - k; }
-        if (6u - k < c) { wc = w; rc = 7u - k; }
-        if (19u - k < c) { wd = w; rd = 20u - k; }
-        k += c;
+// 1 to 20 decimal digits in [s, e): same rules as count_u64.
+__device__ __forceinline__ bool staged_count(const Staged& b, uint32_t s, uint32_t e, uint64_t& out) {
+    const uint32_t n = e - s;
+    if (n < 1u || n > 20u) return false;
+    if (n == 20u) return count_u64(LdsLine{b.text}, s, e, out);
+    uint32_t bad = 0;
+    uint64_t v = 0, p10 = 1;
+    for (uint32_t k = 0; k < n; k += 4) {  // from the last four digits on
+        v += p10 * last_digits(b, e - k, min(n - k, 4u), bad);
+        p10 *= 10000u;
     }
-    if (k < 20) return false;  // fewer than 21 fields
-    // stage position of the first comma after bit q of word w, or b1
-    auto after = [&](uint32_t w, uint32_t q) {
-        uint32_t m = word(w) & (0xFFFFFFFEu << q);
-        while (!m && w < w1) m = word(++w);
-        return m ? 32 * w + (uint32_t)__builtin_ctz(m) : b1;
-    };
-    const uint32_t q1 = nth_bit(word(wa), ra), q4 = nth_bit(word(wb), rb);
-    const uint32_t q7 = nth_bit(word(wc), rc), q20 = nth_bit(word(wd), rd);
-    const uint32_t c1 = 32 * wa + q1 - b0, c4 = 32 * wb + q4 - b0, c5 = after(wb, q4) - b0;
-    const uint32_t c7 = 32 * wc + q7 - b0, c8 = after(wc, q7) - b0;
-    const uint32_t c20 = 32 * wd + q20 - b0, c21 = after(wd, q20) - b0;
-    const LdsLine b{stage + b0};
-    return capture_time(b, 0u, c1, origin, ts) && ipv4(b, c4 + 1, c5, src) &&
-           ipv4(b, c7 + 1, c8, dst) && count_u64(b, c20 + 1, c21, nbytes);
+    out = v;
+    return bad == 0u;
 }
 
 struct ParseArgs {
-    const uint8_t* text;
-    uint64_t len;
-    const uint64_t* starts;  // [n_nl + 1]
-    uint64_t n_nl;           // newlines
-    uint64_t n_lines;        // n_nl, + 1 for a last line without newline
+    Text t;
+    unsigned long long* state;  // [blocks], zero at first
+    unsigned long long* total;  // newlines
+    unsigned long long* bad;    // bad lines
+    uint32_t* ticket;
+    uint32_t n_blocks;
+    uint64_t cap;               // lines the columns hold
     int64_t origin;
     uint32_t* ts;
     uint32_t* src;
     uint32_t* dst;
     uint64_t* bytes;
-    unsigned long long* bad;
 };
 
+// Newlines before block b, by one wave: lanes read 64 blocks' states at a time,
+// from b - 1 down, until every block after the nearest sum has its count.
+__device__ __forceinline__ uint64_t newlines_before(const ParseArgs& a, uint32_t b, uint32_t lane) {
+    uint64_t sum = 0;
+    for (int64_t top = (int64_t)b - 1; top >= 0; top -= 64) {
+        const int64_t i = top - (int64_t)lane;
+        uint64_t x, sums;
+        for (;;) {
+            x = i >= 0 ? __hip_atomic_load(a.state + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kSumCount;
+            sums = __ballot(x >= kSumCount);
+            const uint64_t none = __ballot(x < kOwnCount);
+            // ready when no lane before the nearest sum (or none at all) is empty
+            if ((none & (sums ? (sums & -sums) - 1 : ~0ull)) == 0) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        const uint32_t last = sums ? (uint32_t)__builtin_ctzll(sums) : 63u;
+        uint64_t v = lane <= last ? x & kCountMask : 0ull;
+#pragma unroll
+        for (int o = 32; o; o >>= 1) v += __shfl_xor(v, o);
+        sum += v;
+        if (sums) break;
+    }
+    return sum;
+}
+
+// The line from position s on, from device memory.
+__device__ __forceinline__ bool line_slow(const ParseArgs& a, uint64_t s, uint32_t& ts, uint32_t& src,
+                                          uint32_t& dst, uint64_t& nb) {
+    const uint64_t n = a.t.end - s;
+    return parse_line(GlobalLine{a.t.base + s}, n < 0xFFFFFFFFull ? (uint32_t)n : 0xFFFFFFFEu, a.origin, ts,
+                      src, dst, nb);
+}
+
+__device__ __forceinline__ uint32_t put_line(const ParseArgs& a, uint64_t l, bool ok, uint32_t ts,
+                                             uint32_t src, uint32_t dst, uint64_t nb) {
+    if (l >= a.cap) return 0u;  // the call is refused then
+    a.ts[l] = ok ? ts : kBadTs;
+    a.src[l] = ok ? src : 0u;
+    a.dst[l] = ok ? dst : 0u;
+    a.bytes[l] = ok ? nb : 0ull;
+    return ok ? 0u : 1u;
+}
+
 __global__ void __launch_bounds__(kParseBlock) k_parse(ParseArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t stage[kStageBytes + 16];
-    __shared__ uint32_t s_comma[kStageBytes / 32];  // bit i of word j: stage[32 j + i] is ','
-    __shared__ uint64_t s_start[kParseBlock], s_end[kParseBlock];  // the group's line bytes
-    // start and end of the bytes of this lane's line in the group at l0x
-    // (0, 0 past the last line); the next group's are loaded while this
-    // group is parsed
-    auto bounds = [&](uint64_t l0x, uint64_t& xs, uint64_t& xg) {
-        const uint64_t lx = l0x + threadIdx.x;
-        xs = xg = 0;
-        if (lx < a.n_lines) {
-            xs = a.starts[lx];
-            xg = lx < a.n_nl ? a.starts[lx + 1] : a.len;
+    __shared__ __attribute__((aligned(16))) uint8_t s_text[kWindow + 16];
+    __shared__ uint16_t s_delim[kDelims];             // positions in the window, ascending
+    __shared__ uint16_t s_start[kLines], s_rank[kLines];  // per newline: position + 1, its delimiter rank
+    __shared__ uint32_t s_wave[kParseBlock / 64];
+    __shared__ uint32_t s_blk, s_own;
+    __shared__ uint64_t s_base;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    if (tid == 0) s_blk = atomicAdd(a.ticket, 1u);
+    __syncthreads();
+    const uint32_t blk = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_blk);  // below n_blocks, the grid
+    const uint64_t b0 = (uint64_t)blk * kOwn;
+    uint32_t bad = 0;
+    uint4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = group16(a.t, b0 + 64u * tid + 16 * k);
+    // 64 bytes: delimiter and newline masks, the bytes to LDS
+    uint64_t dm = 0, nm = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        reinterpret_cast<uint4*>(s_text)[4 * tid + k] = v[k];
+        const uint32_t n = chars16<10>(v[k]), d = n | chars16<','>(v[k]);
+        dm |= (uint64_t)d << (16 * k);
+        nm |= (uint64_t)n << (16 * k);
+    }
+    // ranks: delimiters in the low half, newlines in the high half
+    const uint32_t mine = (uint32_t)__popcll(dm) | (uint32_t)__popcll(nm) << 16;
+    uint32_t incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, o);
+        if (lane >= (uint32_t)o) incl += y;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before = incl - mine, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kParseBlock / 64; ++w) {
+        const uint32_t x = s_wave[w];
+        if (w < wave) before += x;
+        total += x;
+    }
+    const uint32_t n_delim = total & 0xFFFFu, n_nl = total >> 16;
+    const bool at_end = b0 + kWindow >= a.t.end;  // nothing follows the window
+    if (tid == kOwnLanes - 1) {  // the block's own newlines, known to its successors from here on
+        s_own = (before + mine) >> 16;
+        __hip_atomic_store(a.state + blk, kOwnCount | s_own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the last wave finds the newlines before the block
+    auto place = [&]() {
+        if (wave != kParseBlock / 64 - 1) return;
+        const uint64_t sum = newlines_before(a, blk, lane);
+        if (lane == 0) {
+            const uint64_t upto = sum + s_own;
+            s_base = sum;
+            __hip_atomic_store(a.state + blk, kSumCount | upto, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (blk + 1 == a.n_blocks) *a.total = upto;
         }
     };
-    const uint64_t stride = (uint64_t)gridDim.x * kParseBlock;
-    uint64_t ns = 0, ng = 0;
-    bounds((uint64_t)blockIdx.x * kParseBlock, ns, ng);
-    for (uint64_t l0 = (uint64_t)blockIdx.x * kParseBlock; l0 < a.n_lines; l0 += stride) {
-        const uint64_t l1 = l0 + kParseBlock < a.n_lines ? l0 + kParseBlock : a.n_lines;
-        const uint64_t l = l0 + threadIdx.x;
-        // this lane's line [s, e) (without its newline) and the end of its bytes
-        const uint64_t s = ns, g = ng;
-        const uint64_t e = l < l1 ? (l < a.n_nl ? g - 1 : a.len) : 0;
-        if (l0 + stride < a.n_lines) bounds(l0 + stride, ns, ng);
-        s_start[threadIdx.x] = s;
-        s_end[threadIdx.x] = g;  // read after the first barrier below
-        uint32_t ts = kBadTs, src = 0, dst = 0;
+    if (n_nl > kLines) {
+        // more lines than the list holds (shorter than 32 bytes on average, so
+        // nearly all are bad): each lane parses those after its own newlines
+        place();
+        __syncthreads();
+        uint64_t l = s_base + (before >> 16) + 1;
+        for (uint64_t m = nm; m; m &= m - 1, ++l) {
+            const uint32_t q = 64u * tid + (uint32_t)__builtin_ctzll(m);
+            const uint64_t s = b0 + q + 1;
+            if (tid >= kOwnLanes || s >= a.t.end) continue;
+            uint32_t ts = 0, src = 0, dst = 0;
+            uint64_t nb = 0;
+            const bool ok = line_slow(a, s, ts, src, dst, nb);
+            bad += put_line(a, l, ok, ts, src, dst, nb);
+        }
+        if (blk == 0 && tid == 0) {
+            uint32_t ts = 0, src = 0, dst = 0;
+            uint64_t nb = 0;
+            const bool ok = line_slow(a, a.t.skew, ts, src, dst, nb);
+            bad += put_line(a, 0, ok, ts, src, dst, nb);
+        }
+    } else {
+        uint32_t r = before & 0xFFFFu;
+        if (n_delim > kDelims && r + 64u > kDelims) {  // the list ends in this lane's bytes, or has ended
+            for (uint64_t m = dm; m && r < kDelims; m &= m - 1, ++r)
+                s_delim[r] = (uint16_t)(64u * tid + (uint32_t)__builtin_ctzll(m));
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                for (uint32_t m = (uint32_t)(dm >> (32 * h)); m; m &= m - 1u, ++r)
+                    s_delim[r] = (uint16_t)(64u * tid + 32u * h + (uint32_t)__builtin_ctz(m));
+        }
+        uint32_t k = before >> 16;
+        for (uint64_t m = nm; m; m &= m - 1, ++k) {
+            const uint32_t q = (uint32_t)__builtin_ctzll(m);
+            s_start[k] = (uint16_t)(64u * tid + q + 1u);
+            s_rank[k] = (uint16_t)((before & 0xFFFFu) + (uint32_t)__popcll(dm & ((1ull << q) - 1ull)));
+        }
+        __syncthreads();
+        const uint32_t n_own = s_own, lead = blk == 0 ? 1u : 0u;
+        uint32_t ts = 0, src = 0, dst = 0;
         uint64_t nb = 0;
         bool ok = false;
-        // lines [next, l1) are left; each step stages the longest prefix of
-        // them whose bytes fit in LDS (line ends grow with l, so the lanes
-        // that fit are a prefix), or parses one line too long for the
-        // staging from device memory
-        __syncthreads();
-        for (uint64_t next = l0; next < l1;) {
-            const uint64_t a0 = s_start[next - l0] & ~15ull;  // 16-byte aligned copy start
-            const bool fits = l >= next && l < l1 && g - a0 <= kStageBytes;
-            const uint64_t n_fit = (uint64_t)__syncthreads_count(fits ? 1 : 0);
-            if (n_fit == 0) {
-                if (l == next && e - s < 0xFFFFFFFFull)  // longer lines are bad
-                    ok = parse_line(GlobalLine{a.text + s}, (uint32_t)(e - s), a.origin, ts, src, dst, nb);
-                next += 1;
-                continue;
-            }
-            const uint64_t m = next + n_fit;  // lines [next, m) are staged
-            const uint64_t g1 = s_end[m - 1 - l0];
-            const uint64_t full = (g1 - a0) / 16;
-            if ((((uintptr_t)a.text) & 15u) == 0) {
-                // four 16-byte loads of the lane in flight before its LDS writes
-                const uint4* src4 = reinterpret_cast<const uint4*>(a.text + a0);
-                uint4* dst4 = reinterpret_cast<uint4*>(stage);
-                for (uint64_t k = threadIdx.x; k < full; k += 4 * kParseBlock) {
-                    const uint64_t q1 = k + kParseBlock, q2 = k + 2 * kParseBlock,
-                                   q3 = k + 3 * kParseBlock;
-                    const uint4 r0 = src4[k];
-                    const uint4 r1 = q1 < full ? src4[q1] : r0;
-                    const uint4 r2 = q2 < full ? src4[q2] : r0;
-                    const uint4 r3 = q3 < full ? src4[q3] : r0;
-                    dst4[k] = r0;
-                    if (q1 < full) dst4[q1] = r1;
-                    if (q2 < full) dst4[q2] = r2;
-                    if (q3 < full) dst4[q3] = r3;
+        // line r0 of the block into ts .. ok; false when there is none
+        auto one = [&](uint32_t r0) -> bool {
+            if (r0 >= n_own + lead) return false;
+            // list entry i is the newline before the line (none: the first line)
+            const uint32_t i = r0 - lead;
+            const bool top = r0 < lead;
+            const uint32_t s = top ? a.t.skew : (uint32_t)s_start[i];
+            if (b0 + s >= a.t.end) return false;  // nothing after the text's last newline
+            const uint32_t d0 = top ? 0u : (uint32_t)s_rank[i] + 1u;  // rank of the line's first delimiter
+            const uint32_t nx = top ? 0u : i + 1u;                    // the next newline's entry
+            const uint32_t dn = nx < n_nl ? (uint32_t)s_rank[nx] : n_delim;
+            const bool seen = nx < n_nl || at_end;  // the line's end is in the window
+            if (d0 + 20u < min(n_delim, kDelims) || (seen && min(dn + 1u, n_delim) <= kDelims)) {
+                // every delimiter the line needs is listed, or its last one is
+                ok = dn - d0 >= 20u;  // 20 commas before its newline
+                if (ok) {
+                    const uint32_t c1 = s_delim[d0], c4 = s_delim[d0 + 3], c5 = s_delim[d0 + 4];
+                    const uint32_t c7 = s_delim[d0 + 6], c8 = s_delim[d0 + 7], c20 = s_delim[d0 + 19];
+                    const uint32_t c21 = d0 + 20u < n_delim ? (uint32_t)s_delim[d0 + 20]
+                                                            : (uint32_t)(a.t.end - b0);
+                    const Staged b{s_text};
+                    ok = c1 - s == 23u && staged_time(b, s, a.origin, ts) &&
+                         staged_ipv4(b, c4 + 1, c5, src) && staged_ipv4(b, c7 + 1, c8, dst) &&
+                         staged_count(b, c20 + 1, c21, nb);
                 }
             } else {
-                for (uint64_t k = threadIdx.x; k < 16 * full; k += kParseBlock) stage[k] = a.text[a0 + k];
+                ok = line_slow(a, b0 + s, ts, src, dst, nb);
             }
-            for (uint64_t k = a0 + 16 * full + threadIdx.x; k < g1; k += kParseBlock)
-                stage[k - a0] = a.text[k];
-            __syncthreads();
-            // the comma bitmap of the staged bytes, 16 bytes per lane at a time
-            // (bits past g1 are stale and lie outside every staged line)
-            const uint32_t n_chunk = (uint32_t)((g1 - a0 + 15) / 16);
-            for (uint32_t c = threadIdx.x; c < n_chunk; c += kParseBlock) {
-                reinterpret_cast<uint16_t*>(s_comma)[c] =
-                    (uint16_t)comma_bits16(reinterpret_cast<const uint4*>(stage)[c]);
-            }
-            __syncthreads();
-            if (l >= next && l < m)
-                ok = parse_line_lds(stage, s_comma, (uint32_t)(s - a0), (uint32_t)(e - a0), a.origin, ts,
-                                    src, dst, nb);
-            __syncthreads();  // the staging is free for the next step
-            next = m;
-        }
-        if (l < l1) {
-            if (!ok) {
-                ts = kBadTs;
-                src = dst = 0;
-                nb = 0;
-            }
-            a.ts[l] = ts;
-            a.src[l] = src;
-            a.dst[l] = dst;
-            a.bytes[l] = nb;
-        }
-        // also keeps s_start / s_end until every lane is past the group
-        const int n_bad = __syncthreads_count(l < l1 && !ok ? 1 : 0);
-        if (threadIdx.x == 0 && n_bad) atomicAdd(a.bad, (unsigned long long)n_bad);
+            return true;
+        };
+        // the first kParseBlock lines are parsed while the last wave still finds
+        // the block's line number
+        place();
+        const bool has = one(tid);
+        __syncthreads();
+        const uint64_t l0 = s_base + 1u - lead;
+        if (has) bad += put_line(a, l0 + tid, ok, ts, src, dst, nb);
+        for (uint32_t r0 = tid + kParseBlock; one(r0); r0 += kParseBlock)
+            bad += put_line(a, l0 + r0, ok, ts, src, dst, nb);
     }
+    if (bad) atomicAdd(a.bad, (unsigned long long)bad);
 }
 
 }  // namespace
@@ -528,67 +550,36 @@ sinet_status parse_sessions(const uint8_t* text, uint64_t len, int64_t origin, c
     *n_lines = 0;
     *n_bad = 0;
     if (len == 0) return SINET_OK;
-    const uint64_t n_blocks = (len + kScanBytes - 1) / kScanBytes;
-    if (n_blocks >= (1ull << 31)) return fail(SINET_ERR_UNSUPPORTED, "text above 2^47 bytes");
-    uint64_t* counts = nullptr;
-    unsigned long long* bad = nullptr;
-    uint64_t* starts = nullptr;
-    hipError_t e = hipMallocAsync((void**)&counts, 8 * (n_blocks + 1), s);
-    if (e == hipSuccess) e = hipMallocAsync((void**)&bad, 8, s);
-    sinet_status st = check_hip(e, "parse workspace");
-    auto release = [&]() {
-        if (counts) (void)hipFreeAsync(counts, s);
-        if (bad) (void)hipFreeAsync(bad, s);
-        if (starts) (void)hipFreeAsync(starts, s);
-    };
-    if (st != SINET_OK) {
-        release();
-        return st;
-    }
-    const uint32_t vec = (((uintptr_t)text) & 15u) == 0 ? 1u : 0u;
-    hipLaunchKernelGGL(k_count_lines, dim3((unsigned)n_blocks), dim3(kParseBlock), 0, s, text, len,
-                       counts, vec);
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, counts, (uint32_t)n_blocks);
-    uint64_t n_nl = 0;
+    const uint32_t skew = (uint32_t)((uintptr_t)text & 15u);
+    const Text t{text - skew, skew, skew + len};
+    const uint64_t n_blocks = (t.end + kOwn - 1) / kOwn;
+    if (n_blocks >= (1ull << 31)) return fail(SINET_ERR_UNSUPPORTED, "text above 2^46 bytes");
+    // block states, newlines, bad lines, ticket
+    unsigned long long* ws = nullptr;
+    sinet_status st = check_hip(hipMallocAsync((void**)&ws, 8 * (n_blocks + 3), s), "parse workspace");
+    if (st != SINET_OK) return st;
+    st = launch_zero(ws, n_blocks + 3, s);
+    uint64_t out2[2] = {0, 0};
     uint8_t last = 0;
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&n_nl, counts + n_blocks, 8, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&last, text + len - 1, 1, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    st = check_hip(e, "parse line count");
-    if (st != SINET_OK) {
-        release();
-        return st;
-    }
-    const uint64_t lines = n_nl + (last != 10 ? 1 : 0);
-    *n_lines = lines;
-    if (lines > out->n) {
-        release();
-        return fail(SINET_ERR_INVALID_ARG, "output columns hold fewer sessions than the text has lines");
-    }
-    e = hipMallocAsync((void**)&starts, 8 * (n_nl + 1), s);
-    if (e == hipSuccess) e = hipMemsetAsync(bad, 0, 8, s);
-    st = check_hip(e, "parse workspace");
     if (st == SINET_OK) {
-        hipLaunchKernelGGL(k_line_starts, dim3((unsigned)n_blocks), dim3(kParseBlock), 0, s, text, len,
-                           counts, starts, vec);
-        ParseArgs a{text, len, starts, n_nl, lines, origin,
-                    const_cast<uint32_t*>(out->ts), const_cast<uint32_t*>(out->src),
-                    const_cast<uint32_t*>(out->dst), const_cast<uint64_t*>(out->bytes), bad};
-        uint64_t grid = (lines + kParseBlock - 1) / kParseBlock;
-        const uint64_t cap = (uint64_t)device_cu_count() * 8;
-        if (grid > cap) grid = cap;
-        if (grid < 1) grid = 1;
-        hipLaunchKernelGGL(k_parse, dim3((unsigned)grid), dim3(kParseBlock), 0, s, a);
-        unsigned long long nb = 0;
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpyAsync(&nb, bad, 8, hipMemcpyDeviceToHost, s);
+        const ParseArgs a{t, ws, ws + n_blocks, ws + n_blocks + 1, (uint32_t*)(ws + n_blocks + 2),
+                          (uint32_t)n_blocks, out->n, origin,
+                          const_cast<uint32_t*>(out->ts), const_cast<uint32_t*>(out->src),
+                          const_cast<uint32_t*>(out->dst), const_cast<uint64_t*>(out->bytes)};
+        hipLaunchKernelGGL(k_parse, dim3((unsigned)n_blocks), dim3(kParseBlock), 0, s, a);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(out2, ws + n_blocks, 16, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&last, text + len - 1, 1, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         st = check_hip(e, "parse");
-        *n_bad = nb;
     }
-    release();
-    return st;
+    (void)hipFreeAsync(ws, s);
+    if (st != SINET_OK) return st;
+    *n_lines = out2[0] + (last != 10 ? 1 : 0);
+    if (*n_lines > out->n)
+        return fail(SINET_ERR_INVALID_ARG, "output columns hold fewer sessions than the text has lines");
+    *n_bad = out2[1];
+    return SINET_OK;
 }
 
 }  // namespace sinet
