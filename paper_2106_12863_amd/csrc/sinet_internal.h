@@ -85,7 +85,7 @@ constexpr int kExtraRecs = 384;     // records beyond one per session a chunk ma
 // record slots of a chunk: one per session, the extra part records of large byte
 // counts, and the padding of every block's segment to whole 16-byte groups
 constexpr int kChunkSlots = kChunk + kExtraRecs + 3 * kWin;
-constexpr int kStage1Run = 4;       // chunks a stage-1 workgroup takes at a time
+constexpr int kStage1Run = 4;       // chunks a stage-1 workgroup takes at a time (many chunks)
 constexpr int kStage1Block = kChunk / 4;  // stage-1 lanes: 4 sessions each
 
 // Device workspace of the partitioned histogram (carved from one allocation).
@@ -96,7 +96,7 @@ struct PartWs {
     uint32_t* farbits;              // [n_chunks * kChunk / 32] far sessions (flagged chunks)
     uint32_t* farlist;              // [n_chunks] chunks holding far sessions
     uint32_t* farcount;             // [1]
-    uint32_t* next_run;             // [1] next run of kStage1Run chunks to take (k_stage1)
+    uint32_t* next_run;             // [1] next run of chunks to take (k_stage1)
     uint32_t* seg_count;            // [n_blocks] directory entries per block
     uint32_t* seg_off;              // [n_blocks + 1] exclusive scan of seg_count
     uint2* segs;                    // [n_chunks * kWin] (first slot, slots) grouped by block
@@ -104,6 +104,8 @@ struct PartWs {
     uint64_t n_chunks;
     uint32_t n_blocks;
     uint32_t vec;                   // 16-byte vector loads allowed
+    uint32_t run;                   // chunks a stage-1 workgroup takes at a time
+    uint32_t keep_dropped;          // the caller clears the dropped counters
     const uint32_t* gate;           // NULL, or a word: zero when another reduce runs instead
 };
 
@@ -157,14 +159,13 @@ struct WinArgs {
     uint32_t* T;                    // [P + 1] owned bins of piece q: [T[q], T[q+1])
     uint32_t* V;                    // [P] first bin of piece q's left spill that was written
     uint32_t* E;                    // [P] end of piece q's right spill that was written
-    uint32_t* counters;             // [4] -, events, event overflow, -
+    uint32_t* ev_n;                 // [P] events of piece q
     uint32_t* far_n;                // [P] steps of piece q holding far sessions
     uint32_t* far_steps;            // [steps] those steps, piece q's listed from its first
                                     // step's slot on
     uint32_t* far_bits;             // [steps * kWinStep / 32] far-session bits of listed steps
-    unsigned long long* events;     // [ev_cap] bin << 3 | label << 1 | wrap
+    unsigned long long* events;     // bin << 3 | label << 1 | wrap, a range per piece
     uint32_t* spill;                // [P][left, right][4][kWinBins] ring words (count, byte sum)
-    uint64_t ev_cap;
     uint32_t vec;                   // 16-byte column loads allowed
     int accumulate;
     const uint32_t* gate;           // NULL, or a word: zero when another reduce runs instead

@@ -29,8 +29,8 @@
 //     byte field or out of the 32-bit word records an event; with the events
 //     the decode (count = w >> 27, bytes = w & (2^27 - 1)) plus (-1, +2^27)
 //     per carry and (+32, 0) per wrap is exact for any number of sessions.
-//     At most n/32 carries and n/32 + n/1024 wraps can happen, so the event
-//     list is bounded.
+//     At most m/32 carries and m/32 + m/1024 wraps can happen in a piece of m
+//     sessions, so its event list is bounded.
 //   * Sliding.  A lane holds 4 consecutive sessions; a step is 4,096
 //     sessions.  A session whose bin is inside the current window is added at
 //     once.  The others of a step are pending: the step's largest pending bin
@@ -81,13 +81,12 @@ __device__ __forceinline__ uint64_t piece_begin(uint64_t n, uint32_t P, uint32_t
 // sessions around piece q's first session (0 for sessions before the window,
 // n_bins after it); piece q then owns [T[q], T[q+1]) with T[q] the running
 // maximum of est[0..q] (est[0] = 0) and T[P] = n_bins, so every bin has one
-// owner.  One wave per piece; workgroup 0 also clears the counters.
+// owner.  One wave per piece.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(64) k_window_bounds(WinArgs a) {
     const uint32_t lane = threadIdx.x, q = blockIdx.x;
     if (a.gate && !*glob(a.gate)) return;
     if (q == 0) {
-        if (lane < 4) a.counters[lane] = 0;
         if (lane == 0) a.est[0] = 0;
         return;
     }
@@ -187,17 +186,23 @@ __device__ __forceinline__ void win_flush(const WinArgs& a, const WinPiece& g, u
     }
 }
 
-// Carry / wrap events of one add (rare: only a bin with more than 32
-// sessions of one label, or 2^27 bytes, in one window).
-__device__ __forceinline__ void win_event(const WinArgs& a, uint32_t bin, uint32_t lab, uint32_t carry,
-                                          uint32_t wrap) {
-    const uint32_t k = carry + wrap;
-    const uint32_t e = atomicAdd(a.counters + 1, k);
+// First event of piece q: room for 1/15 of the sessions before it (a piece of m
+// sessions has at most m/32 carries and m/32 + m/1024 wraps) and a few each.
+__device__ __host__ __forceinline__ uint64_t piece_events(uint64_t begin, uint32_t q) {
+    return begin / 15 + 8ull * q;
+}
+
+// Carry / wrap events of one add: only a bin with more than 32 sessions of one
+// label, or 2^27 bytes, in one window.  A piece counts its events in LDS and
+// lists them in a range of its own: with narrow bins of many sessions (one
+// event per 16), one counter for all pieces took 29 ms of the 29.4 ms of 4e8
+// sessions of an hour in 1-ms bins.
+__device__ __forceinline__ void win_event(const WinArgs& a, uint64_t ev0, uint32_t* s_ev, uint32_t bin,
+                                          uint32_t lab, uint32_t carry, uint32_t wrap) {
+    uint64_t j = ev0 + atomicAdd(s_ev, carry + wrap);
     const unsigned long long key = ((unsigned long long)bin << 3) | (lab << 1);
-    uint32_t j = e;
-    if (carry && j < a.ev_cap) a.events[j++] = key;
-    if (wrap && j < a.ev_cap) a.events[j] = key | 1ull;
-    if (e + k > a.ev_cap) atomicOr(a.counters + 2, 1u);
+    if (carry) *glob(a.events + j++) = key;
+    if (wrap) *glob(a.events + j) = key | 1ull;
 }
 
 // Events of one add of `add` to a ring word that held `old` (bit 0 carry
@@ -282,7 +287,8 @@ __device__ __forceinline__ void win_list_far(const WinArgs& a, WinState& st, uin
 template <bool ACC, bool FULL>
 __device__ __forceinline__ void win_step(const WinArgs& a, const WinPiece& g, uint32_t* ring,
                                          uint4 (*s_x)[kWinWaves], WinState& st, Dropped& d,
-                                         const WinRaw& cur, uint64_t s0, uint64_t i0, uint64_t i1) {
+                                         const WinRaw& cur, uint64_t s0, uint64_t i0, uint64_t i1,
+                                         uint64_t ev0, uint32_t* s_ev) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint64_t i = s0 + 4ull * tid;
     const uint32_t tsv[4] = {cur.ts.x, cur.ts.y, cur.ts.z, cur.ts.w};
@@ -408,7 +414,7 @@ __device__ __forceinline__ void win_step(const WinArgs& a, const WinPiece& g, ui
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t e = (evm >> (2 * u)) & 3u;
-            if (e) win_event(a, bin[u], lab[u], e & 1u, e >> 1);
+            if (e) win_event(a, ev0, s_ev, bin[u], lab[u], e & 1u, e >> 1);
         }
     }
     // far bits: session 4 * tid + u of the step is bit (4 * tid + u) % 32 of
@@ -431,7 +437,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
     uint4* ring4 = reinterpret_cast<uint4*>(ring);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t P = a.pieces;
-    __shared__ uint32_t s_t[4];
+    __shared__ uint32_t s_t[4], s_ev;
     if (a.gate && !*glob(a.gate)) return;
     WinPiece g;
     g.q = blockIdx.x;
@@ -449,6 +455,8 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
         }
     }
     const uint64_t i0 = piece_begin(a.n, P, g.q), i1 = piece_begin(a.n, P, g.q + 1);
+    const uint64_t ev0 = piece_events(i0, g.q);
+    if (tid == 0) s_ev = 0;
     for (uint32_t k = tid; k < kWinBins; k += kWinLanes) ring4[k] = make_uint4(0u, 0u, 0u, 0u);
     lds_barrier();
 
@@ -471,7 +479,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
                 const uint64_t s0 = i0 + (s + k) * kWinStep;
                 const WinRaw cur = r[k];
                 win_load_full<VEC>(a, min(s0 + 2ull * kWinStep + 4ull * tid, last), r[k]);
-                win_step<ACC, true>(a, g, ring, s_x, st, d, cur, s0, i0, i1);
+                win_step<ACC, true>(a, g, ring, s_x, st, d, cur, s0, i0, i1, ev0, &s_ev);
             }
         }
     }
@@ -479,7 +487,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
         const uint64_t s0 = i0 + nfull * kWinStep;
         WinRaw t;
         win_load_tail(a, s0 + 4ull * tid, i1, t);
-        win_step<ACC, false>(a, g, ring, s_x, st, d, t, s0, i0, i1);
+        win_step<ACC, false>(a, g, ring, s_x, st, d, t, s0, i0, i1, ev0, &s_ev);
     }
     // the last step's far ballots, then the remaining window
     if (lane == 0)
@@ -506,6 +514,7 @@ __global__ void __launch_bounds__(kWinLanes) k_window(WinArgs a) {
         a.V[g.q] = st.V;
         a.E[g.q] = (uint32_t)end;
         a.far_n[g.q] = st.nfar_steps;
+        a.ev_n[g.q] = s_ev;  // every event came before the barriers above
     }
     d.flush(a.dropped);
 }
@@ -585,12 +594,12 @@ __global__ void __launch_bounds__(256) k_window_far(WinArgs a) {
             }
         }
     }
-    if (blockIdx.y != 0) return;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t nev = min(a.counters[1], (uint32_t)a.ev_cap);
-    for (uint64_t e = t0; e < nev; e += stride) {
-        const unsigned long long key = a.events[e];
+    const uint32_t stride = gridDim.x * blockDim.x;
+    const uint32_t nev = a.ev_n[blockIdx.y];
+    const unsigned long long* events =
+        a.events + piece_events(piece_begin(a.n, a.pieces, blockIdx.y), blockIdx.y);
+    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < nev; e += stride) {
+        const unsigned long long key = *glob(events + e);
         const uint64_t k = ((key >> 1) & 3ull) * a.n_bins + (key >> 3);
         if (key & 1ull) {  // wrap: 32 sessions the count field lost
             __hip_atomic_fetch_add(a.count + k, 32ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -615,12 +624,12 @@ uint32_t win_pieces(uint64_t n) {
     return (uint32_t)(P < 1 ? 1 : P);
 }
 
-uint64_t win_event_cap(uint64_t n) { return n / 15 + 1024; }
+static uint64_t win_event_cap(uint64_t n, uint32_t P) { return piece_events(n, P) + 8; }
 
 size_t win_ws_bytes(uint64_t n, uint32_t P) {
     const uint64_t steps = (n + kWinStep - 1) / kWinStep;
-    return al256w(4ull * (P + 1)) + 4 * al256w(4ull * P) + al256w(16) + al256w(4ull * steps) +
-           al256w(4ull * kStepWords * steps) + al256w(8ull * win_event_cap(n)) +
+    return al256w(4ull * (P + 1)) + 5 * al256w(4ull * P) + al256w(4ull * steps) +
+           al256w(4ull * kStepWords * steps) + al256w(8ull * win_event_cap(n, P)) +
            al256w(4ull * P * 2 * 4 * kWinBins);
 }
 
@@ -645,13 +654,12 @@ WinArgs win_carve(void* base, const PassParams& p, uint32_t P, int accumulate) {
     a.est = (uint32_t*)take(4ull * P);
     a.V = (uint32_t*)take(4ull * P);
     a.E = (uint32_t*)take(4ull * P);
-    a.counters = (uint32_t*)take(16);
+    a.ev_n = (uint32_t*)take(4ull * P);
     a.far_n = (uint32_t*)take(4ull * P);
     a.far_steps = (uint32_t*)take(4ull * steps);
     a.far_bits = (uint32_t*)take(4ull * kStepWords * steps);
-    a.events = (unsigned long long*)take(8ull * win_event_cap(p.n));
+    a.events = (unsigned long long*)take(8ull * win_event_cap(p.n, P));
     a.spill = (uint32_t*)take(4ull * P * 2 * 4 * kWinBins);
-    a.ev_cap = win_event_cap(p.n);
     a.pieces = P;
     a.vec = ((((uintptr_t)p.ts | (uintptr_t)p.bytes) & 15u) == 0 && ((uintptr_t)p.label_in & 3u) == 0)
                 ? 1u : 0u;
