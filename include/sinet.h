@@ -496,8 +496,8 @@ sinet_status sinet_timing_read(sinet_timing* out);
  *            once (labels are stored by a lookup pass first; about 1 byte
  *            of workspace per session plus 330 MB);
  *   AUTO     (the default) the local reduce from 16 sessions per bin on, for
- *            bins narrower than 48 ms only if a probe of the sessions' order
- *            on the device allows it; else WINDOW from 2^28 sessions on, else
+ *            bins of 4 to 47 ms only if a probe of the sessions' order on the
+ *            device allows it and not for narrower ones; else WINDOW from 2^28 sessions on, else
  *            RECORDS (the measured crossover of the two on a day of 1-ms bins).
  * Process-wide; takes effect for calls made after it returns.
  * Errors: INVALID_ARG (unknown mode). */

@@ -1219,16 +1219,16 @@ __global__ void __launch_bounds__(kStage1Block, 4) k_stage1(PassParams p, PartWs
     uint32_t iter = 0;
     // a chunk is "full" when its kChunk sessions exist and vector loads are allowed
     auto full = [&](uint64_t c) { return w.vec && (c + 1) * kChunk <= p.n; };
-    // workgroups take runs of kStage1Run consecutive chunks from a counter, so
+    // workgroups take runs of consecutive chunks from a counter, so
     // one that falls behind (a busy XCD, a chunk of far sessions) takes fewer;
     // every lane reads s_run before the chunk's first barrier, tid 0 writes it
     // again only after the run's last one
     for (;;) {
         if (tid == 0) s_run = atomicAdd(w.next_run, 1u);
         __syncthreads();
-        const uint64_t c0 = (uint64_t)__builtin_amdgcn_readfirstlane((int)s_run) * kStage1Run;
+        const uint64_t c0 = (uint64_t)__builtin_amdgcn_readfirstlane((int)s_run) * w.run;
         if (c0 >= n_chunks) break;
-        const uint64_t c1 = c0 + kStage1Run < n_chunks ? c0 + kStage1Run : n_chunks;
+        const uint64_t c1 = c0 + w.run < n_chunks ? c0 + w.run : n_chunks;
         Raw4 cur{}, nxt{};
         if (full(c0)) load4<KIND>(p, c0 * kChunk + (uint64_t)tid * 4, cur);
         for (uint64_t c = c0; c < c1; ++c) {
@@ -1458,6 +1458,34 @@ __global__ void __launch_bounds__(1024) k_scan_final(const uint32_t* __restrict_
     const uint32_t exc = tile_off[blockIdx.x] + inc - x;
     if (i < n) out[i] = exc;
     if (i == n) out[n] = exc;  // the total (x = 0 there)
+}
+
+// The whole scan in one workgroup, 8 counts a lane and step: for few blocks,
+// whose scan is one launch's latency instead of three (4.5 us each).
+constexpr uint32_t kScanOneMax = 16 * 1024;
+__global__ void __launch_bounds__(1024) k_scan_one(const uint32_t* __restrict__ in, uint32_t n,
+                                                   uint32_t* __restrict__ out) {
+    __shared__ uint32_t s_w[16], s_end;
+    uint32_t carry = 0;
+    for (uint32_t base = 0; base <= n; base += 8192) {
+        const uint32_t i = base + threadIdx.x * 8;
+        uint32_t x[8], sum = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            x[k] = i + k < n ? in[i + k] : 0u;
+            sum += x[k];
+        }
+        const uint32_t inc = block_incl_scan(sum, s_w);  // ends with a barrier
+        if (threadIdx.x == 1023) s_end = inc;
+        uint32_t at = carry + inc - sum;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            if (i + k <= n) out[i + k] = at;
+            at += x[k];
+        }
+        __syncthreads();
+        carry += s_end;
+    }
 }
 
 // Group the directory entries by block: segs[seg_off[b] ..] = (first slot,
@@ -1819,11 +1847,6 @@ __global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
         if (i == 0 && head) *glob(c.p[a]) = 0;
         if (i == 0 && ((c.n[a] - head) & 1)) *glob(c.p[a] + c.n[a] - 1) = 0;
     }
-}
-
-__global__ void k_zero32(uint32_t* __restrict__ p, uint64_t n) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) p[k] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -2502,11 +2525,10 @@ sinet_status launch_zero(unsigned long long* p, uint64_t n_words, hipStream_t s)
 
 // The histogram's arrays (cells words each; with a gate only if it says so) and
 // dropped counters cleared in one launch; dropped may be NULL, cells 0.
-static sinet_status launch_clear(const PassParams& p, uint64_t cells, hipStream_t s,
-                                 const uint32_t* gate = nullptr) {
-    const ClearArgs c{{p.count, p.hbytes, p.dropped}, {cells, cells, p.dropped ? 8ull : 0ull}, gate};
-    if (c.n[0] + c.n[2] == 0) return SINET_OK;
-    uint64_t blocks = (cells / 2 + 255) / 256;
+static sinet_status launch_clears(const ClearArgs& c, hipStream_t s) {
+    const uint64_t most = c.n[0] > c.n[1] ? c.n[0] : c.n[1];
+    if (most + c.n[2] == 0) return SINET_OK;
+    uint64_t blocks = (most / 2 + 255) / 256;
     const uint64_t cap = (uint64_t)device_cu_count() * 8;
     if (blocks > cap) blocks = cap;
     if (blocks < 1) blocks = 1;
@@ -2514,13 +2536,9 @@ static sinet_status launch_clear(const PassParams& p, uint64_t cells, hipStream_
     return check_hip(hipGetLastError(), "clear launch");
 }
 
-static sinet_status launch_zero32(uint32_t* p, uint64_t n, hipStream_t s) {
-    if (n == 0) return SINET_OK;
-    uint64_t blocks = (n + 255) / 256;
-    const uint64_t cap = (uint64_t)device_cu_count() * 8;
-    if (blocks > cap) blocks = cap;
-    hipLaunchKernelGGL(k_zero32, dim3((unsigned)blocks), dim3(256), 0, s, p, n);
-    return check_hip(hipGetLastError(), "zero kernel launch");
+static sinet_status launch_clear(const PassParams& p, uint64_t cells, hipStream_t s,
+                                 const uint32_t* gate = nullptr) {
+    return launch_clears({{p.count, p.hbytes, p.dropped}, {cells, cells, p.dropped ? 8ull : 0ull}, gate}, s);
 }
 
 // ---- workspace of the partitioned histogram --------------------------------
@@ -2571,10 +2589,14 @@ PartWs part_ws_carve(void* base, uint64_t n, uint32_t n_bins) {
 sinet_status launch_scan_fill(const PartWs& w, hipStream_t s) {
     const uint32_t nb = w.n_blocks;
     const uint32_t ntiles = (nb + 1 + 1023) / 1024;
-    hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(1024), 0, s, w.seg_count, nb, w.scan_tiles);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, w.scan_tiles, ntiles);
-    hipLaunchKernelGGL(k_scan_final, dim3(ntiles), dim3(1024), 0, s, w.seg_count, nb, w.scan_tiles,
-                       w.seg_off);
+    if (nb < kScanOneMax) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, s, w.seg_count, nb, w.seg_off);
+    } else {
+        hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(1024), 0, s, w.seg_count, nb, w.scan_tiles);
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, w.scan_tiles, ntiles);
+        hipLaunchKernelGGL(k_scan_final, dim3(ntiles), dim3(1024), 0, s, w.seg_count, nb, w.scan_tiles,
+                           w.seg_off);
+    }
     uint64_t fb = (w.n_chunks * kWin + 255) / 256;
     const uint64_t cap = (uint64_t)device_cu_count() * 16;
     if (fb > cap) fb = cap;
@@ -2687,9 +2709,15 @@ sinet_status run_partitioned(const PassParams& p0, uint32_t kind, const PartWs& 
     const bool vec = vector_ok(p, kind, true);
     PartWs wv = w;
     wv.vec = vec ? 1u : 0u;
-    sinet_status st = launch_zero32(w.seg_count, w.n_blocks, s);
-    if (st == SINET_OK) st = launch_zero32(w.farcount, 2, s);  // far count, run counter
+    // directory counts (their array is padded to whole 64-bit words), far count
+    // and run counter, and the dropped counters unless accumulating
+    const ClearArgs c{{(unsigned long long*)w.seg_count, (unsigned long long*)w.farcount, p.dropped},
+                      {((uint64_t)w.n_blocks + 1) / 2, 1, !accumulate && !w.keep_dropped && p.dropped ? 8ull : 0ull},
+                      nullptr};
+    sinet_status st = launch_clears(c, s);
     if (st != SINET_OK) return st;
+    // runs of fewer chunks where there are too few for every CU's workgroups
+    wv.run = w.n_chunks >= 8ull * device_cu_count() ? (uint32_t)kStage1Run : 1u;
     Stage1Fn f1 = pick_stage1(kind);
     const size_t lds = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 8;
     if (lds + kStage1StaticLds > 160 * 1024)
@@ -2902,6 +2930,8 @@ constexpr uint32_t kLocalAlways = 2048;    // bins that always take the local re
 // reduce, whose window they leave, 1.45 ms with the sliding window; at 10 ms per
 // bin 1.71 against 15.6 ms.
 constexpr uint32_t kLocalSureWidth = 48;
+// Width below which not even +-5 s of jitter fits the window: no probe.
+constexpr uint32_t kLocalMinWidth = 4;
 
 struct Strategy {
     int reduce;   // R_RECORDS or R_WINDOW, or R_LOCAL when the local reduce is sure
@@ -2914,7 +2944,7 @@ static Strategy hist_strategy(const PassParams& p) {
     if (mode == SINET_REDUCE_WINDOW) return {R_WINDOW, false};
     if (mode == SINET_REDUCE_RECORDS) return {R_RECORDS, false};
     const int other = p.n >= kWindowMinSessions ? R_WINDOW : R_RECORDS;
-    if (p.n / p.n_bins < kLocalMinPerBin) return {other, false};
+    if (p.n / p.n_bins < kLocalMinPerBin || p.width < kLocalMinWidth) return {other, false};
     if (p.width >= kLocalSureWidth) return {R_LOCAL, false};
     return {other, true};
 }
@@ -3158,6 +3188,7 @@ static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulat
     } else if (st == SINET_OK) {
         PartWs w = part_ws_carve(ws, p.n, p.n_bins);
         w.gate = gate;
+        w.keep_dropped = 1;  // cleared above, and the local reduce may have added to it
         st = run_partitioned(q, k2, w, accumulate, s);
     }
     const sinet_status st2 = ws_free(ws, s);
@@ -3185,11 +3216,10 @@ sinet_status run_hist(const PassParams& p, uint32_t mode, int accumulate, hipStr
     const Strategy strat = hist_strategy(p);
     if (strat.reduce == R_LOCAL) return run_local(p, kind, accumulate, s);
     if (strat.probe) return run_probed(p, kind, accumulate, strat.reduce, s);
-    if (!accumulate) {
-        const sinet_status st = launch_clear(p, 0, s);
-        if (st != SINET_OK) return st;
+    if (strat.reduce == R_WINDOW) {
+        const sinet_status st = accumulate ? SINET_OK : launch_clear(p, 0, s);
+        return st == SINET_OK ? run_window(p, kind, accumulate, s) : st;
     }
-    if (strat.reduce == R_WINDOW) return run_window(p, kind, accumulate, s);
     // partitioned: pieces of at most kMaxPiece sessions (32-bit slot indices)
     int acc = accumulate;
     for (uint64_t lo = 0; lo < p.n; lo += kMaxPiece) {

@@ -87,3 +87,33 @@ def test_local_reduce_equals_oracle(n, span, jitter, width, n_bins, order, big, 
         for got, twice, e in zip(out, h, (ec, eb, ed)):
             assert np.array_equal(sinet.to_host_u64(got), e)
             assert np.array_equal(sinet.to_host_u64(twice), e + e)
+
+
+@pytest.mark.parametrize("mode,n,n_bins,width", [
+    ("window", 1_200_001, 9_000, 400),           # 130 sessions a bin: an event for every 16, in every piece
+    ("window", 300_007, 2_100, 1),               # pieces that own few bins
+    ("records", 3_000, 1, 1),                    # (always the local reduce)
+    ("records", 200_003, 16_383 * 1_024, 1),     # one scan workgroup, and the first size past it
+    ("records", 200_003, 16_384 * 1_024 - 1, 1),
+    ("records", 5_000_011, 86_400, 50),          # runs of several chunks
+])
+def test_forced_reduces_equal_oracle(mode, n, n_bins, width):
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    print("forced", mode, n, n_bins, width, flush=True)
+    rng = np.random.default_rng(n)
+    span = n_bins * width
+    ts, by = _sessions(rng, n, span, min(5_000, span / 3))
+    lab = (rng.integers(0, 4, n) * (rng.random(n) < 0.3)).astype(np.uint8)
+    exp = oracle.histogram(ts, by, lab, 1000, width, n_bins)
+    d = sinet.to_device_u32(ts), sinet.to_device_u64(by), torch.from_numpy(lab).cuda()
+    try:
+        sinet.set_reduce(mode)
+        out = sinet.histogram(*d, 1000, width, n_bins)
+        sinet.histogram(*d, 1000, width, n_bins, out=out, accumulate=True)
+        torch.cuda.synchronize()
+    finally:
+        sinet.set_reduce("auto")
+    for got, e in zip(out, exp):
+        assert np.array_equal(sinet.to_host_u64(got), e + e)
