@@ -35,10 +35,8 @@ struct sinet_batch_plan {
 
 namespace {
 
-constexpr uint32_t kPrivMaxBins = 1024;            // LDS-private histograms up to this size
-constexpr size_t kPrivLdsCap = 150 * 1024;         // table + private bins per workgroup
-
 constexpr uint32_t kNoLookup = 0xFFFFFFFFu;
+constexpr uint64_t kZeroWords = 16384;  // words one workgroup clears
 
 struct Prepared {
     std::vector<BatchStreamDev> desc;
@@ -47,6 +45,7 @@ struct Prepared {
     std::vector<size_t> lds_look;       // table LDS of the lookup pass
     std::vector<uint64_t> tmp_off;      // offset of a plan-owned label buffer, or ~0
     uint64_t tmp_bytes = 0;
+    std::map<uint32_t, size_t> kind_lds;  // largest table LDS of each lookup kind
     std::vector<uint32_t> kind;         // kernel kind per stream
     std::vector<size_t> lds_tab;        // table LDS per stream
     std::vector<uint64_t> n_chunks;     // chunks of each stream (sessions / kChunk)
@@ -56,7 +55,23 @@ struct Prepared {
     uint32_t k_tot = 0;
 };
 
-sinet_status prepare(const sinet_stream* st, uint32_t ns, Prepared& pr) {
+// Streams that take the local reduce (k_local) inside stage 1: those whose whole
+// histogram fits the window, and those of coarse bins, when the window holds an
+// item's advance and any nearly sorted log's time jitter.
+void choose_local(BatchStreamDev& d, uint32_t words, uint64_t item_sessions) {
+    const uint32_t cap = words / 4;
+    const uint64_t per_bin = d.p.n / d.p.n_bins + 1;
+    const bool whole = d.p.n_bins <= cap;
+    if (!whole && (d.p.n / d.p.n_bins < kLocalMinPerBin || (uint64_t)cap * d.p.width < kLocalSureSpan ||
+                   per_bin * cap * 3 / 8 < item_sessions))
+        return;
+    uint64_t want = whole ? d.p.n_bins : 8 * (item_sessions / per_bin) + 64;
+    if (!whole && want * d.p.width < kLocalSureSpan) want = kLocalSureSpan / d.p.width;
+    while (d.reps < 4 && want << (d.reps + 1) <= cap) ++d.reps;
+    d.local_bins = whole ? d.p.n_bins : cap >> d.reps;
+}
+
+sinet_status prepare(const sinet_stream* st, uint32_t ns, uint64_t item_sessions, Prepared& pr) {
     if (!st || ns == 0) return fail(SINET_ERR_INVALID_ARG, "no streams");
     pr.desc.resize(ns);
     pr.ldesc.resize(ns);
@@ -97,13 +112,19 @@ sinet_status prepare(const sinet_stream* st, uint32_t ns, Prepared& pr) {
         pr.kind[s] = p.t.kind;
         pr.lds_tab[s] = p.t.lds_bytes;
         pr.n_chunks[s] = (p.n + kChunk - 1) / kChunk;
-        d.priv = (p.n_bins <= kPrivMaxBins &&
-                  pr.lds_tab[s] + 48ull * p.n_bins + 16 <= kPrivLdsCap) ? 1u : 0u;
         d.vec = vector_ok(p, p.t.kind, true) ? 1u : 0u;
+        size_t& most = pr.kind_lds[p.t.kind];
+        most = std::max(most, pr.lds_tab[s]);
+    }
+    for (uint32_t s = 0; s < ns; ++s) {
+        const sinet_stream& x = st[s];
+        BatchStreamDev& d = pr.desc[s];
+        const PassParams& p = d.p;
+        choose_local(d, batch_window_words(pr.kind_lds[p.t.kind]), item_sessions);
         // lookups that walk global memory: a lookup pass stores the labels (in
         // the stream's label output, or a plan-owned buffer when it has none),
         // stage 1 reads them
-        if (!d.priv && p.n && lookup_splits(p.t)) {
+        if (!d.local_bins && p.n && lookup_splits(p.t)) {
             pr.lkind[s] = p.t.kind;
             pr.lds_look[s] = p.t.lds_bytes;
             BatchStreamDev& l = pr.ldesc[s];
@@ -127,7 +148,7 @@ sinet_status prepare(const sinet_stream* st, uint32_t ns, Prepared& pr) {
         BatchStreamDev& d = pr.desc[s];
         d.chunk0 = c;
         d.block0 = (uint32_t)k;
-        if (!d.priv) {
+        if (!d.local_bins) {
             c += pr.n_chunks[s];
             k += (d.p.n_bins + kBlockBins - 1) / kBlockBins;
         }
@@ -145,10 +166,12 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& tune,
                         sinet_batch_plan* plan) {
+    // an item of a local stream is one run of its window's 17-bit counts
+    const uint32_t item_chunks = std::min<uint32_t>(std::max<uint32_t>(1, tune.chunk / kChunk),
+                                                    ((1u << 17) - 1) / kChunk);
     Prepared pr;
-    sinet_status rc = prepare(st, ns, pr);
+    sinet_status rc = prepare(st, ns, (uint64_t)item_chunks * kChunk, pr);
     if (rc != SINET_OK) return rc;
-    const uint32_t item_chunks = std::max<uint32_t>(1, tune.chunk / kChunk);
 
     // kind groups and their work items
     std::vector<uint32_t> kinds;
@@ -156,20 +179,20 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
         if (std::find(kinds.begin(), kinds.end(), pr.kind[s]) == kinds.end()) kinds.push_back(pr.kind[s]);
     std::vector<std::vector<uint4>> items(kinds.size());
     std::vector<size_t> group_lds(kinds.size(), 8);
-    std::vector<uint32_t> group_priv(kinds.size(), 0);
+    std::vector<uint32_t> group_win(kinds.size(), 0);
     for (uint32_t s = 0; s < ns; ++s) {
         const size_t g = std::find(kinds.begin(), kinds.end(), pr.kind[s]) - kinds.begin();
         const BatchStreamDev& d = pr.desc[s];
-        size_t need = pr.lds_tab[s] + 16;
-        if (d.priv) {
-            need += 48ull * d.p.n_bins;
-            group_priv[g] = std::max(group_priv[g], d.p.n_bins);
-        }
-        group_lds[g] = std::max(group_lds[g], need);
+        group_lds[g] = std::max(group_lds[g], pr.lds_tab[s] + 16);
+        if (d.local_bins) group_win[g] = std::max(group_win[g], 4u * d.local_bins << d.reps);
         for (uint64_t c0 = 0; c0 < pr.n_chunks[s]; c0 += item_chunks) {
             const uint64_t c1 = std::min<uint64_t>(pr.n_chunks[s], c0 + item_chunks);
             items[g].push_back(make_uint4(s, (uint32_t)c0, (uint32_t)c1, 0u));
         }
+    }
+    for (size_t g = 0; g < kinds.size(); ++g) {
+        group_win[g] = (group_win[g] + 1) & ~1u;  // the table behind it starts on 16 bytes
+        group_lds[g] += 8ull * group_win[g];
     }
     // lookup-pass groups of the split streams
     std::vector<uint32_t> lkinds;
@@ -209,7 +232,9 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
                                           std::max<uint32_t>(1, pr.k_tot) * kBlockBins);
     const size_t oWs = take(ws_bytes);
     // zero jobs are counted before the arena is final
-    size_t n_jobs_max = 4 + 3 * ns;
+    size_t n_jobs_max = 4 + ns + pr.k_tot / kZeroWords;
+    for (uint32_t s = 0; s < ns; ++s)
+        if (pr.desc[s].local_bins) n_jobs_max += 2 * (4ull * pr.desc[s].p.n_bins / kZeroWords + 1);
     const size_t oJobs = take(sizeof(ZeroJob) * n_jobs_max);
     void* arena = nullptr;
     hipError_t e = hipMalloc(&arena, off);
@@ -233,15 +258,19 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
         l.vec = vector_ok(l.p, l.p.t.kind, false) ? 1u : 0u;
         d.vec = vector_ok(d.p, kLabelInKind, true) ? 1u : 0u;
     }
-    jobs.push_back({(unsigned long long*)(a + oCtl), (uint64_t)n_ctl});
-    jobs.push_back({(unsigned long long*)w.farcount, 1});
-    if (pr.k_tot) jobs.push_back({(unsigned long long*)w.seg_count, (pr.k_tot + 1) / 2});
+    auto clear = [&](void* q, uint64_t n) {
+        for (uint64_t k = 0; k < n; k += kZeroWords)
+            jobs.push_back({(unsigned long long*)q + k, std::min<uint64_t>(n - k, kZeroWords)});
+    };
+    clear(a + oCtl, n_ctl);
+    clear(w.farcount, 1);
+    if (pr.k_tot) clear(w.seg_count, (pr.k_tot + 1) / 2);
     for (uint32_t s = 0; s < ns; ++s) {
         const BatchStreamDev& d = pr.desc[s];
-        if (d.p.dropped) jobs.push_back({d.p.dropped, 8});
-        if (d.priv) {
-            jobs.push_back({d.p.count, 4ull * d.p.n_bins});
-            jobs.push_back({d.p.hbytes, 4ull * d.p.n_bins});
+        if (d.p.dropped) clear(d.p.dropped, 8);
+        if (d.local_bins) {
+            clear(d.p.count, 4ull * d.p.n_bins);
+            clear(d.p.hbytes, 4ull * d.p.n_bins);
         }
     }
     e = hipMemcpy(a + oDesc, pr.desc.data(), sizeof(BatchStreamDev) * ns, hipMemcpyHostToDevice);
@@ -271,7 +300,7 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
         ba.counter = (uint32_t*)(a + oCtl + 8 * g);
         ba.chunk_base = (const uint64_t*)(a + oCb);
         ba.block_base = (const uint32_t*)(a + oBb);
-        ba.priv_bins = group_priv[g];
+        ba.win_words = group_win[g];
         // occupancy queries before capture
         const uint32_t occ = batch_stage1_blocks_per_cu(kinds[g], group_lds[g]);
         grids[g] = tune.grid ? tune.grid : device_cu_count() * occ;
@@ -329,10 +358,15 @@ void destroy_plan(sinet_batch_plan* p) {
     delete p;
 }
 
-sinet_tune default_tune() {
+// Items of 16 chunks amortise what an item costs (its first loads, the window's
+// placing and flush), as long as two workgroups per CU get about eight each: 64
+// streams of 3e8 sessions took 5.96 ms with them, 6.30 with items of 4, 6.54 of 2.
+sinet_tune default_tune(const sinet_stream* st, uint32_t ns) {
+    uint64_t n = 0;
+    for (uint32_t s = 0; st && s < ns; ++s) n += st[s].cols.n;
     sinet_tune t{};
     t.block = kStage1Block;
-    t.chunk = 4 * kChunk;
+    t.chunk = (n / (16 * kChunk) >= 16ull * device_cu_count() ? 16 : 4) * kChunk;
     t.grid = 0;
     return t;
 }
@@ -401,7 +435,7 @@ sinet_status sinet_batch_plan_create(const sinet_stream* streams, uint32_t n_str
     (void)stream;
     if (!out) return fail(SINET_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
-    sinet_tune t = tune ? *tune : default_tune();
+    sinet_tune t = tune ? *tune : default_tune(streams, n_streams);
     if (t.chunk < (uint32_t)kChunk) t.chunk = kChunk;
     sinet_batch_plan* plan = new sinet_batch_plan();
     (void)hipGetDevice(&plan->device);
@@ -436,7 +470,7 @@ sinet_status sinet_autotune(const sinet_stream* streams, uint32_t n_streams, con
     const uint32_t cus = device_cu_count();
     const uint32_t chunks[] = {(uint32_t)kChunk, 4u * kChunk, 16u * kChunk};
     const uint32_t grids[] = {0u, cus / 2};
-    sinet_tune best = default_tune();
+    sinet_tune best = default_tune(streams, n_streams);
     float best_ms = 1e30f;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)

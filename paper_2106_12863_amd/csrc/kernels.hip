@@ -701,18 +701,11 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
 
 enum HistMode : int {
     H_NONE = 0,     // labels / institutions / positions only
-    H_ATOMIC = 1,   // device-scope atomics into the output bins
-    H_PRIVATE = 2   // whole histogram privatised in LDS per workgroup (batches)
-};
-
-// LDS histogram of the private mode: counts u32 [4][n_bins], bytes u64 [4][n_bins].
-struct PrivHist {
-    uint32_t* c;
-    unsigned long long* b;
+    H_ATOMIC = 1    // device-scope atomics into the output bins
 };
 
 template <int HM>
-__device__ __forceinline__ void account(const PassParams& p, const PrivHist& h, uint32_t lab,
+__device__ __forceinline__ void account(const PassParams& p, uint32_t lab,
                                         uint32_t ts, uint64_t nbytes, Dropped& d) {
     if constexpr (HM == H_NONE) return;
     uint32_t b;
@@ -721,14 +714,8 @@ __device__ __forceinline__ void account(const PassParams& p, const PrivHist& h, 
         return;
     }
     const uint64_t k = (uint64_t)lab * p.n_bins + b;
-    if constexpr (HM == H_ATOMIC) {
-        __hip_atomic_fetch_add(p.count + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(p.hbytes + k, (unsigned long long)nbytes, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        atomicAdd(h.c + k, 1u);
-        atomicAdd(h.b + k, (unsigned long long)nbytes);
-    }
+    __hip_atomic_fetch_add(p.count + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(p.hbytes + k, (unsigned long long)nbytes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // 16 bytes read once (the columns of a lookup pass): nontemporal loads.  On
@@ -755,8 +742,8 @@ __device__ __forceinline__ uint32_t label1(const PassParams& p, const LdsView& v
 }
 
 template <uint32_t KIND, int HM>
-__device__ __forceinline__ void one_session(const PassParams& p, const LdsView& v,
-                                            const PrivHist& h, uint64_t i, Dropped& d) {
+__device__ __forceinline__ void one_session(const PassParams& p, const LdsView& v, uint64_t i,
+                                            Dropped& d) {
     if (p.pos_out) {
         if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT && KIND != KK_UNION) {
             const uint32_t a = p.src[i];
@@ -772,7 +759,7 @@ __device__ __forceinline__ void one_session(const PassParams& p, const LdsView& 
     } else {
         lab = label1<KIND, HM == H_NONE && queued_kind(KIND) ? kQueueAll : 0>(p, v, i);
     }
-    if constexpr (HM != H_NONE) account<HM>(p, h, lab, *glob(p.ts + i), *glob(p.bytes + i), d);
+    if constexpr (HM != H_NONE) account<HM>(p, lab, *glob(p.ts + i), *glob(p.bytes + i), d);
 }
 
 // Labels of four consecutive sessions starting at i from their loaded source
@@ -835,8 +822,8 @@ __device__ __forceinline__ void labels4(const PassParams& p, const LdsView& v, u
 }
 
 template <uint32_t KIND, int HM>
-__device__ __forceinline__ void four_sessions(const PassParams& p, const LdsView& v,
-                                              const PrivHist& h, uint64_t i, Dropped& d) {
+__device__ __forceinline__ void four_sessions(const PassParams& p, const LdsView& v, uint64_t i,
+                                            Dropped& d) {
     if (p.pos_out) {
         if constexpr (KIND != KK_SCAN && KIND != KK_LABEL_IN && KIND != KK_INOUT && KIND != KK_UNION) {
             const uint4 a4 = *reinterpret_cast<const uint4*>(p.src + i);
@@ -853,10 +840,10 @@ __device__ __forceinline__ void four_sessions(const PassParams& p, const LdsView
         const uint4 ts = gload4(p.ts + i);
         const ulonglong2 b01 = gload2(p.bytes + i);
         const ulonglong2 b23 = gload2(p.bytes + i + 2);
-        account<HM>(p, h, lab[0], ts.x, b01.x, d);
-        account<HM>(p, h, lab[1], ts.y, b01.y, d);
-        account<HM>(p, h, lab[2], ts.z, b23.x, d);
-        account<HM>(p, h, lab[3], ts.w, b23.y, d);
+        account<HM>(p, lab[0], ts.x, b01.x, d);
+        account<HM>(p, lab[1], ts.y, b01.y, d);
+        account<HM>(p, lab[2], ts.z, b23.x, d);
+        account<HM>(p, lab[3], ts.w, b23.y, d);
     }
 }
 
@@ -918,7 +905,6 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
     if constexpr (HM == H_NONE && queued_kind(KIND)) {
         if (p.queue_words) v.queue = lds + used + (threadIdx.x >> 6) * p.queue_words;
     }
-    const PrivHist h{nullptr, nullptr};
     Dropped d{};
     if (HM == H_ATOMIC && far.list) {
         const uint32_t nfar = *far.count;
@@ -927,7 +913,7 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
             for (uint32_t s = threadIdx.x; s < kChunk; s += blockDim.x) {
                 const uint64_t i = c * kChunk + s;
                 if (i < p.n && ((far.bits[c * (kChunk / 32) + s / 32] >> (s & 31)) & 1u))
-                    one_session<KIND, HM>(p, v, h, i, d);
+                    one_session<KIND, HM>(p, v, i, d);
             }
         }
     } else {
@@ -969,7 +955,7 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
                         labels4_from<KIND, kQ>(p, v, g * 4, cs, cd, 0u, lab);
                     } else if (g * 4 < p.n) {
                         for (uint64_t i = g * 4; i < p.n && i < g * 4 + 4; ++i)
-                            one_session<KIND, HM>(p, v, h, i, d);
+                            one_session<KIND, HM>(p, v, i, d);
                     }
                     cs = ns;
                     cd = nd;
@@ -981,10 +967,10 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
             const uint64_t g = tl * tile + threadIdx.x;
             if (g >= groups) continue;
             if (VEC && g * 4 + 4 <= p.n) {
-                four_sessions<KIND, HM>(p, v, h, g * 4, d);
+                four_sessions<KIND, HM>(p, v, g * 4, d);
             } else {
                 for (uint64_t i = g * 4; i < p.n && i < g * 4 + 4; ++i)
-                    one_session<KIND, HM>(p, v, h, i, d);
+                    one_session<KIND, HM>(p, v, i, d);
             }
         }
     }
@@ -1279,6 +1265,112 @@ struct LocalArgs {
     const uint32_t* gate;  // NULL, or a word: nonzero when another reduce runs instead
 };
 
+// A workgroup's window: `bins` bins from w0 on, 2^reps copies.
+struct LocalWin {
+    unsigned long long* h;
+    uint32_t bins, reps, w0;
+};
+
+// First bin of the next window: a sixteenth of it before the median of the
+// waves' first bins (a few stray sessions do not move it).  m: this lane's first
+// bin, ~0 for none.  Called by the whole workgroup; s_min holds a word per wave.
+__device__ __forceinline__ uint32_t local_place(uint32_t m, uint32_t bins, uint32_t* s_min) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    m = wave_min(m);
+    if (lane == 0) s_min[wave] = m;
+    lds_barrier();
+    const uint32_t mine = lane < nw ? s_min[lane] : 0xFFFFFFFFu;
+    const uint32_t valid = (uint32_t)__popcll(__ballot(mine != 0xFFFFFFFFu));
+    uint32_t rank = 0;
+    for (uint32_t k = 0; k < nw; ++k) {
+        const uint32_t o = s_min[k];
+        rank += (o < mine || (o == mine && k < lane)) ? 1u : 0u;
+    }
+    const unsigned long long at = __ballot(mine != 0xFFFFFFFFu && rank == valid / 2);
+    const uint32_t med = at ? (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(at)) : 0u;
+    return med > bins / 16u ? med - bins / 16u : 0u;
+}
+
+// One session into the window (copy rep), the output or the dropped counters.
+__device__ __forceinline__ void local_add(const PassParams& p, const LocalWin& w, uint32_t rep, uint32_t lab,
+                                          uint32_t ts, unsigned long long by, Dropped& d) {
+    uint32_t bin;
+    const bool inw = in_window(p, ts, bin);
+    const uint32_t off = bin - w.w0;
+    if (inw && off < w.bins && by < kLocalMaxBytes) {
+        atomicAdd(&w.h[((off * 4u + lab) << w.reps) + rep], (1ull << kLocalShift) | by);
+    } else if (inw) {
+        const uint64_t x = (uint64_t)lab * p.n_bins + bin;
+        __hip_atomic_fetch_add(p.count + x, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(p.hbytes + x, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        d.add(lab, by);
+    }
+}
+
+// The lane's four sessions from i0 on: loaded ones (full), or those below n.
+template <uint32_t KIND>
+__device__ __forceinline__ void local_add4(const PassParams& p, const LdsView& v, const LocalWin& w,
+                                           uint32_t rep, uint64_t i0, const Raw4& cur, bool full, Dropped& d) {
+    uint32_t lab[4], ts[4];
+    unsigned long long by[4];
+    if (full) {
+        labels4_from<KIND>(p, v, i0, cur.src, cur.dst, cur.l4, lab);
+        ts[0] = cur.ts.x; ts[1] = cur.ts.y; ts[2] = cur.ts.z; ts[3] = cur.ts.w;
+        by[0] = cur.b01.x; by[1] = cur.b01.y; by[2] = cur.b23.x; by[3] = cur.b23.y;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint64_t i = i0 + k;
+            lab[k] = ts[k] = 0;
+            by[k] = 0;
+            if (i >= p.n) continue;
+            if constexpr (KIND == KK_LABEL_IN) lab[k] = *glob(p.label_in + i) & 3u;
+            else lab[k] = label1<KIND>(p, v, i);
+            ts[k] = *glob(p.ts + i);
+            by[k] = *glob(p.bytes + i);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (full || i0 + k < p.n) local_add(p, w, rep, lab[k], ts[k], by[k], d);
+}
+
+// First bin of the lane's four sessions (~0: none in the histogram).
+__device__ __forceinline__ uint32_t local_first(const PassParams& p, uint64_t i0, const Raw4& cur, bool full) {
+    const uint32_t t4[4] = {cur.ts.x, cur.ts.y, cur.ts.z, cur.ts.w};
+    uint32_t m = 0xFFFFFFFFu;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool has = full || i0 + k < p.n;
+        const uint32_t ts = full ? t4[k] : (has ? *glob(p.ts + i0 + k) : 0u);
+        uint32_t bin;
+        if (has && in_window(p, ts, bin)) m = min(m, bin);
+    }
+    return m;
+}
+
+// The window's words added to the output and cleared; consecutive lanes take
+// consecutive bins of a label, as the output does.  Between barriers.
+__device__ __forceinline__ void local_flush(const PassParams& p, const LocalWin& w) {
+    for (uint32_t k = threadIdx.x; k < 4u * w.bins; k += blockDim.x) {
+        const uint32_t l = k / w.bins, b = k - l * w.bins;
+        unsigned long long c = 0, y = 0;
+        for (uint32_t r = 0; r < 1u << w.reps; ++r) {
+            unsigned long long* e = &w.h[((b * 4u + l) << w.reps) + r];
+            const unsigned long long x = *e;
+            if (x) *e = 0;
+            c += x >> kLocalShift;
+            y += x & ((1ull << kLocalShift) - 1ull);
+        }
+        if (c) {
+            const uint64_t x = (uint64_t)l * p.n_bins + w.w0 + b;
+            __hip_atomic_fetch_add(p.count + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(p.hbytes + x, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 template <uint32_t KIND, bool VEC>
 __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -1286,11 +1378,10 @@ __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) 
     if (a.gate && *glob(a.gate)) return;
     uint32_t used = 0;
     const LdsView v = stage_lds<KIND>(p.t, lds, &used);
-    unsigned long long* h = reinterpret_cast<unsigned long long*>(lds + ((used + 1) & ~1u));
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t words = a.bins * 4u;
-    for (uint32_t k = tid; k < words << a.reps; k += blockDim.x) h[k] = 0;
-    const uint32_t rep = lane & ((1u << a.reps) - 1u);
+    LocalWin w{reinterpret_cast<unsigned long long*>(lds + ((used + 1) & ~1u)), a.bins, a.reps, 0u};
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t k = tid; k < a.bins * 4u << a.reps; k += blockDim.x) w.h[k] = 0;
+    const uint32_t rep = tid & ((1u << a.reps) - 1u);
     Dropped d{};
     const uint64_t step = 4ull * blockDim.x;
     const uint64_t n_steps = (p.n + step - 1) / step;
@@ -1298,97 +1389,17 @@ __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) 
     auto full = [&](uint64_t s) { return VEC && (s + 1) * step <= p.n; };
     Raw4 cur{}, nxt{};
     if (s0 < s1 && full(s0)) load4<KIND>(p, s0 * step + 4ull * tid, cur);
-    uint32_t w0 = 0;
     __syncthreads();
     for (uint64_t r0 = s0; r0 < s1; r0 += a.run) {
         const uint64_t r1 = r0 + a.run < s1 ? r0 + a.run : s1;
-        if (!a.whole) {
-            // the window starts a sixteenth of itself before the median of the
-            // waves' first bins (a few stray sessions do not move it)
-            uint32_t m = 0xFFFFFFFFu;
-            const uint32_t t4[4] = {cur.ts.x, cur.ts.y, cur.ts.z, cur.ts.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint64_t i = r0 * step + 4ull * tid + k;
-                const uint32_t ts = full(r0) ? t4[k] : (i < p.n ? *glob(p.ts + i) : 0u);
-                uint32_t bin;
-                if (i < p.n && in_window(p, ts, bin)) m = min(m, bin);
-            }
-            m = wave_min(m);
-            if (lane == 0) s_min[wave] = m;
-            lds_barrier();
-            const uint32_t nw = blockDim.x >> 6;
-            const uint32_t mine = lane < nw ? s_min[lane] : 0xFFFFFFFFu;
-            const uint32_t valid = (uint32_t)__popcll(__ballot(mine != 0xFFFFFFFFu));
-            uint32_t rank = 0;
-            for (uint32_t k = 0; k < nw; ++k) {
-                const uint32_t o = s_min[k];
-                rank += (o < mine || (o == mine && k < lane)) ? 1u : 0u;
-            }
-            const unsigned long long at = __ballot(mine != 0xFFFFFFFFu && rank == valid / 2);
-            const uint32_t med =
-                at ? (uint32_t)__builtin_amdgcn_readlane((int)mine, __builtin_ctzll(at)) : 0u;
-            w0 = med > a.bins / 16u ? med - a.bins / 16u : 0u;
-        }
+        if (!a.whole) w.w0 = local_place(local_first(p, r0 * step + 4ull * tid, cur, full(r0)), a.bins, s_min);
         for (uint64_t s = r0; s < r1; ++s) {
             if (s + 1 < s1 && full(s + 1)) load4<KIND>(p, (s + 1) * step + 4ull * tid, nxt);
-            const uint64_t i0 = s * step + 4ull * tid;
-            uint32_t lab[4], ts[4];
-            unsigned long long by[4];
-            if (full(s)) {
-                labels4_from<KIND>(p, v, i0, cur.src, cur.dst, cur.l4, lab);
-                ts[0] = cur.ts.x; ts[1] = cur.ts.y; ts[2] = cur.ts.z; ts[3] = cur.ts.w;
-                by[0] = cur.b01.x; by[1] = cur.b01.y; by[2] = cur.b23.x; by[3] = cur.b23.y;
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint64_t i = i0 + k;
-                    lab[k] = ts[k] = 0;
-                    by[k] = 0;
-                    if (i >= p.n) continue;
-                    if constexpr (KIND == KK_LABEL_IN) lab[k] = *glob(p.label_in + i) & 3u;
-                    else lab[k] = label1<KIND>(p, v, i);
-                    ts[k] = *glob(p.ts + i);
-                    by[k] = *glob(p.bytes + i);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (!full(s) && i0 + k >= p.n) continue;
-                uint32_t bin;
-                const bool inw = in_window(p, ts[k], bin);
-                const uint32_t off = bin - w0;
-                if (inw && off < a.bins && by[k] < kLocalMaxBytes) {
-                    atomicAdd(&h[((off * 4u + lab[k]) << a.reps) + rep], (1ull << kLocalShift) | by[k]);
-                } else if (inw) {
-                    const uint64_t x = (uint64_t)lab[k] * p.n_bins + bin;
-                    __hip_atomic_fetch_add(p.count + x, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(p.hbytes + x, by[k], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                } else {
-                    d.add(lab[k], by[k]);
-                }
-            }
+            local_add4<KIND>(p, v, w, rep, s * step + 4ull * tid, cur, full(s), d);
             cur = nxt;
         }
         lds_barrier();
-        // consecutive lanes take consecutive bins of a label, as the output does
-        for (uint32_t k = tid; k < words; k += blockDim.x) {
-            const uint32_t l = k / a.bins, b = k - l * a.bins;
-            unsigned long long c = 0, y = 0;
-            for (uint32_t r = 0; r < 1u << a.reps; ++r) {
-                unsigned long long* e = &h[((b * 4u + l) << a.reps) + r];
-                const unsigned long long x = *e;
-                if (x) *e = 0;
-                c += x >> kLocalShift;
-                y += x & ((1ull << kLocalShift) - 1ull);
-            }
-            if (c) {
-                const uint64_t x = (uint64_t)l * p.n_bins + w0 + b;
-                __hip_atomic_fetch_add(p.count + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(p.hbytes + x, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        local_flush(p, w);
         lds_barrier();
     }
     d.flush(p.dropped);
@@ -1859,8 +1870,11 @@ __global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
 // workgroups pull until it is exhausted; a workgroup restages the table in
 // LDS only when the stream changes.  Partitioned streams share one workspace
 // (chunk and block index spaces concatenated), so one scan, one fill, one
-// stage-2 launch and one far pass serve all of them.  Streams with few bins
-// keep their whole histogram in LDS for the item and merge it with atomics.
+// stage-2 launch and one far pass serve all of them.  Streams of coarse bins
+// take the local reduce instead, an item being a run: their records made a few
+// blocks very long, which stage 2 ended on, and their private histograms held a
+// CU to one workgroup.  64 streams (3e8 sessions, a third in 1-s bins): stage 1
+// 3.20 -> 1.91 ms, stage 2 5.72 -> 4.16 ms, the whole batch 9.27 -> 6.31 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
@@ -1873,11 +1887,15 @@ __device__ __forceinline__ void batch_stage1(const BatchArgs& a, const PartWs& w
     __shared__ uint4 srec[kChunkSlots / 4];
     __shared__ uint32_t s_item;
     __shared__ BatchStreamDev s_bs;  // the current stream's descriptor
+    __shared__ uint32_t s_min[kStage1Block / 64];
     const uint32_t tid = threadIdx.x;
     uint32_t staged = 0xFFFFFFFFu;
     LdsView v{};
     uint32_t used = 0;
     uint32_t iter = 0;
+    // the local streams' window, then the table
+    unsigned long long* win = reinterpret_cast<unsigned long long*>(lds);
+    for (uint32_t k = tid; k < a.win_words; k += blockDim.x) win[k] = 0;
     for (;;) {
         if (tid == 0) s_item = atomicAdd(a.counter, 1u);
         __syncthreads();
@@ -1893,7 +1911,7 @@ __device__ __forceinline__ void batch_stage1(const BatchArgs& a, const PartWs& w
             uint32_t* dst = reinterpret_cast<uint32_t*>(&s_bs);
             for (uint32_t k = tid; k < kWords; k += blockDim.x) dst[k] = src[k];
             __syncthreads();
-            v = stage_lds<KIND>(s_bs.p.t, lds, &used);  // ends with a barrier
+            v = stage_lds<KIND>(s_bs.p.t, lds + 2 * a.win_words, &used);  // ends with a barrier
             staged = si;
         }
         // the descriptor in scalar registers for the item: read from LDS after
@@ -1907,36 +1925,23 @@ __device__ __forceinline__ void batch_stage1(const BatchArgs& a, const PartWs& w
         }
         const PassParams& p = bs.p;
         Dropped d{};
-        if (bs.priv) {
-            PrivHist h;
-            const uint32_t base = (used + 1) & ~1u;
-            h.b = reinterpret_cast<unsigned long long*>(lds + base);
-            h.c = lds + base + 2 * 4 * p.n_bins;
-            for (uint32_t k = tid; k < 4 * p.n_bins; k += blockDim.x) {
-                h.b[k] = 0;
-                h.c[k] = 0;
-            }
-            __syncthreads();
+        if (bs.local_bins) {
+            LocalWin w{win, bs.local_bins, bs.reps, 0u};
             const bool vec = bs.vec != 0;
-            for (uint64_t c = item.y; c < item.z; ++c) {
-                const uint64_t g4 = c * (kChunk / 4) + tid;  // group of 4 sessions
-                if (vec && g4 * 4 + 4 <= p.n) {
-                    four_sessions<KIND, H_PRIVATE>(p, v, h, g4 * 4, d);
-                } else {
-                    for (uint64_t i = g4 * 4; i < p.n && i < g4 * 4 + 4; ++i)
-                        one_session<KIND, H_PRIVATE>(p, v, h, i, d);
-                }
+            auto full = [&](uint64_t c) { return vec && (c + 1) * kChunk <= p.n; };
+            const uint32_t rep = tid & ((1u << bs.reps) - 1u);
+            Raw4 cur{}, nxt{};
+            uint64_t c = item.y;
+            if (c < item.z && full(c)) load4<KIND>(p, c * kChunk + 4ull * tid, cur);
+            if (bs.local_bins < p.n_bins)
+                w.w0 = local_place(local_first(p, c * kChunk + 4ull * tid, cur, full(c)), w.bins, s_min);
+            for (; c < item.z; ++c) {
+                if (c + 1 < item.z && full(c + 1)) load4<KIND>(p, (c + 1) * kChunk + 4ull * tid, nxt);
+                local_add4<KIND>(p, v, w, rep, c * kChunk + 4ull * tid, cur, full(c), d);
+                cur = nxt;
             }
             __syncthreads();
-            for (uint32_t k = tid; k < 4 * p.n_bins; k += blockDim.x) {
-                if (h.c[k]) {
-                    __hip_atomic_fetch_add(p.count + k, (unsigned long long)h.c[k], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_fetch_add(p.hbytes + k, h.b[k], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-            __syncthreads();
+            local_flush(p, w);  // cleared before the next item's first barrier
         } else {
             const bool vec = bs.vec != 0;
             auto full = [&](uint64_t c) { return vec && (c + 1) * kChunk <= p.n; };
@@ -1994,7 +1999,6 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_far(BatchArgs a, PartWs w) 
     uint32_t staged = 0xFFFFFFFFu;
     LdsView v{};
     uint32_t used = 0;
-    const PrivHist h{nullptr, nullptr};
     const uint32_t nfar = *w.farcount;
     for (uint32_t q = blockIdx.x; q < nfar; q += gridDim.x) {
         const uint64_t g = w.farlist[q];
@@ -2007,7 +2011,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_far(BatchArgs a, PartWs w) 
         while (lo + 1 < a.n_streams && a.chunk_base[lo + 1] <= g) ++lo;
         const uint32_t si = uniform_u32(lo);
         const BatchStreamDev& bs = a.streams[si];
-        if (bs.priv || bs.p.t.kind != KIND) continue;  // another kind group's chunk
+        if (bs.local_bins || bs.p.t.kind != KIND) continue;  // another kind group's chunk
         PassParams p = bs.p;
         p.label_out = nullptr;
         p.src_inst = nullptr;
@@ -2023,7 +2027,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_far(BatchArgs a, PartWs w) 
         for (uint32_t s = threadIdx.x; s < kChunk; s += blockDim.x) {
             const uint64_t i = c * kChunk + s;
             if (i < p.n && ((w.farbits[g * (kChunk / 32) + s / 32] >> (s & 31)) & 1u))
-                one_session<KIND, H_ATOMIC>(p, v, h, i, d);
+                one_session<KIND, H_ATOMIC>(p, v, i, d);
         }
     }
 }
@@ -2043,7 +2047,6 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_lookup(BatchArgs a) {
     uint32_t staged = 0xFFFFFFFFu;
     LdsView v{};
     uint32_t used = 0;
-    const PrivHist h{nullptr, nullptr};
     for (;;) {
         __syncthreads();  // every lane is done with the previous item
         if (tid == 0) s_item = atomicAdd(a.counter, 1u);
@@ -2096,7 +2099,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_lookup(BatchArgs a) {
             } else {
                 Dropped d{};
                 for (uint64_t i = g * 4; i < p.n && i < g * 4 + 4; ++i)
-                    one_session<KIND, H_NONE>(p, v, h, i, d);
+                    one_session<KIND, H_NONE>(p, v, i, d);
             }
             cs = ns;
             cd = nd;
@@ -2820,6 +2823,15 @@ sinet_status launch_batch_lookup(uint32_t kind, const BatchArgs& a, size_t lds, 
     return check_hip(hipGetLastError(), "batch lookup launch");
 }
 
+// Two workgroups per CU where the table leaves 8 KB or more for the window
+// then, else one; at most 32 KB.
+uint32_t batch_window_words(size_t table) {
+    const size_t used = kStage1StaticLds + sizeof(BatchStreamDev) + 256 + table;
+    for (const size_t lds : {(size_t)80 * 1024, (size_t)160 * 1024})
+        if (lds >= used + 8 * 1024) return (uint32_t)((lds - used < 32 * 1024 ? lds - used : 32 * 1024) / 8);
+    return 0;
+}
+
 uint32_t batch_stage1_blocks_per_cu(uint32_t kind, size_t lds) {
     BatchFn fn = pick_batch_stage1(kind);
     return fn ? (uint32_t)blocks_per_cu((const void*)fn, kStage1Block, lds) : 1u;
@@ -2922,7 +2934,7 @@ constexpr uint64_t kWindowMinSessions = 1ull << 28;
 // day took 1.11 ms with 12 sessions per bin, 0.76 with 23, 0.60 with 58 and 0.44
 // with 116, the records 0.89-0.93 ms each.  Small calls gain before that (4e6
 // sessions, 11 per bin: 62 against 91 us) but would need a probe of their order.
-constexpr uint64_t kLocalMinPerBin = 16;
+static_assert(kLocalMinPerBin == 16, "the line measured above");
 constexpr uint32_t kLocalAlways = 2048;    // bins that always take the local reduce
 // Width from which a window of bins (about 2,500) takes the time order of any
 // nearly sorted log: +-1 minute.  With narrower bins a probe looks first: with

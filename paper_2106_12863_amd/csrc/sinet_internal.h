@@ -176,9 +176,9 @@ struct BatchStreamDev {
     PassParams p;               // label view of its table, columns, outputs, window
     uint64_t chunk0;            // first workspace chunk (partitioned streams)
     uint32_t block0;            // first workspace block (partitioned streams)
-    uint32_t priv;              // 1: histogram privatised in LDS, merged by atomics
+    uint32_t local_bins;        // bins of the local reduce's window (0: records)
     uint32_t vec;               // 1: the stream's columns allow 16-byte loads
-    uint32_t pad;
+    uint32_t reps;              // log2 of the window's copies
 };
 
 struct BatchArgs {
@@ -189,7 +189,7 @@ struct BatchArgs {
     uint32_t* counter;          // work-queue head of the group
     const uint64_t* chunk_base; // [n_streams + 1] first workspace chunk of each stream
     const uint32_t* block_base; // [n_streams + 1] first workspace block of each stream
-    uint32_t priv_bins;         // largest private histogram (bins) of the group
+    uint32_t win_words;         // 64-bit LDS words of the group's local windows
     uint32_t queue_words;       // lookup pass: LDS words per wave for the window PLA's queue
 };
 
@@ -306,6 +306,11 @@ sinet_status launch_batch_far(uint32_t kind, const BatchArgs& a, const PartWs& w
                               hipStream_t s);
 sinet_status launch_zero_jobs(const ZeroJob* jobs, uint32_t n_jobs, hipStream_t s);
 sinet_status launch_scan_fill(const PartWs& w, hipStream_t s);
+// 64-bit words of the local window of a stage-1 workgroup whose largest table
+// takes `table` bytes of LDS (0: no room)
+uint32_t batch_window_words(size_t table);
+constexpr uint64_t kLocalMinPerBin = 16;        // sessions per bin from which the local reduce pays
+constexpr uint64_t kLocalSureSpan = 120000;     // time (ms) a window must span to hold any log's jitter
 uint32_t batch_stage1_blocks_per_cu(uint32_t kind, size_t lds);
 // lookups that run as their own pass before stage 1
 bool lookup_splits(const DevTable& t);

@@ -117,3 +117,42 @@ def test_forced_reduces_equal_oracle(mode, n, n_bins, width):
         sinet.set_reduce("auto")
     for got, e in zip(out, exp):
         assert np.array_equal(sinet.to_host_u64(got), e + e)
+
+
+@pytest.mark.parametrize("chunk", [None, 2_048, 1 << 20])
+def test_batch_with_coarse_streams_equals_oracle(chunk):
+    """Streams of every reduce and label lookup in one plan, over two replays."""
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    cases = [CASES[0], CASES[2], (200_003, 60_000, 3_000, 1_000, 60, "sorted", True, "nested"),
+             (300_001, 3_600_000, 5_000, 1_000, 3_000, "stray", True, "edges"),   # a moving window
+             (150_001, 3_600_000, 5_000, 1_000, 3_000, "shuffled", False, "trie"),
+             (100_003, 600_000, 5_000, 10, 60_000, "sorted", False, "nested"),    # records
+             (120_007, 600_000, 5_000, 10, 60_000, "sorted", False, "trie")]
+    streams, exps, keep = [], [], []
+    for j, (n, span, jitter, width, n_bins, order, big, kind) in enumerate(cases):
+        rng = np.random.default_rng(100 + j)
+        base, plen, tab = _tables(sinet, kind)
+        ts, by = _sessions(rng, n, span, jitter, order, big)
+        src, dst = (rng.integers(0, 1 << 32, n).astype(np.uint32) for _ in range(2))
+        exps.append(oracle.pipeline(base, plen, ts, src, dst, by, 900, width, n_bins))
+        lab = torch.empty(n, dtype=torch.uint8, device="cuda") if j % 2 == 0 else None
+        out = [torch.full_like(t, -1) for t in sinet.new_hist(n_bins)]
+        keep.append((lab, out))
+        streams.append(sinet.BatchStream(tab, sinet.to_device_u32(ts), sinet.to_device_u32(src),
+                                         sinet.to_device_u32(dst), sinet.to_device_u64(by), 900, width,
+                                         n_bins, label=lab, out=out))
+    print("batch of coarse streams", chunk, flush=True)
+    tune = None
+    if chunk:
+        tune = sinet.Tune()
+        tune.block, tune.chunk, tune.grid = 512, chunk, 0
+    plan = sinet.BatchPlan(streams, tune)
+    for _ in range(2):
+        plan.run()
+        torch.cuda.synchronize()
+        for j, ((lab, out), (elab, ec, eb, ed)) in enumerate(zip(keep, exps)):
+            assert lab is None or np.array_equal(lab.cpu().numpy(), elab), j
+            for got, e in zip(out, (ec, eb, ed)):
+                assert np.array_equal(sinet.to_host_u64(got), e), j
