@@ -2124,7 +2124,11 @@ __global__ void k_zero_jobs(const ZeroJob* __restrict__ jobs, uint32_t n_jobs) {
 // pass is a streaming read of the address columns: the /16 filter in LDS
 // rejects most addresses with one LDS read, only addresses in blocks the
 // list touches run the interval search, and the timestamps and byte counts
-// are loaded only for a lane whose four sessions include a match.  Small
+// are loaded only for matches.  Bound by the address read and vector issue:
+// searched in every iteration, a wave paid a whole search round (12 steps and
+// the matches' loads) for about a dozen addresses, and eight ballots to queue
+// them; collected over iterations and queued one per lane and round, 4e8
+// sessions with 1,177 hosts take 0.70 ms instead of 0.92 (4.6 TB/s).  Small
 // histograms live in LDS per workgroup (merged with atomics at the end);
 // larger ones take device-scope atomics directly.
 // ---------------------------------------------------------------------------
@@ -2206,62 +2210,12 @@ __device__ __forceinline__ void watch_add(const WatchParams& w, uint32_t* hc, un
     }
 }
 
-// Match codes of the lane's eight addresses (four sources, four
-// destinations): key + 1 from the LDS key array when given, else the owner
-// row + 1 from device memory, 0 for no match; the interval search is shared
-// by the wave: an address whose /16 block
-// the list touches goes to the wave's queue in LDS (slots ordered by address
-// number, then lane, from ballots), the wave searches the queue 64 entries at
-// a time (one entry per lane) and each lane reads its answers back.  Few
-// addresses need the search, so a wave runs one round of it rather than
-// eight searches in every lane.  Ballots see only the lanes running the call,
-// so lanes a branch masked off neither add entries nor take them.  The queue
-// is only touched by its own wave,
-// whose LDS operations complete in order; the wavefront fences keep the
-// compiler from moving them across each other.
-template <uint32_t KIND>
-__device__ __forceinline__ void owners8_shared(const DevTable& t, const LdsView& v, const uint32_t* a,
-                                               uint32_t* queue, const uint32_t* lkey, uint32_t* code) {
-    uint32_t need = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        code[q] = 0;
-        const uint32_t st = (v.filter[a[q] >> 20] >> (((a[q] >> 16) & 15u) * 2)) & 3u;
-        need |= (st != 0u ? 1u : 0u) << q;
-    }
-    if (__ballot(need != 0u) == 0ull) return;
-    uint32_t slot[8];
-    uint32_t total = 0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const uint64_t m = __ballot((need >> q) & 1u);
-        slot[q] = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if ((need >> q) & 1u) queue[slot[q]] = a[q];
-        total += (uint32_t)__popcll(m);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    // the lanes running this call (a branch may have masked some off) take
-    // the queue's entries in turn
-    const uint64_t act = __ballot(1);
-    const uint32_t n_act = (uint32_t)__popcll(act);
-    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-    for (uint32_t b = 0; b < total; b += n_act) {
-        const uint32_t k = b + rank;
-        if (k < total) {
-            const uint32_t x = queue[k];
-            uint32_t j;
-            intervals<KIND, 1>(t, v, &x, &j, 1u);
-            queue[k] = lkey ? lkey[j] : *glob(t.owner + j);
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        if ((need >> q) & 1u) code[q] = queue[slot[q]];
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the queue is reused next tile
-}
+// Addresses that the /16 filter lets through, per wave in LDS: the address and
+// where it came from (iteration << 9 | lane << 3 | session << 1 | direction).
+// Few are let through (2 % with 1,177 hosts), so they are collected over
+// iterations and searched 64 at a time, one per lane; a lane whose address is on
+// the list then loads that session's time and byte count and adds it.
+constexpr uint32_t kWatchQueue = 128;  // entries of a wave: fewer than 64 kept and 64 added
 
 template <uint32_t KIND, bool PRIV>
 __global__ void __launch_bounds__(kWatchBlock) k_watch(WatchParams w) {
@@ -2269,9 +2223,9 @@ __global__ void __launch_bounds__(kWatchBlock) k_watch(WatchParams w) {
     uint32_t used = 0;
     const PassParams& p = w.p;
     const LdsView v = stage_lds<KIND>(p.t, lds, &used);
-    // each wave's search queue: eight addresses per lane at most
-    uint32_t* queue = lds + used + (threadIdx.x >> 6) * 512u;
-    if constexpr (KIND != KK_SCAN) used += (kWatchBlock / 64) * 512u;
+    uint32_t* qa = lds + used + (threadIdx.x >> 6) * (2 * kWatchQueue);  // this wave's queue
+    uint32_t* qi = qa + kWatchQueue;
+    if constexpr (KIND != KK_SCAN) used += (kWatchBlock / 64) * 2 * kWatchQueue;
     // key + 1 (0: no match) of every interval, when the list is small enough
     uint32_t* lkey = nullptr;
     if constexpr (KIND != KK_SCAN) {
@@ -2301,61 +2255,83 @@ __global__ void __launch_bounds__(kWatchBlock) k_watch(WatchParams w) {
     WatchDropped d{};
     const uint64_t groups = (p.n + 3) / 4;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint32_t lane = lane_id();
+    const uint64_t g0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, wave_g0 = g0 - lane;
     // the next group's addresses are loaded while this one is looked up
     auto full = [&](uint64_t g) { return w.vec && g * 4 + 4 <= p.n; };
-    uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint4 cs = make_uint4(0, 0, 0, 0), cd = cs;
-    if (g < groups && full(g)) {
-        cs = gload4(p.src + g * 4);
-        cd = gload4(p.dst + g * 4);
+    if (full(g0)) {
+        cs = gload4_nt(p.src + g0 * 4);
+        cd = gload4_nt(p.dst + g0 * 4);
     }
-    // a group's matches are added one iteration later, so the loads of their
-    // times and byte counts overlap the next group's lookups
-    uint32_t pcode[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    uint4 pt = make_uint4(0, 0, 0, 0);
-    ulonglong2 pb01 = make_ulonglong2(0, 0), pb23 = pb01;
-    bool pend = false;
-    auto apply = [&]() {
-        if (!pend) return;
-        const uint32_t ts[4] = {pt.x, pt.y, pt.z, pt.w};
-        const uint64_t by[4] = {pb01.x, pb01.y, pb23.x, pb23.y};
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (pcode[q])
-                watch_add<PRIV>(w, hc, hb, q >> 2, pcode[q], lkey != nullptr, ts[q & 3], by[q & 3], d);
-        pend = false;
-    };
-    for (; g < groups; g += stride) {
-        const uint64_t i = g * 4;
-        uint4 ns = cs, nd = cd;
-        if (g + stride < groups && full(g + stride)) {
-            ns = gload4(p.src + (g + stride) * 4);
-            nd = gload4(p.dst + (g + stride) * 4);
+    uint32_t held = 0;  // entries of the wave's queue (wave-uniform)
+    // search and add the queue's last 64 entries (or all that are left)
+    auto drain = [&]() {
+        const uint32_t n = min(held, 64u);
+        held -= n;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        if (lane < n) {
+            const uint32_t x = qa[held + lane], id = qi[held + lane];
+            uint32_t j;
+            intervals<KIND == KK_SCAN ? KK_BSEARCH : KIND, 1>(p.t, v, &x, &j, 1u);
+            const uint32_t code = lkey ? lkey[j] : *glob(p.t.owner + j);
+            if (code) {
+                const uint64_t i = (wave_g0 + (id >> 9) * stride + ((id >> 3) & 63u)) * 4 + ((id >> 1) & 3u);
+                watch_add<PRIV>(w, hc, hb, id & 1u, code, lkey != nullptr, *glob(p.ts + i), *glob(p.bytes + i), d);
+            }
         }
-        if (full(g)) {
-            const uint4 s4 = cs, d4 = cd;
-            const uint32_t a[8] = {s4.x, s4.y, s4.z, s4.w, d4.x, d4.y, d4.z, d4.w};
-            uint32_t code[8];
-            if constexpr (KIND == KK_SCAN) owners<KIND, 8>(p.t, v, a, code);
-            else owners8_shared<KIND>(p.t, v, a, queue, lkey, code);
-            uint32_t any = 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // its slots are written again
+    };
+    uint32_t it = 0;
+    for (uint64_t wg = wave_g0; wg < groups; wg += stride, ++it) {  // wave-uniform
+        const uint64_t g = wg + lane, i = g * 4;
+        uint4 ns = cs, nd = cd;
+        if (full(g + stride)) {
+            ns = gload4_nt(p.src + (g + stride) * 4);
+            nd = gload4_nt(p.dst + (g + stride) * 4);
+        }
+        const uint32_t a[8] = {cs.x, cs.y, cs.z, cs.w, cd.x, cd.y, cd.z, cd.w};
+        if constexpr (KIND != KK_SCAN) {
+            uint32_t need = 0;  // bit q: address q may be on the list
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint32_t st = (v.filter[a[q] >> 20] >> (((a[q] >> 16) & 15u) * 2)) & 3u;
+                need |= (st != 0u ? 1u : 0u) << q;
+            }
+            if (!full(g)) need = 0;
+            // each lane queues one of its addresses per round
+            for (uint64_t m = __ballot(need != 0u); m; m = __ballot(need != 0u)) {
+                if (need) {
+                    const uint32_t q = (uint32_t)__builtin_ctz(need), at = held + rank_in(m);
+                    const uint32_t lo = q & 2u ? (q & 1u ? cs.w : cs.z) : (q & 1u ? cs.y : cs.x);
+                    const uint32_t hi = q & 2u ? (q & 1u ? cd.w : cd.z) : (q & 1u ? cd.y : cd.x);
+                    qa[at] = q & 4u ? hi : lo;
+                    qi[at] = it << 9 | lane << 3 | (q & 3u) << 1 | q >> 2;
+                    need &= need - 1u;
+                }
+                held += (uint32_t)__popcll(m);
+                if (held >= 64u) drain();
+            }
+        } else if (full(g)) {
+            uint32_t code[8], any = 0;
+            owners<KIND, 8>(p.t, v, a, code);
 #pragma unroll
             for (int q = 0; q < 8; ++q) any |= code[q];
-            apply();  // the previous group's, its loads issued an iteration ago
             if (any) {
-                pt = gload4(p.ts + i);
-                pb01 = gload2(p.bytes + i);
-                pb23 = gload2(p.bytes + i + 2);
+                const uint4 ts = gload4(p.ts + i);
+                const ulonglong2 b01 = gload2(p.bytes + i), b23 = gload2(p.bytes + i + 2);
+                const uint32_t t4[4] = {ts.x, ts.y, ts.z, ts.w};
+                const uint64_t by[4] = {b01.x, b01.y, b23.x, b23.y};
 #pragma unroll
-                for (int q = 0; q < 8; ++q) pcode[q] = code[q];
-                pend = true;
+                for (int q = 0; q < 8; ++q)
+                    if (code[q]) watch_add<PRIV>(w, hc, hb, q >> 2, code[q], false, t4[q & 3], by[q & 3], d);
             }
-        } else {
-            apply();
+        }
+        if (!full(g)) {  // the ragged last group, or unaligned columns
             for (uint64_t e = i; e < p.n && e < i + 4; ++e) {
-                const uint32_t a[2] = {*glob(p.src + e), *glob(p.dst + e)};
+                const uint32_t x[2] = {*glob(p.src + e), *glob(p.dst + e)};
                 uint32_t code[2];
-                owners<KIND, 2>(p.t, v, a, code);
+                owners<KIND, 2>(p.t, v, x, code);
                 if (code[0] | code[1]) {
                     const uint32_t ts = *glob(p.ts + e);
                     const uint64_t by = *glob(p.bytes + e);
@@ -2367,7 +2343,8 @@ __global__ void __launch_bounds__(kWatchBlock) k_watch(WatchParams w) {
         cs = ns;
         cd = nd;
     }
-    apply();
+    if constexpr (KIND != KK_SCAN)
+        while (held) drain();
     d.flush(p.dropped);
     if constexpr (PRIV) {
         __syncthreads();
@@ -3315,7 +3292,7 @@ sinet_status run_watch(const PassParams& p, uint32_t n_keys, int accumulate, hip
     // kinds), the private cells
     const bool lds_keys = kind != KK_SCAN && p.t.m <= kWatchLdsKeys;
     const size_t table_lds = (size_t)p.t.lds_bytes +
-                             (kind == KK_SCAN ? 0 : 4 * 512 * (kWatchBlock / 64)) +
+                             (kind == KK_SCAN ? 0 : 8 * kWatchQueue * (kWatchBlock / 64)) +
                              (lds_keys ? 4ull * p.t.m : 0) + 8;
     const bool priv = cells <= kWatchPrivCells && table_lds + 12 * cells + 8 <= 64 * 1024;
     WatchFn fn = pick_watch(kind, priv);
