@@ -31,6 +31,7 @@
 
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <map>
 #include <mutex>
@@ -75,22 +76,33 @@ constexpr uint64_t kMaxPiece = 1ull << 31;  // sessions per partitioned pass (32
 // loads in flight instead of waiting out one dependent chain per address.
 // ---------------------------------------------------------------------------
 
-// Per-workgroup LDS view of the table.
+// Per-workgroup LDS view of the table.  The pointers say that they address LDS:
+// through generic pointers that are chosen at run time (a filter in LDS or in
+// device memory, a view set inside a loop over streams) the compiler reads LDS
+// with flat loads, which take both kinds of memory's paths and waits.
+typedef const __attribute__((address_space(3))) uint32_t* lds_u32;
+typedef const __attribute__((address_space(3))) float* lds_f32;
 struct LdsView {
-    const uint32_t* io;      // in/out index, or the union's boundaries
-    const uint32_t* filter;  // 2-bit state of every /16 block (interval kinds)
-    const uint32_t* top;     // BSEARCH
-    const uint32_t* member;  // all interval kinds (or global)
-    const uint32_t* cb;      // SCAN
-    const uint32_t* mask;
-    const uint32_t* len;
-    const uint32_t* knot;    // PLA
-    const float* c;
-    const float* g;
-    const uint32_t* radix;   // PLA: first segment of each radix bucket (u16 pairs)
-    const float* w;          // MLP
-    uint32_t* queue;         // lookup pass of the interval kinds: this wave's search queue
+    lds_u32 io;      // in/out index, or the union's boundaries
+    lds_u32 filter;  // 2-bit state of every /16 block (interval kinds)
+    lds_u32 top;     // BSEARCH
+    lds_u32 member;  // all interval kinds, when it is in LDS
+    lds_u32 cb;      // SCAN
+    lds_u32 mask;
+    lds_u32 len;
+    lds_u32 knot;    // PLA
+    lds_f32 c;
+    lds_f32 g;
+    lds_u32 radix;   // PLA: first segment of each radix bucket (u16 pairs)
+    lds_f32 w;       // MLP
+    __attribute__((address_space(3))) uint32_t* queue;  // lookup pass of the interval kinds: this wave's search queue
 };
+
+// Membership bit of interval j.
+__device__ __forceinline__ uint32_t member_bit(const DevTable& t, const LdsView& v, uint32_t j) {
+    const uint32_t w = t.lds_member_words ? v.member[j >> 5] : *glob(t.member + (j >> 5));
+    return (w >> (j & 31u)) & 1u;
+}
 
 // Entries of a wave's search queue: the searches of the 8 address slots (4
 // sessions) of the wave's 64 lanes.
@@ -102,13 +114,15 @@ constexpr int kPlaGroup = 2;
 constexpr uint32_t kPlaQueue = 64u * kPlaGroup;
 
 // Kinds whose lookup pass queues its searches: the binary searches, the trie,
-// the MLP and the PLA.  The window PLA reads each queued window with a quad of
+// the MLP and the PLA.  The window PLA reads each queued window with a pair of
 // lanes; the kinds whose search ends in a leaf of B in global memory (the
 // LDS-sampled binary search, the MLP, a PLA with a wider bound) read each
-// queued leaf with a quad of lanes, one round trip instead of a dependent
-// binary search (on the 1.6e9-session day: sampled binary search 18.9 -> 11.2
-// ms, MLP 23.2 -> 14.4 ms, 256-segment PLA 24.4 -> 13.2 ms; the same PLA queued
-// with its leaf binary searches was slower than unqueued, 24.3 -> 37.5 ms).
+// queued leaf with a pair of lanes, one round trip instead of a dependent
+// binary search (read by quads, on the 1.6e9-session day: sampled binary search
+// 18.9 -> 11.2 ms, MLP 23.2 -> 14.4 ms, 256-segment PLA 24.4 -> 13.2 ms; the
+// same PLA queued with its leaf binary searches was slower than unqueued, 24.3
+// -> 37.5 ms.  Pairs instead of quads, 2e8 addresses of clustered prefixes:
+// sampled binary search 1.42 -> 1.31 ms, MLP 1.90 -> 1.83 ms).
 __host__ __device__ constexpr bool queued_kind(uint32_t kind) {
     return kind == KK_BSEARCH || kind == KK_TRIE || kind == KK_MLP || kind == KK_PLA;
 }
@@ -128,8 +142,7 @@ __device__ __forceinline__ void lds_wave_sync() {
 
 // For each q: the last arr[i] <= a[q] among arr[0..n), given arr[0] <= a[q].
 template <int N>
-__device__ __forceinline__ void upper_last_n(const uint32_t* arr, uint32_t n, const uint32_t* a,
-                                             uint32_t* lo) {
+__device__ __forceinline__ void upper_last_n(lds_u32 arr, uint32_t n, const uint32_t* a, uint32_t* lo) {
 #pragma unroll
     for (int q = 0; q < N; ++q) lo[q] = 0;
     while (n > 1) {
@@ -140,7 +153,7 @@ __device__ __forceinline__ void upper_last_n(const uint32_t* arr, uint32_t n, co
     }
 }
 
-__device__ __forceinline__ uint32_t radix_entry(const uint32_t* radix, uint32_t i) {
+__device__ __forceinline__ uint32_t radix_entry(lds_u32 radix, uint32_t i) {
     return (radix[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu;
 }
 
@@ -159,7 +172,7 @@ __device__ __forceinline__ void leaf_search(const DevTable& t, const uint32_t* a
         const uint32_t half = n >> 1;
 #pragma unroll
         for (int q = 0; q < N; ++q)
-            if ((need >> q) & 1u) j[q] = (t.B[j[q] + half] <= a[q]) ? j[q] + half : j[q];
+            if ((need >> q) & 1u) j[q] = (*glob(t.B + j[q] + half) <= a[q]) ? j[q] + half : j[q];
         n -= half;
     }
 #pragma unroll
@@ -240,10 +253,10 @@ __device__ __forceinline__ void window_search_n(const DevTable& t, const uint32_
         for (int q = 0; q < G; ++q) {
             s[q] = (uint32_t)max(p[q0 + q] - e, 0) & ~3u;
             if ((need >> (q0 + q)) & 1u) {
-                const uint4* b4 = reinterpret_cast<const uint4*>(t.B + s[q]);
+                const uint32_t* b4 = t.B + s[q];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) w[q][v] = b4[v];
-                nx[q] = t.B[s[q] + 16u];  // for the bracket check (in the padding at worst)
+                for (int v = 0; v < 4; ++v) w[q][v] = gload4(b4 + 4 * v);
+                nx[q] = *glob(t.B + s[q] + 16u);  // for the bracket check (in the padding at worst)
             } else {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) w[q][v] = make_uint4(0u, 0u, 0u, 0u);
@@ -265,7 +278,7 @@ __device__ __forceinline__ void window_search_n(const DevTable& t, const uint32_
             uint32_t r = s[q] + c - 1u;
             if (!ok) {
                 atomicAdd(t.fallbacks, 1ull);
-                r = upper_last(t.B, t.m, x);
+                r = upper_last(glob(t.B), t.m, x);
             }
             j[qq] = min(r, t.m - 1);
         }
@@ -288,12 +301,10 @@ __device__ __forceinline__ uint32_t from_lane(uint32_t src, uint32_t x) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src << 2), (int)x);
 }
 
-// Sum over the four lanes of each quad, in every lane of the quad (DPP quad
-// permutations [1,0,3,2] then [2,3,0,1]; every lane active).
-__device__ __forceinline__ uint32_t quad_sum(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false);
-    return x;
+// Sum over the two lanes of each pair, in both (DPP quad permutation [1,0,3,2];
+// every lane active).
+__device__ __forceinline__ uint32_t pair_sum(uint32_t x) {
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);
 }
 
 // Membership bits of the addresses in cut /16 blocks by the window PLA, for a
@@ -304,12 +315,15 @@ __device__ __forceinline__ uint32_t quad_sum(uint32_t x) {
 // Here the addresses that need one, two slots at a time, are ranked with a
 // ballot and mbcnt and queued in LDS; each round gives one queued address to
 // every lane, which finds its segment, evaluates the line and forms the
-// window's first index; then each quad of lanes takes one
+// window's first index; then each pair of lanes takes one
 // address per step (its address and window start moved over with
-// ds_bpermute), each lane loads and compares four of the 16 boundaries, and
-// the quad's counts are added with DPP.  One load instruction covers 16
-// windows.  The lane at place k of a quad then finishes the quad's address of
-// step k: it checks the bracket (falling back to the full search, counted, as
+// ds_bpermute), each lane loads and compares eight of the 16 boundaries, and
+// the pair's counts are added with DPP.  One load instruction covers half of 32
+// windows.  The pass is bound by VALU issue, and a step's moves, address
+// arithmetic and sum cost more than a load: with pairs a round has two steps,
+// with quads it had four (5e8 labels of the 1024-segment table, together with
+// the LDS-typed pointers, 4.05 -> 3.74 ms).  The lane at place k of a pair then
+// finishes the pair's address of step k: it checks the bracket (falling back to the full search, counted, as
 // window_search_n does), reads the interval's membership bit and writes it
 // over the queue entry, from which the address's lane reads it back.
 template <int N>
@@ -343,54 +357,59 @@ __device__ __forceinline__ void pla_window_queued(const DevTable& t, const LdsVi
                 const int pp = clamp_pos(pla_eval(v.knot[sg], v.c[sg], v.g[sg], x), t.m);
                 wb = (uint32_t)max(pp - e, 0) & ~3u;
             }
-            // the round's steps of 16 addresses (at most four; a step past the
+            // the round's steps of 32 addresses (at most two; a step past the
             // round's entries is skipped, wave-uniformly): every window load,
             // and the boundary after each window for the bracket check, is
             // issued before any is used
-            const uint32_t me = lane & 3u;
-            uint32_t xx[4], bb[4], c[4], nx = 0xFFFFFFFFu;
-            uint4 w[4];
+            const uint32_t me = lane & 1u;
+            uint32_t xx[2], bb[2], c[2], nx = 0xFFFFFFFFu;
+            uint4 w[2][2];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < 2; ++k) {
                 xx[k] = 0u;
                 bb[k] = 0u;
-                if (16u * k < nr) {
-                    const uint32_t src = 16u * k + (lane >> 2);
+                if (32u * k < nr) {
+                    const uint32_t src = 32u * k + (lane >> 1);
                     xx[k] = from_lane(src, x);
                     bb[k] = from_lane(src, wb);
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                w[k] = make_uint4(0u, 0u, 0u, 0u);
-                if (16u * k + (lane >> 2) < nr) {  // quad-uniform
-                    w[k] = *reinterpret_cast<const uint4*>(t.B + bb[k] + 4u * me);
-                    if (me == (uint32_t)k) nx = t.B[bb[k] + 16u];  // in the padding at worst
+            for (int k = 0; k < 2; ++k) {
+                w[k][0] = w[k][1] = make_uint4(0u, 0u, 0u, 0u);
+                if (32u * k + (lane >> 1) < nr) {  // pair-uniform
+                    w[k][0] = gload4(t.B + bb[k] + 4u * me);
+                    w[k][1] = gload4(t.B + bb[k] + 4u * me + 8u);
+                    if (me == (uint32_t)k) nx = *glob(t.B + bb[k] + 16u);  // in the padding at worst
                 }
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < 2; ++k) {
                 c[k] = 0u;
-                if (16u * k < nr)
-                    c[k] = quad_sum((uint32_t)(w[k].x <= xx[k]) + (uint32_t)(w[k].y <= xx[k]) +
-                                    (uint32_t)(w[k].z <= xx[k]) + (uint32_t)(w[k].w <= xx[k]));
+                if (32u * k < nr) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        c[k] += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
+                                (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
+                    c[k] = pair_sum(c[k]);
+                }
             }
-            // each lane finishes the step of its place in the quad: the bracket
+            // each lane finishes the step of its place in the pair: the bracket
             // check, the interval's membership bit over the queue entry
-            const uint32_t cm = me == 0u ? c[0] : me == 1u ? c[1] : me == 2u ? c[2] : c[3];
-            const uint32_t xm = me == 0u ? xx[0] : me == 1u ? xx[1] : me == 2u ? xx[2] : xx[3];
-            const uint32_t bm = me == 0u ? bb[0] : me == 1u ? bb[1] : me == 2u ? bb[2] : bb[3];
-            const uint32_t src = 16u * me + (lane >> 2);
+            const uint32_t cm = me == 0u ? c[0] : c[1];
+            const uint32_t xm = me == 0u ? xx[0] : xx[1];
+            const uint32_t bm = me == 0u ? bb[0] : bb[1];
+            const uint32_t src = 32u * me + (lane >> 1);
             if (src < nr) {
                 bool ok = cm >= 1u;
                 if (cm == 16u && bm + 16u < t.m) ok = xm < nx;
                 uint32_t j = bm + cm - 1u;
                 if (!ok) {
                     atomicAdd(t.fallbacks, 1ull);
-                    j = upper_last(t.B, t.m, xm);
+                    j = upper_last(glob(t.B), t.m, xm);
                 }
                 j = min(j, t.m - 1);
-                v.queue[r + src] = (v.member[j >> 5] >> (j & 31)) & 1u;
+                v.queue[r + src] = member_bit(t, v, j);
             }
         }
         lds_wave_sync();
@@ -413,7 +432,7 @@ __device__ __forceinline__ void leaf_blocks(const DevTable& t, const LdsView& v,
         int p[N];
 #pragma unroll
         for (int q = 0; q < N; ++q)
-            p[q] = (need >> q) & 1u ? clamp_pos(mlp_predict(v.w, t.m_f, a[q]), t.m) : 0;
+            p[q] = (need >> q) & 1u ? clamp_pos(mlp_predict((const float*)v.w, t.m_f, a[q]), t.m) : 0;
         learned_top_n<N>(t, v, a, p, b, need);
     } else if constexpr (KIND == KK_PLA) {  // a PLA whose bound is too wide for one window
         int p[N];
@@ -430,65 +449,65 @@ __device__ __forceinline__ void leaf_blocks(const DevTable& t, const LdsView& v,
     }
 }
 
-// Leaves read by quads of lanes: a wave whose 64 lanes are all active holds up
+// Leaves read by pairs of lanes: a wave whose 64 lanes are all active holds up
 // to 128 queued addresses x[h] (entry r + 64 h + lane) with their leaf blocks
-// b[h].  For each half, four steps of 16 addresses: a quad takes one address
-// per step (moved over with ds_bpermute), each of its lanes loads NL 16-byte
-// groups of the leaf's 16 NL boundaries and counts those <= the address, and
-// the quad adds its counts with DPP; every load of a half is issued before any
-// is used.  The interval is the leaf's first index plus the count minus one
+// b[h].  For each half, two steps of 32 addresses: a pair takes one address per
+// step (moved over with ds_bpermute), each of its lanes loads every other
+// 16-byte group of the leaf's 16 NL boundaries and counts those <= the address,
+// and the pair adds its counts with DPP; every load of a half is issued before
+// any is used.  The interval is the leaf's first index plus the count minus one
 // (the leaf's first boundary is <= the address, as the sample said), exactly
-// what the leaf's binary search finds.  The lane at place k of a quad then
-// writes the membership bit of its quad's address of step k over the entry.
+// what the leaf's binary search finds.  The lane at place k of a pair then
+// writes the membership bit of its pair's address of step k over the entry.
+// Pairs instead of quads halve the steps, whose moves, address arithmetic and
+// sums cost more than the further loads (see pla_window_queued).
 template <int NL>
-__device__ __forceinline__ void leaf_quads(const DevTable& t, const LdsView& v, const uint32_t* x,
+__device__ __forceinline__ void leaf_pairs(const DevTable& t, const LdsView& v, const uint32_t* x,
                                            const uint32_t* b, uint32_t r, uint32_t nr,
                                            uint32_t lane) {
-    const uint32_t me = lane & 3u, L = t.top_log2;
+    const uint32_t me = lane & 1u, L = t.top_log2;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         if (64u * h >= nr) break;  // wave-uniform
         const uint32_t nh = min(nr - 64u * h, 64u);  // entries of this half
-        uint32_t xx[4], bb[4], c[4];
-        uint4 w[4][NL];
+        uint32_t xx[2], bb[2], c[2];
+        uint4 w[2][2 * NL];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 2; ++k) {
             xx[k] = 0u;
             bb[k] = 0u;
-            if (16u * k < nh) {
-                const uint32_t src = 16u * k + (lane >> 2);
+            if (32u * k < nh) {
+                const uint32_t src = 32u * k + (lane >> 1);
                 xx[k] = from_lane(src, x[h]);
                 bb[k] = from_lane(src, b[h]);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 2; ++k) {
 #pragma unroll
-            for (int u = 0; u < NL; ++u) w[k][u] = make_uint4(0u, 0u, 0u, 0u);
-            if (16u * k + (lane >> 2) < nh) {  // quad-uniform
-                const uint4* leaf = reinterpret_cast<const uint4*>(t.B + (bb[k] << L));
+            for (int u = 0; u < 2 * NL; ++u) w[k][u] = make_uint4(0u, 0u, 0u, 0u);
+            if (32u * k + (lane >> 1) < nh) {  // pair-uniform
 #pragma unroll
-                for (int u = 0; u < NL; ++u) w[k][u] = leaf[4 * u + me];
+                for (int u = 0; u < 2 * NL; ++u) w[k][u] = gload4(t.B + (bb[k] << L) + 4u * (2 * u + me));
             }
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 2; ++k) {
             c[k] = 0u;
-            if (16u * k < nh) {
+            if (32u * k < nh) {
                 uint32_t n = 0;
 #pragma unroll
-                for (int u = 0; u < NL; ++u)
+                for (int u = 0; u < 2 * NL; ++u)
                     n += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
                          (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
-                c[k] = quad_sum(n);
+                c[k] = pair_sum(n);
             }
         }
-        const uint32_t cm = me == 0u ? c[0] : me == 1u ? c[1] : me == 2u ? c[2] : c[3];
-        const uint32_t bm = me == 0u ? bb[0] : me == 1u ? bb[1] : me == 2u ? bb[2] : bb[3];
-        const uint32_t src = 16u * me + (lane >> 2);
+        const uint32_t cm = me == 0u ? c[0] : c[1], bm = me == 0u ? bb[0] : bb[1];
+        const uint32_t src = 32u * me + (lane >> 1);
         if (src < nh) {
             const uint32_t j = min((bm << L) + cm - 1u, t.m - 1);
-            v.queue[r + 64u * h + src] = (v.member[j >> 5] >> (j & 31)) & 1u;
+            v.queue[r + 64u * h + src] = member_bit(t, v, j);
         }
     }
 }
@@ -505,13 +524,13 @@ __device__ __forceinline__ void intervals(const DevTable& t, const LdsView& v, c
     } else if constexpr (KIND == KK_TRIE) {
         uint32_t e[N];
 #pragma unroll
-        for (int q = 0; q < N; ++q) e[q] = (need >> q) & 1u ? t.trie[a[q] >> 16] : 0x80000000u;
+        for (int q = 0; q < N; ++q) e[q] = (need >> q) & 1u ? *glob(t.trie + (a[q] >> 16)) : 0x80000000u;
 #pragma unroll
         for (int q = 0; q < N; ++q)
-            if (!(e[q] >> 31)) e[q] = t.trie[65536u + e[q] * 256u + ((a[q] >> 8) & 255u)];
+            if (!(e[q] >> 31)) e[q] = *glob(t.trie + 65536u + e[q] * 256u + ((a[q] >> 8) & 255u));
 #pragma unroll
         for (int q = 0; q < N; ++q)
-            if (!(e[q] >> 31)) e[q] = t.trie[65536u + e[q] * 256u + (a[q] & 255u)];
+            if (!(e[q] >> 31)) e[q] = *glob(t.trie + 65536u + e[q] * 256u + (a[q] & 255u));
 #pragma unroll
         for (int q = 0; q < N; ++q) j[q] = e[q] & 0x7FFFFFFFu;
     } else if constexpr (KIND == KK_PLA) {
@@ -532,7 +551,7 @@ __device__ __forceinline__ void intervals(const DevTable& t, const LdsView& v, c
         int p[N];
 #pragma unroll
         for (int q = 0; q < N; ++q)
-            p[q] = (need >> q) & 1u ? clamp_pos(mlp_predict(v.w, t.m_f, a[q]), t.m) : 0;
+            p[q] = (need >> q) & 1u ? clamp_pos(mlp_predict((const float*)v.w, t.m_f, a[q]), t.m) : 0;
         learned_search_n<N>(t, v, a, p, j, need);
     }
 }
@@ -560,8 +579,8 @@ __device__ __forceinline__ uint32_t scan_owner(const DevTable& t, const LdsView&
 // 21 us for the few workgroups of a 10,000-session call; this is 7 rounds of 8
 // independent ones.
 template <int N>
-__device__ __forceinline__ void union_lookup(const uint32_t* un, uint32_t steps, uint32_t in0,
-                                             const uint32_t* a, uint32_t* in) {
+__device__ __forceinline__ void union_lookup(lds_u32 un, uint32_t steps, uint32_t in0, const uint32_t* a,
+                                             uint32_t* in) {
     uint32_t c[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) c[q] = 0;
@@ -581,7 +600,7 @@ template <uint32_t KIND, int N, int QUEUE = 0>
 __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, const uint32_t* a,
                                         bool want_code, uint32_t* in, uint32_t* code) {
     if constexpr (KIND == KK_INOUT) {
-        inout_lookup<N>(v.io, t.io_slot, t.io_list, a, in);
+        inout_lookup<N>((const uint32_t*)v.io, t.io_slot, t.io_list, a, in);
 #pragma unroll
         for (int q = 0; q < N; ++q) code[q] = 0;
     } else if constexpr (KIND == KK_UNION) {
@@ -641,11 +660,11 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
                 }
                 if (cnt) {  // wave-uniform
                     lds_wave_sync();
-                    // leaves of 16 or 32 boundaries in global memory, read by quads
+                    // leaves of 16 or 32 boundaries in global memory, read by pairs
                     // of lanes when the whole wave is active
-                    const bool quads = KIND != KK_TRIE && n_live == 64u && t.n_top > 1 &&
+                    const bool pairs = KIND != KK_TRIE && n_live == 64u && t.n_top > 1 &&
                                        (t.top_log2 == 4 || t.top_log2 == 5);
-                    if (quads) {
+                    if (pairs) {
                         for (uint32_t r = 0; r < cnt; r += 128) {
                             const uint32_t nr = min(cnt - r, 128u);  // wave-uniform
                             uint32_t x[2] = {me < nr ? v.queue[r + me] : 0u,
@@ -653,17 +672,17 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
                             uint32_t b[2] = {0u, 0u};
                             leaf_blocks<KIND, 2>(t, v, x, b,
                                                  (me < nr ? 1u : 0u) | (me + 64u < nr ? 2u : 0u));
-                            if (t.top_log2 == 4) leaf_quads<1>(t, v, x, b, r, nr, me);
-                            else leaf_quads<2>(t, v, x, b, r, nr, me);
+                            if (t.top_log2 == 4) leaf_pairs<1>(t, v, x, b, r, nr, me);
+                            else leaf_pairs<2>(t, v, x, b, r, nr, me);
                         }
                     }
-                    for (uint32_t r = quads ? cnt : 0u; r < cnt; r += 2 * n_live) {
+                    for (uint32_t r = pairs ? cnt : 0u; r < cnt; r += 2 * n_live) {
                         const uint32_t e0 = r + me, e1 = r + n_live + me;
                         uint32_t x[2] = {e0 < cnt ? v.queue[e0] : 0u, e1 < cnt ? v.queue[e1] : 0u};
                         uint32_t j[2] = {0u, 0u};
                         intervals<KIND, 2>(t, v, x, j, (e0 < cnt ? 1u : 0u) | (e1 < cnt ? 2u : 0u));
-                        if (e0 < cnt) v.queue[e0] = (v.member[j[0] >> 5] >> (j[0] & 31)) & 1u;
-                        if (e1 < cnt) v.queue[e1] = (v.member[j[1] >> 5] >> (j[1] & 31)) & 1u;
+                        if (e0 < cnt) v.queue[e0] = member_bit(t, v, j[0]);
+                        if (e1 < cnt) v.queue[e1] = member_bit(t, v, j[1]);
                     }
                     lds_wave_sync();
 #pragma unroll
@@ -685,8 +704,8 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
 #pragma unroll
             for (int q = 0; q < N; ++q) {
                 if (!((need >> q) & 1u)) continue;
-                in[q] = (v.member[j[q] >> 5] >> (j[q] & 31)) & 1u;
-                code[q] = want_code ? t.owner[j[q]] : 0u;
+                in[q] = member_bit(t, v, j[q]);
+                code[q] = want_code ? *glob(t.owner + j[q]) : 0u;
             }
         }
         if (!want_code && t.filter_lds) {
@@ -736,8 +755,8 @@ __device__ __forceinline__ uint32_t label1(const PassParams& p, const LdsView& v
     lookups<KIND, 2, QUEUE>(p.t, v, a, wc, in, code);
     const uint32_t lab = in[0] | (in[1] << 1);
     if (p.label_out) *glob(p.label_out + i) = (uint8_t)lab;
-    if (p.src_inst) *glob(p.src_inst + i) = code[0] ? p.t.inst[code[0] - 1] : SINET_NO_INST;
-    if (p.dst_inst) *glob(p.dst_inst + i) = code[1] ? p.t.inst[code[1] - 1] : SINET_NO_INST;
+    if (p.src_inst) *glob(p.src_inst + i) = code[0] ? *glob(p.t.inst + code[0] - 1) : SINET_NO_INST;
+    if (p.dst_inst) *glob(p.dst_inst + i) = code[1] ? *glob(p.t.inst + code[1] - 1) : SINET_NO_INST;
     return lab;
 }
 
@@ -790,18 +809,18 @@ __device__ __forceinline__ void labels4_from(const PassParams& p, const LdsView&
         }
         if (p.src_inst) {
             uint4 o;
-            o.x = sc[0] ? p.t.inst[sc[0] - 1] : SINET_NO_INST;
-            o.y = sc[1] ? p.t.inst[sc[1] - 1] : SINET_NO_INST;
-            o.z = sc[2] ? p.t.inst[sc[2] - 1] : SINET_NO_INST;
-            o.w = sc[3] ? p.t.inst[sc[3] - 1] : SINET_NO_INST;
+            o.x = sc[0] ? *glob(p.t.inst + sc[0] - 1) : SINET_NO_INST;
+            o.y = sc[1] ? *glob(p.t.inst + sc[1] - 1) : SINET_NO_INST;
+            o.z = sc[2] ? *glob(p.t.inst + sc[2] - 1) : SINET_NO_INST;
+            o.w = sc[3] ? *glob(p.t.inst + sc[3] - 1) : SINET_NO_INST;
             gstore4(p.src_inst + i, o);
         }
         if (p.dst_inst) {
             uint4 o;
-            o.x = dc[0] ? p.t.inst[dc[0] - 1] : SINET_NO_INST;
-            o.y = dc[1] ? p.t.inst[dc[1] - 1] : SINET_NO_INST;
-            o.z = dc[2] ? p.t.inst[dc[2] - 1] : SINET_NO_INST;
-            o.w = dc[3] ? p.t.inst[dc[3] - 1] : SINET_NO_INST;
+            o.x = dc[0] ? *glob(p.t.inst + dc[0] - 1) : SINET_NO_INST;
+            o.y = dc[1] ? *glob(p.t.inst + dc[1] - 1) : SINET_NO_INST;
+            o.z = dc[2] ? *glob(p.t.inst + dc[2] - 1) : SINET_NO_INST;
+            o.w = dc[3] ? *glob(p.t.inst + dc[3] - 1) : SINET_NO_INST;
             gstore4(p.dst_inst + i, o);
         }
     }
@@ -853,8 +872,8 @@ template <uint32_t KIND>
 __device__ __forceinline__ LdsView stage_lds(const DevTable& t, uint32_t* lds, uint32_t* words) {
     LdsView v{};
     uint32_t off = 0;
-    auto copy = [&](const uint32_t* src, uint32_t n) -> const uint32_t* {
-        uint32_t* dst = lds + off;
+    auto copy = [&](const uint32_t* src, uint32_t n) -> lds_u32 {
+        auto* dst = (__attribute__((address_space(3))) uint32_t*)(lds + off);
         for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) dst[k] = *glob(src + k);
         off += n;
         return dst;
@@ -868,21 +887,19 @@ __device__ __forceinline__ LdsView stage_lds(const DevTable& t, uint32_t* lds, u
         v.mask = copy(t.mask, t.n_prefix);
         v.len = copy(t.len, t.n_prefix);
     } else if constexpr (KIND != KK_LABEL_IN) {
-        v.filter = t.filter_lds ? copy(t.filter, kFilterWords) : t.filter;
+        if (t.filter_lds) v.filter = copy(t.filter, kFilterWords);
         if constexpr (KIND == KK_BSEARCH || KIND == KK_MLP) v.top = copy(t.top, t.n_top);
-        if constexpr (KIND == KK_PLA) v.top = t.pla_window ? nullptr : copy(t.top, t.n_top);
+        if constexpr (KIND == KK_PLA)
+            if (!t.pla_window) v.top = copy(t.top, t.n_top);
         if constexpr (KIND == KK_PLA) {
             v.knot = copy(t.knot, t.segments);
-            v.c = reinterpret_cast<const float*>(
-                copy(reinterpret_cast<const uint32_t*>(t.pla_c), t.segments));
-            v.g = reinterpret_cast<const float*>(
-                copy(reinterpret_cast<const uint32_t*>(t.pla_g), t.segments));
+            v.c = (lds_f32)copy(reinterpret_cast<const uint32_t*>(t.pla_c), t.segments);
+            v.g = (lds_f32)copy(reinterpret_cast<const uint32_t*>(t.pla_g), t.segments);
             v.radix = copy(t.radix, radix_words(t.radix_bits));
         }
         if constexpr (KIND == KK_MLP)
-            v.w = reinterpret_cast<const float*>(
-                copy(reinterpret_cast<const uint32_t*>(t.mlp), SINET_MLP_PARAMS));
-        v.member = t.lds_member_words ? copy(t.member, t.lds_member_words) : t.member;
+            v.w = (lds_f32)copy(reinterpret_cast<const uint32_t*>(t.mlp), SINET_MLP_PARAMS);
+        if (t.lds_member_words) v.member = copy(t.member, t.lds_member_words);
     }
     *words = off;
     __syncthreads();
@@ -903,7 +920,7 @@ __device__ __forceinline__ void pass_body(const PassParams& p, const FarList& fa
     if (HM == H_ATOMIC && far.list && *glob(far.count) == 0) return;  // before the table is staged
     LdsView v = stage_lds<KIND>(p.t, lds, &used);
     if constexpr (HM == H_NONE && queued_kind(KIND)) {
-        if (p.queue_words) v.queue = lds + used + (threadIdx.x >> 6) * p.queue_words;
+        if (p.queue_words) v.queue = (__attribute__((address_space(3))) uint32_t*)(lds + used + (threadIdx.x >> 6) * p.queue_words);
     }
     Dropped d{};
     if (HM == H_ATOMIC && far.list) {
@@ -2065,8 +2082,9 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_lookup(BatchArgs a) {
             // the window PLA's search queue, after the table (a.queue_words
             // per wave when the launch made room for it)
             if constexpr (KIND == KK_PLA)  // window PLAs only (the wider search needs a larger queue)
-                v.queue = a.queue_words && s_bs.p.t.pla_window ? lds + used + (tid >> 6) * a.queue_words
-                                                               : nullptr;
+                v.queue = a.queue_words && s_bs.p.t.pla_window
+                              ? (__attribute__((address_space(3))) uint32_t*)(lds + used + (tid >> 6) * a.queue_words)
+                              : nullptr;
             staged = si;
         }
         BatchStreamDev bs;
@@ -2430,6 +2448,15 @@ int blocks_per_cu(const void* fn, int block, size_t lds) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, block, lds) != hipSuccess || nb < 1)
         nb = 1;
+    // The answer divides the 160 KB by the bytes asked for, but LDS is handed
+    // out in 1,280-byte granules: five workgroups of 32 KB are reported and
+    // four are resident, and a grid for five runs a fifth round of a quarter
+    // of its workgroups (0.91 against 0.69 ms for 2e8 addresses).
+    hipFuncAttributes at{};
+    if (hipFuncGetAttributes(&at, fn) == hipSuccess) {
+        const size_t granules = (lds + at.sharedSizeBytes + 1279) / 1280;
+        if (granules) nb = std::max(1, std::min(nb, (int)(128 / granules)));
+    }
     cache[key] = nb;
     return nb;
 }

@@ -10,7 +10,8 @@ namespace sinet {
 
 // Index of the last arr[i] <= a among arr[0..n), given arr[0] <= a.  The trip
 // count depends on n only, so lanes of a wave stay converged.
-__device__ __forceinline__ uint32_t upper_last(const uint32_t* arr, uint32_t n, uint32_t a) {
+template <class P>  // a pointer to uint32_t in any address space
+__device__ __forceinline__ uint32_t upper_last(P arr, uint32_t n, uint32_t a) {
     uint32_t lo = 0;
     while (n > 1) {
         uint32_t half = n >> 1;
