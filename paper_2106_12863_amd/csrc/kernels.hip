@@ -108,10 +108,10 @@ __device__ __forceinline__ uint32_t member_bit(const DevTable& t, const LdsView&
 // sessions) of the wave's 64 lanes.
 constexpr uint32_t kSearchQueue = 512;
 
-// The window PLA queues the searches of two address slots at a time (128
-// entries per wave: the PLA's tables leave little LDS beside them).
-constexpr int kPlaGroup = 2;
-constexpr uint32_t kPlaQueue = 64u * kPlaGroup;
+// The window PLA's queue per wave: a ring of 128 addresses (fewer than 64 wait
+// when a slot's up to 64 are added; the PLA's tables leave little LDS beside
+// them).
+constexpr uint32_t kPlaQueue = 128;
 
 // Kinds whose lookup pass queues its searches: the binary searches, the trie,
 // the MLP and the PLA.  The window PLA reads each queued window with a pair of
@@ -307,116 +307,121 @@ __device__ __forceinline__ uint32_t pair_sum(uint32_t x) {
     return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false);
 }
 
+// One round of the window PLA's queue: the membership bits of the nr <= 64
+// addresses at places head.. of the wave's ring, one bit per address in order.
+// Lane s takes the address of place E(s) = 2 (s mod 32) + s / 32, finds its
+// segment, evaluates the line and forms the window's first index; then, in two
+// steps of 32 addresses, each pair of lanes takes one address (moved over with
+// ds_bpermute), each lane loads and compares eight of the 16 boundaries, and
+// the pair's counts are added with DPP.  One load instruction covers half of 32
+// windows.  The lane at place k of a pair then finishes the pair's address of
+// step k, which by the choice of E is the address whose place is that lane's
+// own index: it checks the bracket (falling back to the full search, counted,
+// as window_search_n does) and reads the interval's membership bit.  The
+// boundary after a window is read only where all 16 are <= the address: read
+// with the window for every address it took up to 64 cache lines per round
+// (5e8 labels 3.47 -> 3.27 ms without).
+// The pass is bound by VALU issue, and a step's moves, address arithmetic and
+// sum cost more than a load: with pairs a round has two steps, with quads it
+// had four (5e8 labels of the 1024-segment table, together with the LDS-typed
+// pointers, 4.05 -> 3.74 ms).
+__device__ __forceinline__ unsigned long long pla_round(const DevTable& t, const LdsView& v,
+                                                        uint32_t head, uint32_t nr, uint32_t lane) {
+    const int e = (int)t.max_err;
+    const uint32_t place = ((lane & 31u) << 1) | (lane >> 5);
+    // (a lane without an address searches address 0, in bounds like any other,
+    // and its bit is dropped: no load is conditional)
+    const uint32_t x = place < nr ? v.queue[(head + place) & (kPlaQueue - 1u)] : 0u;
+    // radix bucket -> candidate segments -> last knot <= x -> line
+    const uint32_t rb = x >> (32 - t.radix_bits);
+    const uint32_t s0 = radix_entry(v.radix, rb), s1 = radix_entry(v.radix, rb + 1);
+    const uint32_t sg = s0 + upper_last(v.knot + s0, s1 - s0 + 1, x);
+    const int pp = clamp_pos(pla_eval(v.knot[sg], v.c[sg], v.g[sg], x), t.m);
+    const uint32_t wb = (uint32_t)max(pp - e, 0) & ~3u;
+    // every window load, and the boundary after each window for the bracket
+    // check, is issued before any is used
+    const uint32_t me = lane & 1u;
+    uint32_t xx[2], bb[2], c[2];
+    uint4 w[2][2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t src = 32u * k + (lane >> 1);
+        xx[k] = from_lane(src, x);
+        bb[k] = from_lane(src, wb);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        w[k][0] = gload4(t.B + bb[k] + 4u * me);
+        w[k][1] = gload4(t.B + bb[k] + 4u * me + 8u);
+    }
+    const uint32_t xm = me == 0u ? xx[0] : xx[1];
+    const uint32_t bm = me == 0u ? bb[0] : bb[1];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        c[k] = 0u;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            c[k] += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
+                    (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
+        c[k] = pair_sum(c[k]);
+    }
+    const uint32_t cm = me == 0u ? c[0] : c[1];
+    uint32_t bit = 0;
+    if (lane < nr) {
+        bool ok = cm >= 1u;
+        if (cm == 16u && bm + 16u < t.m) ok = xm < *glob(t.B + bm + 16u);
+        uint32_t j = bm + cm - 1u;
+        if (!ok) {
+            atomicAdd(t.fallbacks, 1ull);
+            j = upper_last(glob(t.B), t.m, xm);
+        }
+        bit = member_bit(t, v, min(j, t.m - 1));
+    }
+    return __ballot(bit != 0u);
+}
+
 // Membership bits of the addresses in cut /16 blocks by the window PLA, for a
 // wave whose 64 lanes are all active.  Unqueued, each address reads its
 // 16-boundary window with four 16-byte loads of its own lane, in waves where
 // about a third of the lanes need a search, so a wave pays every slot's
 // segment search, window loads and compares whichever of its lanes need them.
-// Here the addresses that need one, two slots at a time, are ranked with a
-// ballot and mbcnt and queued in LDS; each round gives one queued address to
-// every lane, which finds its segment, evaluates the line and forms the
-// window's first index; then each pair of lanes takes one
-// address per step (its address and window start moved over with
-// ds_bpermute), each lane loads and compares eight of the 16 boundaries, and
-// the pair's counts are added with DPP.  One load instruction covers half of 32
-// windows.  The pass is bound by VALU issue, and a step's moves, address
-// arithmetic and sum cost more than a load: with pairs a round has two steps,
-// with quads it had four (5e8 labels of the 1024-segment table, together with
-// the LDS-typed pointers, 4.05 -> 3.74 ms).  The lane at place k of a pair then
-// finishes the pair's address of step k: it checks the bracket (falling back to the full search, counted, as
-// window_search_n does), reads the interval's membership bit and writes it
-// over the queue entry, from which the address's lane reads it back.
+// Here the addresses that need one are ranked with a ballot and mbcnt and
+// queued in a ring in LDS; whenever 64 are waiting, a round (pla_round) gives
+// one to every lane, and the round's 64 bits, in queue order, go to two lanes of
+// a register, from which each address's lane fetches its own (ds_bpermute) once
+// the last, partial round has run.  Queued two slots at a time, 2e8 addresses of
+// clustered prefixes took four rounds of 43 busy lanes per iteration; the ring
+// takes three, of which two are full (1.50 -> 1.24 ms; 5e8 sessions' labels 3.73
+// -> 3.07 ms, with the filter state handed over as it is and the rare load).
 template <int N>
 __device__ __forceinline__ void pla_window_queued(const DevTable& t, const LdsView& v,
-                                                  const uint32_t* a, uint32_t need, uint32_t* in) {
+                                                  const uint32_t* a, const uint32_t* st, uint32_t* in) {
     const uint32_t lane = lane_id();
-    const int e = (int)t.max_err;
-#pragma unroll
-    for (int q0 = 0; q0 < N; q0 += kPlaGroup) {
-        uint32_t slot[kPlaGroup], cnt = 0;
-#pragma unroll
-        for (int k = 0; k < kPlaGroup; ++k) {
-            const bool nd = (need >> (q0 + k)) & 1u;
-            const unsigned long long m = __ballot(nd);
-            slot[k] = cnt + rank_in(m);
-            if (nd) v.queue[slot[k]] = a[q0 + k];
-            cnt += (uint32_t)__popcll(m);
-        }
-        if (cnt == 0) continue;  // wave-uniform
+    uint32_t pos[N], head = 0, tail = 0;  // head, tail: wave-uniform
+    uint32_t bits = 0;  // lane w: results of the places 32 w .. 32 w + 31
+    auto round = [&](uint32_t nr) {
         lds_wave_sync();
-        for (uint32_t r = 0; r < cnt; r += 64) {
-            const uint32_t nr = min(cnt - r, 64u);  // entries this round (wave-uniform)
-            const bool mine = lane < nr;
-            const uint32_t x = mine ? v.queue[r + lane] : 0u;
-            uint32_t wb = 0;
-            if (mine) {
-                // radix bucket -> candidate segments -> last knot <= x -> line
-                const uint32_t rb = x >> (32 - t.radix_bits);
-                const uint32_t s0 = radix_entry(v.radix, rb), s1 = radix_entry(v.radix, rb + 1);
-                const uint32_t sg = s0 + upper_last(v.knot + s0, s1 - s0 + 1, x);
-                const int pp = clamp_pos(pla_eval(v.knot[sg], v.c[sg], v.g[sg], x), t.m);
-                wb = (uint32_t)max(pp - e, 0) & ~3u;
-            }
-            // the round's steps of 32 addresses (at most two; a step past the
-            // round's entries is skipped, wave-uniformly): every window load,
-            // and the boundary after each window for the bracket check, is
-            // issued before any is used
-            const uint32_t me = lane & 1u;
-            uint32_t xx[2], bb[2], c[2], nx = 0xFFFFFFFFu;
-            uint4 w[2][2];
+        const unsigned long long m = pla_round(t, v, head, nr, lane);
+        lds_wave_sync();  // read before the ring's places are written again
+        if ((lane & ~1u) == head >> 5) bits = (uint32_t)(m >> (32u * (lane & 1u)));
+    };
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                xx[k] = 0u;
-                bb[k] = 0u;
-                if (32u * k < nr) {
-                    const uint32_t src = 32u * k + (lane >> 1);
-                    xx[k] = from_lane(src, x);
-                    bb[k] = from_lane(src, wb);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                w[k][0] = w[k][1] = make_uint4(0u, 0u, 0u, 0u);
-                if (32u * k + (lane >> 1) < nr) {  // pair-uniform
-                    w[k][0] = gload4(t.B + bb[k] + 4u * me);
-                    w[k][1] = gload4(t.B + bb[k] + 4u * me + 8u);
-                    if (me == (uint32_t)k) nx = *glob(t.B + bb[k] + 16u);  // in the padding at worst
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                c[k] = 0u;
-                if (32u * k < nr) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-                        c[k] += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
-                                (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
-                    c[k] = pair_sum(c[k]);
-                }
-            }
-            // each lane finishes the step of its place in the pair: the bracket
-            // check, the interval's membership bit over the queue entry
-            const uint32_t cm = me == 0u ? c[0] : c[1];
-            const uint32_t xm = me == 0u ? xx[0] : xx[1];
-            const uint32_t bm = me == 0u ? bb[0] : bb[1];
-            const uint32_t src = 32u * me + (lane >> 1);
-            if (src < nr) {
-                bool ok = cm >= 1u;
-                if (cm == 16u && bm + 16u < t.m) ok = xm < nx;
-                uint32_t j = bm + cm - 1u;
-                if (!ok) {
-                    atomicAdd(t.fallbacks, 1ull);
-                    j = upper_last(glob(t.B), t.m, xm);
-                }
-                j = min(j, t.m - 1);
-                v.queue[r + src] = member_bit(t, v, j);
-            }
+    for (int q = 0; q < N; ++q) {
+        const bool nd = st[q] == 2u;
+        const unsigned long long m = __ballot(nd);
+        pos[q] = tail + rank_in(m);
+        if (nd) v.queue[pos[q] & (kPlaQueue - 1u)] = a[q];
+        tail += (uint32_t)__popcll(m);
+        if (tail - head >= 64u) {
+            round(64u);
+            head += 64u;
         }
-        lds_wave_sync();
+    }
+    if (tail != head) round(tail - head);
 #pragma unroll
-        for (int k = 0; k < kPlaGroup; ++k)
-            if ((need >> (q0 + k)) & 1u) in[q0 + k] = v.queue[slot[k]];
-        lds_wave_sync();  // read back before the queue is written again
+    for (int q = 0; q < N; ++q) {
+        const uint32_t w = from_lane(pos[q] >> 5, bits);
+        in[q] = st[q] == 2u ? __builtin_amdgcn_ubfe(w, pos[q] & 31u, 1u) : st[q];
     }
 }
 
@@ -620,18 +625,15 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
             need = 0;
 #pragma unroll
             for (int q = 0; q < N; ++q) {
-                st[q] = (v.filter[a[q] >> 20] >> (((a[q] >> 16) & 15u) * 2)) & 3u;
+                st[q] = __builtin_amdgcn_ubfe(v.filter[a[q] >> 20], (a[q] >> 15) & 30u, 2u);
                 need |= (st[q] == 2u ? 1u : 0u) << q;
             }
         }
         if constexpr ((QUEUE & kQueueWindow) && KIND == KK_PLA) {
             if (v.queue && !want_code && t.filter_lds && t.pla_window && __ballot(1) == ~0ull) {
-                pla_window_queued<N>(t, v, a, need, in);
+                pla_window_queued<N>(t, v, a, st, in);
 #pragma unroll
-                for (int q = 0; q < N; ++q) {
-                    if (st[q] < 2u) in[q] = st[q];
-                    code[q] = 0;
-                }
+                for (int q = 0; q < N; ++q) code[q] = 0;
                 return;
             }
         }
