@@ -122,7 +122,8 @@ constexpr uint32_t kPlaQueue = 128;
 // 18.9 -> 11.2 ms, MLP 23.2 -> 14.4 ms, 256-segment PLA 24.4 -> 13.2 ms; the
 // same PLA queued with its leaf binary searches was slower than unqueued, 24.3
 // -> 37.5 ms.  Pairs instead of quads, 2e8 addresses of clustered prefixes:
-// sampled binary search 1.42 -> 1.31 ms, MLP 1.90 -> 1.83 ms).
+// sampled binary search 1.42 -> 1.31 ms, MLP 1.90 -> 1.83 ms; and without
+// conditional loads, the filter's answer taken as it is: 1.22 and 1.70 ms).
 __host__ __device__ constexpr bool queued_kind(uint32_t kind) {
     return kind == KK_BSEARCH || kind == KK_TRIE || kind == KK_MLP || kind == KK_PLA;
 }
@@ -460,7 +461,8 @@ __device__ __forceinline__ void leaf_blocks(const DevTable& t, const LdsView& v,
 // step (moved over with ds_bpermute), each of its lanes loads every other
 // 16-byte group of the leaf's 16 NL boundaries and counts those <= the address,
 // and the pair adds its counts with DPP; every load of a half is issued before
-// any is used.  The interval is the leaf's first index plus the count minus one
+// any is used (a place without an address reads leaf 0, so no load is
+// conditional).  The interval is the leaf's first index plus the count minus one
 // (the leaf's first boundary is <= the address, as the sample said), exactly
 // what the leaf's binary search finds.  The lane at place k of a pair then
 // writes the membership bit of its pair's address of step k over the entry.
@@ -479,34 +481,23 @@ __device__ __forceinline__ void leaf_pairs(const DevTable& t, const LdsView& v, 
         uint4 w[2][2 * NL];
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            xx[k] = 0u;
-            bb[k] = 0u;
-            if (32u * k < nh) {
-                const uint32_t src = 32u * k + (lane >> 1);
-                xx[k] = from_lane(src, x[h]);
-                bb[k] = from_lane(src, b[h]);
-            }
+            const uint32_t src = 32u * k + (lane >> 1);
+            xx[k] = from_lane(src, x[h]);
+            bb[k] = from_lane(src, b[h]);
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
 #pragma unroll
-            for (int u = 0; u < 2 * NL; ++u) w[k][u] = make_uint4(0u, 0u, 0u, 0u);
-            if (32u * k + (lane >> 1) < nh) {  // pair-uniform
-#pragma unroll
-                for (int u = 0; u < 2 * NL; ++u) w[k][u] = gload4(t.B + (bb[k] << L) + 4u * (2 * u + me));
-            }
+            for (int u = 0; u < 2 * NL; ++u) w[k][u] = gload4(t.B + (bb[k] << L) + 4u * (2 * u + me));
         }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            c[k] = 0u;
-            if (32u * k < nh) {
-                uint32_t n = 0;
+            uint32_t n = 0;
 #pragma unroll
-                for (int u = 0; u < 2 * NL; ++u)
-                    n += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
-                         (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
-                c[k] = pair_sum(n);
-            }
+            for (int u = 0; u < 2 * NL; ++u)
+                n += (uint32_t)(w[k][u].x <= xx[k]) + (uint32_t)(w[k][u].y <= xx[k]) +
+                     (uint32_t)(w[k][u].z <= xx[k]) + (uint32_t)(w[k][u].w <= xx[k]);
+            c[k] = pair_sum(n);
         }
         const uint32_t cm = me == 0u ? c[0] : c[1], bm = me == 0u ? bb[0] : bb[1];
         const uint32_t src = 32u * me + (lane >> 1);
@@ -654,7 +645,7 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
                 uint32_t slot[N], cnt = 0;
 #pragma unroll
                 for (int q = 0; q < N; ++q) {
-                    const bool nd = (need >> q) & 1u;
+                    const bool nd = st[q] == 2u;
                     const unsigned long long m = __ballot(nd);
                     slot[q] = cnt + rank_in(m);
                     if (nd) v.queue[slot[q]] = a[q];
@@ -689,12 +680,12 @@ __device__ __forceinline__ void lookups(const DevTable& t, const LdsView& v, con
                     lds_wave_sync();
 #pragma unroll
                     for (int q = 0; q < N; ++q)
-                        if ((need >> q) & 1u) in[q] = v.queue[slot[q]];
+                        if (st[q] == 2u) st[q] = v.queue[slot[q]];
                     lds_wave_sync();  // read back before the queue is written again
                 }
 #pragma unroll
                 for (int q = 0; q < N; ++q) {
-                    if (st[q] < 2u) in[q] = st[q];
+                    in[q] = st[q];
                     code[q] = 0;
                 }
                 return;
