@@ -515,7 +515,7 @@ def bench_parse(args, torch, sinet, sinetgen, gg):
                    "bytes_per_line": dev.numel() / n_lines, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic("parse_call", workload),
-                     "kernel": "the parse call (count, scan, line starts, parse; synchronous)",
+                     "kernel": "the parse call (one pass over the text; synchronous)",
                      "alg_bytes_per_launch": alg, "launch_ms": ms},
         "forms": {"parse": {"ms_per_step": ms, "ms_min": ms_min, "wall_ms": wall}},
     }
