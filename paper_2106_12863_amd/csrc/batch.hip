@@ -20,6 +20,7 @@
 #include <string>
 #include <vector>
 
+#include "local_shape.h"
 #include "sinet_internal.h"
 
 using namespace sinet;
@@ -168,7 +169,7 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
                         sinet_batch_plan* plan) {
     // an item of a local stream is one run of its window's 17-bit counts
     const uint32_t item_chunks = std::min<uint32_t>(std::max<uint32_t>(1, tune.chunk / kChunk),
-                                                    ((1u << 17) - 1) / kChunk);
+                                                    kLocalRun / kChunk);
     Prepared pr;
     sinet_status rc = prepare(st, ns, (uint64_t)item_chunks * kChunk, pr);
     if (rc != SINET_OK) return rc;

@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "inout_index.h"
+#include "local_shape.h"
 #include "pass_common.h"
 #include "sinet_device.h"
 #include "sinet_internal.h"
@@ -1266,7 +1267,6 @@ __global__ void __launch_bounds__(kStage1Block, 4) k_stage1(PassParams p, PartWs
 // ---------------------------------------------------------------------------
 constexpr uint32_t kLocalShift = 47;                       // window word: count << 47 | bytes
 constexpr uint64_t kLocalMaxBytes = 1ull << 30;            // larger counts go to the output
-constexpr uint32_t kLocalRun = (1u << 17) - 1u;            // sessions of a run at most
 static_assert((kLocalMaxBytes - 1) * kLocalRun < (1ull << kLocalShift), "no carry into the count");
 
 struct LocalArgs {
@@ -2935,11 +2935,11 @@ constexpr uint64_t kWindowMinSessions = 1ull << 28;
 // sessions, 11 per bin: 62 against 91 us) but would need a probe of their order.
 static_assert(kLocalMinPerBin == 16, "the line measured above");
 constexpr uint32_t kLocalAlways = 2048;    // bins that always take the local reduce
-// Width from which a window of bins (about 2,500) takes the time order of any
-// nearly sorted log: +-1 minute.  With narrower bins a probe looks first: with
-// +-5 s of jitter 4e8 sessions at 4 ms per bin took 13.3 ms with the local
-// reduce, whose window they leave, 1.45 ms with the sliding window; at 10 ms per
-// bin 1.71 against 15.6 ms.
+// Width from which the window spans kLocalSureSpan whatever its copies
+// (local_shape): up to about +-1 minute of disorder.  With narrower bins a probe
+// looks first: with +-5 s of jitter 4e8 sessions at 4 ms per bin took 13.3 ms
+// with the local reduce, whose window they leave, 1.45 ms with the sliding
+// window; at 10 ms per bin 1.71 against 15.6 ms.
 constexpr uint32_t kLocalSureWidth = 48;
 // Width below which not even +-5 s of jitter fits the window: no probe.
 constexpr uint32_t kLocalMinWidth = 4;
@@ -3077,33 +3077,14 @@ static sinet_status launch_local(const PassParams& p, uint32_t kind, const uint3
     LocalFn fn = pick_local(kind, vector_ok(p, kind, true));
     if (!fn) return fail(SINET_ERR_UNSUPPORTED, "no kernel for this lookup kind");
     const size_t tab = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 8;
-    const uint32_t cap = local_bins(kind, p.t);
-    // small inputs: smaller steps, so that more CUs take part
     const uint32_t cus = device_cu_count();
-    const uint32_t block = p.n >= 2048ull * cus ? 1024 : 256;
-    const uint32_t step = 4 * block, most = kLocalRun / step;
-    LocalArgs a{};
-    a.gate = gate;
-    a.whole = p.n_bins <= cap ? 1u : 0u;
-    a.run = most;
-    const uint64_t per_bin = p.n / p.n_bins + 1;
-    uint64_t want = p.n_bins;  // bins the copies must each hold
-    if (!a.whole) {
-        // a run moves forward by at most 3/8 of the window, the rest is for the
-        // time jitter; the copies hold eight times a full run's advance
-        const uint64_t fit = (uint64_t)cap * 3 / 8 * per_bin / step;
-        a.run = (uint32_t)(fit < 1 ? 1 : fit < most ? fit : most);
-        want = 8 * ((uint64_t)kLocalRun / per_bin) + 256;
-    }
-    // copies while they fit and hold fewer words than the workgroup has sessions
-    const uint64_t steps = (p.n + step - 1) / step;
-    const uint64_t mine = p.n / (steps < cus ? steps : cus);
-    while (a.reps < 4 && want << (a.reps + 1) <= cap && want << (a.reps + 3) <= mine) ++a.reps;
-    a.bins = a.whole ? p.n_bins : cap >> a.reps;
+    const LocalShape sh = local_shape(p.n, p.n_bins, p.width, local_bins(kind, p.t), cus);
+    const LocalArgs a{sh.bins, sh.reps, sh.run, sh.whole ? 1u : 0u, gate};
     const size_t lds = tab + (32ull * a.bins << a.reps);
-    uint64_t grid = (uint64_t)cus * blocks_per_cu((const void*)fn, block, lds);
+    const uint64_t steps = (p.n + 4 * sh.block - 1) / (4 * sh.block);
+    uint64_t grid = (uint64_t)cus * blocks_per_cu((const void*)fn, (int)sh.block, lds);
     if (grid > steps) grid = steps;
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(block), lds, s, p, a);
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(sh.block), lds, s, p, a);
     return check_hip(hipGetLastError(), "local reduce launch");
 }
 

@@ -310,7 +310,6 @@ sinet_status launch_scan_fill(const PartWs& w, hipStream_t s);
 // takes `table` bytes of LDS (0: no room)
 uint32_t batch_window_words(size_t table);
 constexpr uint64_t kLocalMinPerBin = 16;        // sessions per bin from which the local reduce pays
-constexpr uint64_t kLocalSureSpan = 120000;     // time (ms) a window must span to hold any log's jitter
 uint32_t batch_stage1_blocks_per_cu(uint32_t kind, size_t lds);
 // lookups that run as their own pass before stage 1
 bool lookup_splits(const DevTable& t);
