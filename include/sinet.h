@@ -497,8 +497,14 @@ sinet_status sinet_timing_read(sinet_timing* out);
  *            of workspace per session plus 330 MB);
  *   AUTO     (the default) the local reduce from 16 sessions per bin on, for
  *            bins of 4 to 47 ms only if a probe of the sessions' order on the
- *            device allows it and not for narrower ones; else WINDOW from 2^28 sessions on, else
- *            RECORDS (the measured crossover of the two on a day of 1-ms bins).
+ *            device allows it and not for narrower ones; else WINDOW from 2^28
+ *            sessions on, else RECORDS (the measured crossover of the two on a
+ *            day of 1-ms bins).  With bins of 48 ms and more it is meant for
+ *            sessions in order to within a minute or so.  Out of order, from 9e7
+ *            to 2^28 sessions and up to 65,536 bins, it sets them aside as
+ *            records (at most 5.2 bytes of workspace per session; without that
+ *            room it does not) and takes about twice the time; other calls take
+ *            up to twice the time of RECORDS then.
  * Process-wide; takes effect for calls made after it returns.
  * Errors: INVALID_ARG (unknown mode). */
 typedef enum {

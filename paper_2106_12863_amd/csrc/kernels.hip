@@ -1269,12 +1269,41 @@ constexpr uint32_t kLocalShift = 47;                       // window word: count
 constexpr uint64_t kLocalMaxBytes = 1ull << 30;            // larger counts go to the output
 static_assert((kLocalMaxBytes - 1) * kLocalRun < (1ull << kLocalShift), "no carry into the count");
 
+// Runs out of order (see local_defer): records by block of kBlockBins bins.  The
+// kernels derive it from its base, since scalar registers are short in k_local.
+struct DeferWs {
+    uint32_t* any;     // nonzero: some run's sessions are here
+    uint32_t* on;      // [steps] the step's sessions are here
+    uint32_t* dir;     // [blocks][steps] the step's records of a block: first slot | slots << 16
+    uint32_t* rec;     // [steps][kDeferSlots] records (their format is stage 1's)
+    uint32_t steps, blocks;
+};
+
+constexpr uint32_t kDeferBlocks = kDeferMaxBins / kBlockBins;
+constexpr uint32_t kDeferExtra = 768;  // records beyond one per session a step may hold
+constexpr uint32_t kDeferSlots = 4 * kMaxBlock + kDeferExtra + 3 * kDeferBlocks;
+static_assert(kDeferBlocks == 64, "a wave scans their counts");
+static_assert(kDeferSlots % 4 == 0 && kDeferSlots < (1u << 16), "whole groups, 16-bit slots");
+
+__host__ __device__ inline DeferWs defer_at(uint32_t* base, uint64_t n, uint32_t n_bins) {
+    DeferWs d;
+    d.steps = (uint32_t)((n + 4 * kMaxBlock - 1) / (4 * kMaxBlock));
+    d.blocks = (n_bins + kBlockBins - 1) / kBlockBins;
+    const uint32_t lines = (d.steps + 31u) & ~31u;
+    d.any = base;
+    d.on = base + 32;
+    d.dir = d.on + lines;
+    d.rec = d.dir + (uint64_t)lines * d.blocks;
+    return d;
+}
+
 struct LocalArgs {
     uint32_t bins;     // bins of the window
     uint32_t reps;     // log2 of the window's copies
     uint32_t run;      // steps of a run
     uint32_t whole;    // the window is the whole histogram
     const uint32_t* gate;  // NULL, or a word: nonzero when another reduce runs instead
+    uint32_t* aside;   // k_local's third form only: base of the DeferWs
 };
 
 // A workgroup's window: `bins` bins from w0 on, 2^reps copies.
@@ -1320,32 +1349,44 @@ __device__ __forceinline__ void local_add(const PassParams& p, const LocalWin& w
     }
 }
 
-// The lane's four sessions from i0 on: loaded ones (full), or those below n.
+// The lane's four sessions from i0 on: loaded ones (full), or those below n
+// (bit k of the result: session k).
+template <uint32_t KIND>
+__device__ __forceinline__ uint32_t local_get4(const PassParams& p, const LdsView& v, uint64_t i0,
+                                               const Raw4& cur, bool full, uint32_t* lab, uint32_t* ts,
+                                               unsigned long long* by) {
+    if (full) {
+        labels4_from<KIND>(p, v, i0, cur.src, cur.dst, cur.l4, lab);
+        ts[0] = cur.ts.x; ts[1] = cur.ts.y; ts[2] = cur.ts.z; ts[3] = cur.ts.w;
+        by[0] = cur.b01.x; by[1] = cur.b01.y; by[2] = cur.b23.x; by[3] = cur.b23.y;
+        return 15u;
+    }
+    uint32_t has = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint64_t i = i0 + k;
+        lab[k] = ts[k] = 0;
+        by[k] = 0;
+        if (i >= p.n) continue;
+        has |= 1u << k;
+        if constexpr (KIND == KK_LABEL_IN) lab[k] = *glob(p.label_in + i) & 3u;
+        else lab[k] = label1<KIND>(p, v, i);
+        ts[k] = *glob(p.ts + i);
+        by[k] = *glob(p.bytes + i);
+    }
+    return has;
+}
+
+// They go into the window.
 template <uint32_t KIND>
 __device__ __forceinline__ void local_add4(const PassParams& p, const LdsView& v, const LocalWin& w,
                                            uint32_t rep, uint64_t i0, const Raw4& cur, bool full, Dropped& d) {
     uint32_t lab[4], ts[4];
     unsigned long long by[4];
-    if (full) {
-        labels4_from<KIND>(p, v, i0, cur.src, cur.dst, cur.l4, lab);
-        ts[0] = cur.ts.x; ts[1] = cur.ts.y; ts[2] = cur.ts.z; ts[3] = cur.ts.w;
-        by[0] = cur.b01.x; by[1] = cur.b01.y; by[2] = cur.b23.x; by[3] = cur.b23.y;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint64_t i = i0 + k;
-            lab[k] = ts[k] = 0;
-            by[k] = 0;
-            if (i >= p.n) continue;
-            if constexpr (KIND == KK_LABEL_IN) lab[k] = *glob(p.label_in + i) & 3u;
-            else lab[k] = label1<KIND>(p, v, i);
-            ts[k] = *glob(p.ts + i);
-            by[k] = *glob(p.bytes + i);
-        }
-    }
+    const uint32_t has = local_get4<KIND>(p, v, i0, cur, full, lab, ts, by);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if (full || i0 + k < p.n) local_add(p, w, rep, lab[k], ts[k], by[k], d);
+        if ((has >> k) & 1u) local_add(p, w, rep, lab[k], ts[k], by[k], d);
 }
 
 // First bin of the lane's four sessions (~0: none in the histogram).
@@ -1383,14 +1424,51 @@ __device__ __forceinline__ void local_flush(const PassParams& p, const LocalWin&
     }
 }
 
-template <uint32_t KIND, bool VEC>
+// ---- runs out of order -------------------------------------------------------
+// A session outside the window costs two device atomics, 35 times one inside it,
+// and input in no order has nearly all outside.  So, for the calls that the third
+// form of k_local takes, a run first tries 64 of its sessions, evenly spaced (a
+// line each: 1,024 of them cost 8 % of the call's time); where more than an eighth
+// would miss the window, it leaves its sessions to k_aside, which writes them as
+// records grouped by block of bins, and k_deferred, which adds those up block by
+// block (both return at once when there are none).  Sessions that the records
+// cannot take (2^52 bytes or more, or a step with many large byte counts) go to
+// the output directly.  (Writing the records inside k_local instead saves a launch,
+// but spills registers in the loop of the runs in order: 371 -> 430 us for 1e8
+// sessions looked up in the in/out index.)
+//
+// 1e8 shuffled labelled sessions: into 65,536 bins 8.37 -> 0.65 ms (the two-stage
+// records 4.80, whose stage 2 has one workgroup per block), into 6,000 8.6 -> 0.53
+// (7.40); looked up, into 43,200 8.63 -> 0.79.  In order 0.240 -> 0.250 ms, looked
+// up 0.372 -> 0.382: the room for the records (a gap of 6 us in the stream where
+// it is given back) and the launches that find nothing to do.
+
+// Whether the run's sessions mostly keep to the window: ts is the session that the
+// lanes with `tries` try.  Called by the whole workgroup; s_vote holds a word per
+// wave.
+__device__ __forceinline__ bool local_strays(const PassParams& p, const LocalWin& w, uint32_t ts,
+                                             bool tries, uint32_t* s_vote) {
+    const uint32_t lane = threadIdx.x & 63u, nw = blockDim.x >> 6;
+    uint32_t bin;
+    const bool counts = in_window(p, ts, bin) && tries;
+    const uint32_t in = (uint32_t)__popcll(__ballot(counts));
+    const uint32_t miss = (uint32_t)__popcll(__ballot(counts && bin - w.w0 >= w.bins));
+    if (lane == 0) s_vote[threadIdx.x >> 6] = miss << 16 | in;
+    lds_barrier();
+    uint32_t sum = 0;
+    for (uint32_t k = 0; k < nw; ++k) sum += s_vote[k];
+    return (sum >> 16) * 8u > (sum & 0xFFFFu);
+}
+
+// Its third form (DEFER, 1,024 lanes) sets runs out of order aside.
+template <uint32_t KIND, bool VEC, bool DEFER>
 __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    __shared__ uint32_t s_min[kMaxBlock / 64];
+    __shared__ uint32_t s_min[kMaxBlock / 64], s_vote[DEFER ? kMaxBlock / 64 : 1];
     if (a.gate && *glob(a.gate)) return;
     uint32_t used = 0;
     const LdsView v = stage_lds<KIND>(p.t, lds, &used);
-    LocalWin w{reinterpret_cast<unsigned long long*>(lds + ((used + 1) & ~1u)), a.bins, a.reps, 0u};
+    LocalWin w{reinterpret_cast<unsigned long long*>(lds + ((used + 3) & ~3u)), a.bins, a.reps, 0u};
     const uint32_t tid = threadIdx.x;
     for (uint32_t k = tid; k < a.bins * 4u << a.reps; k += blockDim.x) w.h[k] = 0;
     const uint32_t rep = tid & ((1u << a.reps) - 1u);
@@ -1399,12 +1477,30 @@ __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) 
     const uint64_t n_steps = (p.n + step - 1) / step;
     const uint64_t s0 = n_steps * blockIdx.x / gridDim.x, s1 = n_steps * (blockIdx.x + 1) / gridDim.x;
     auto full = [&](uint64_t s) { return VEC && (s + 1) * step <= p.n; };
+    // every 16th lane's sample of the run from step r0 on
+    const bool tries = (tid & 15u) == 0;
+    auto sample = [&](uint64_t r0) -> uint32_t {
+        if (r0 >= s1 || !tries) return 0u;
+        const uint64_t i0 = r0 * step, i1 = min(p.n, min(r0 + a.run, s1) * step);
+        return *glob(p.ts + i0 + (i1 - i0) * tid / blockDim.x);
+    };
     Raw4 cur{}, nxt{};
     if (s0 < s1 && full(s0)) load4<KIND>(p, s0 * step + 4ull * tid, cur);
     __syncthreads();
     for (uint64_t r0 = s0; r0 < s1; r0 += a.run) {
         const uint64_t r1 = r0 + a.run < s1 ? r0 + a.run : s1;
+        uint32_t tried = 0;
+        if constexpr (DEFER) tried = sample(r0);
         if (!a.whole) w.w0 = local_place(local_first(p, r0 * step + 4ull * tid, cur, full(r0)), a.bins, s_min);
+        if constexpr (DEFER) {
+            const bool aside = local_strays(p, w, tried, tries, s_vote);
+            if (tid < r1 - r0) *glob(defer_at(a.aside, p.n, p.n_bins).on + r0 + tid) = aside ? 1u : 0u;
+            if (aside) {  // k_aside's
+                if (tid == 0) *glob(a.aside) = 1u;
+                if (r1 < s1 && full(r1)) load4<KIND>(p, r1 * step + 4ull * tid, cur);
+                continue;
+            }
+        }
         for (uint64_t s = r0; s < r1; ++s) {
             if (s + 1 < s1 && full(s + 1)) load4<KIND>(p, (s + 1) * step + 4ull * tid, nxt);
             local_add4<KIND>(p, v, w, rep, s * step + 4ull * tid, cur, full(s), d);
@@ -1413,6 +1509,93 @@ __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) 
         lds_barrier();
         local_flush(p, w);
         lds_barrier();
+    }
+    d.flush(p.dropped);
+}
+
+// LDS of a step of records.
+struct DeferShared {
+    uint4 rec[kDeferSlots / 4];
+    uint32_t cnt[kDeferBlocks], base[kDeferBlocks];
+    uint32_t extra, slots, pad[2];
+};
+
+// The steps (of 4,096 sessions) that k_local set aside, as records grouped by
+// block of bins.
+template <uint32_t KIND, bool VEC>
+__global__ void __launch_bounds__(kMaxBlock) k_aside(PassParams p, uint32_t* aside) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    __shared__ DeferShared sh;
+    if (*glob(aside) == 0) return;
+    uint32_t used = 0;
+    const LdsView v = stage_lds<KIND>(p.t, lds, &used);
+    const DeferWs w = defer_at(aside, p.n, p.n_bins);
+    const uint32_t tid = threadIdx.x;
+    uint32_t* lrec = reinterpret_cast<uint32_t*>(sh.rec);
+    Dropped d{};
+    for (uint64_t s = blockIdx.x; s < w.steps; s += gridDim.x) {
+        if (*glob(w.on + s) == 0) continue;
+        const uint64_t i0 = s * (4 * kMaxBlock) + 4ull * tid;
+        const bool full = VEC && (s + 1) * (4 * kMaxBlock) <= p.n;
+        Raw4 raw{};
+        if (full) load4<KIND>(p, i0, raw);
+        uint32_t lab[4], ts[4], bin[4], rank[4];
+        unsigned long long by[4];
+        if (tid < kDeferBlocks) sh.cnt[tid] = 0;  // last read before the previous step's last barrier
+        if (tid == 0) sh.extra = 0;
+        lds_barrier();
+        const uint32_t has = local_get4<KIND>(p, v, i0, raw, full, lab, ts, by);
+        uint32_t rec = 0;  // bit k: session k becomes records
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            rank[k] = 0;
+            const bool inw = in_window(p, ts[k], bin[k]);
+            if (!((has >> k) & 1u)) continue;
+            if (!inw) {
+                d.add(lab[k], by[k]);
+                continue;
+            }
+            const uint32_t more = record_parts(by[k]) - 1u;
+            bool fits = by[k] < (1ull << 52);
+            if (fits && more) fits = atomicAdd(&sh.extra, more) + more <= kDeferExtra;
+            if (fits) {
+                rec |= 1u << k;
+                rank[k] = atomicAdd(&sh.cnt[bin[k] / kBlockBins], more + 1u);
+            } else {
+                const uint64_t x = (uint64_t)lab[k] * p.n_bins + bin[k];
+                __hip_atomic_fetch_add(p.count + x, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(p.hbytes + x, by[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        lds_barrier();
+        if (tid < 64) {  // places of the blocks' groups, each padded to whole 16 bytes
+            const uint32_t c = sh.cnt[tid], x = (c + 3u) & ~3u;
+            uint32_t inc = x;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)inc, o);
+                if ((int)tid >= o) inc += y;
+            }
+            sh.base[tid] = inc - x;
+            for (uint32_t q = inc - x + c; q < inc; ++q) lrec[q] = 0xFFFFFFFFu;
+            if (tid < w.blocks) *glob(w.dir + (uint64_t)tid * w.steps + s) = (inc - x) | x << 16;
+            if (tid == 63) sh.slots = inc;
+        }
+        lds_barrier();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!((rec >> k) & 1u)) continue;
+            const uint32_t blk = bin[k] / kBlockBins, key = lab[k] << 30 | (bin[k] - blk * kBlockBins) << 20;
+            const uint32_t at = sh.base[blk] + rank[k], parts = record_parts(by[k]);
+            if (parts == 1u) {
+                lrec[at] = key | (uint32_t)by[k];
+            } else {
+                for (uint32_t q = 0; q < parts; ++q)
+                    lrec[at + q] = key | 1u << 19 | q << 17 | ((uint32_t)(by[k] >> (17 * q)) & 0x1FFFFu);
+            }
+        }
+        lds_barrier();
+        uint32_t* dst = w.rec + s * kDeferSlots;
+        for (uint32_t k = tid; k < sh.slots / 4; k += kMaxBlock) gstore4(dst + 4 * k, sh.rec[k]);
     }
     d.flush(p.dropped);
 }
@@ -1808,6 +1991,43 @@ __global__ void __launch_bounds__(kStage2Block) k_stage2(PartWs w, unsigned long
     stage2_run(w, sh, PlainOut{count, hbytes, n_bins, accumulate}, lines ? 1u : kStage2Run);
 }
 
+// The records of k_local's runs out of order: a workgroup adds up those of one
+// block and a slice of the steps in LDS and then, with device atomics, to the
+// output.  Slices, because a block's records are as many as its share of all
+// sessions while the blocks are few.
+__global__ void __launch_bounds__(kStage2Block) k_deferred(PassParams p, uint32_t* aside, uint32_t slices) {
+    __shared__ Stage2Shared sh;
+    const DeferWs w = defer_at(aside, p.n, p.n_bins);
+    if (*glob(w.any) == 0) return;
+    const uint32_t tid = threadIdx.x, blk = blockIdx.x / slices, slice = blockIdx.x - blk * slices;
+    const uint32_t t0 = (uint32_t)((uint64_t)w.steps * slice / slices),
+                   t1 = (uint32_t)((uint64_t)w.steps * (slice + 1) / slices);
+    for (uint32_t k = tid; k < 4 * kBlockBins; k += kStage2Block) {
+        sh.b[k] = 0;
+        sh.c[k] = 0;
+    }
+    PartWs recs{};
+    recs.rec = w.rec;
+    for (uint32_t t = t0; t < t1; t += kSegMax) {
+        const uint32_t n = min(t1 - t, (uint32_t)kSegMax);
+        for (uint32_t k = tid; k < n; k += kStage2Block) {
+            const uint32_t g = *glob(w.on + t + k) ? *glob(w.dir + (uint64_t)blk * w.steps + t + k) : 0u;
+            sh.start[0][k] = (t + k) * kDeferSlots + (g & 0xFFFFu);
+            sh.nvec[0][k] = g >> 18;
+        }
+        if (tid == 0) sh.nseg[0] = n;
+        __syncthreads();
+        stage2_segments(recs, sh, 0);
+        __syncthreads();
+    }
+    for (uint32_t k = tid; k < 4 * kBlockBins; k += kStage2Block) {
+        if (!sh.c[k]) continue;
+        const uint64_t x = (uint64_t)(k / kBlockBins) * p.n_bins + blk * kBlockBins + k % kBlockBins;
+        __hip_atomic_fetch_add(p.count + x, (unsigned long long)sh.c[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(p.hbytes + x, sh.b[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 __global__ void k_zero(unsigned long long* __restrict__ p, uint64_t n) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1848,11 +2068,11 @@ __global__ void __launch_bounds__(kMaxBlock) k_local_probe(PassParams p, uint32_
     if (threadIdx.x == 0) *glob(gate) = s_wide > 8u ? 1u : 0u;
 }
 
-// Up to three arrays of 8-byte words cleared in one launch; the first two only
+// Up to four arrays of 8-byte words cleared in one launch; the first two only
 // when the gate (or no gate) says that the local reduce runs.
 struct ClearArgs {
-    unsigned long long* p[3];
-    uint64_t n[3];
+    unsigned long long* p[4];
+    uint64_t n[4];
     const uint32_t* gate;
 };
 
@@ -1861,7 +2081,7 @@ __global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool local = !c.gate || *glob(c.gate) == 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
+    for (int a = 0; a < 4; ++a) {
         if (c.n[a] == 0 || (a < 2 && !local)) continue;
         const uint64_t head = ((uintptr_t)c.p[a] & 15) ? 1 : 0;  // 8-byte aligned
         u64x2_t* q = reinterpret_cast<u64x2_t*>(c.p[a] + head);
@@ -2529,7 +2749,7 @@ sinet_status launch_zero(unsigned long long* p, uint64_t n_words, hipStream_t s)
 // dropped counters cleared in one launch; dropped may be NULL, cells 0.
 static sinet_status launch_clears(const ClearArgs& c, hipStream_t s) {
     const uint64_t most = c.n[0] > c.n[1] ? c.n[0] : c.n[1];
-    if (most + c.n[2] == 0) return SINET_OK;
+    if (most + c.n[2] + c.n[3] == 0) return SINET_OK;
     uint64_t blocks = (most / 2 + 255) / 256;
     const uint64_t cap = (uint64_t)device_cu_count() * 8;
     if (blocks > cap) blocks = cap;
@@ -2906,9 +3126,6 @@ sinet_status ws_free(void* ptr, hipStream_t s) {
     return check_hip(hipFreeAsync(ptr, s), "workspace free");
 }
 
-// Reduces of run_hist.
-enum { R_LOCAL, R_RECORDS, R_WINDOW };
-
 // Which reduce the histogram calls use (sinet_set_reduce).
 static std::atomic<int> g_reduce{SINET_REDUCE_AUTO};
 
@@ -2919,45 +3136,10 @@ sinet_status set_reduce(int mode) {
     return SINET_OK;
 }
 
-// Histogram strategy for a window: small windows are privatised in LDS; long
-// inputs take the sliding-window reduce, the rest the partitioned records.
-// The window reduce has about 0.7 ms of fixed cost per call (its pieces'
-// boundary fix-up and far pass, and the write-out of bins its few sessions
-// leave behind); on the day shape with 86.4 M 1-ms bins it was measured at
-// 2.25 ms against 1.82 ms for the records with 1e8 sessions and 3.38 against
-// 3.70 ms with 4e8, a crossover near 2.7e8 sessions.
-constexpr uint64_t kWindowMinSessions = 1ull << 28;
-
-// The local reduce is a candidate from this many sessions per bin on.  Fewer
-// leave it little to add up in LDS before its device atomics: 1e8 sessions of a
-// day took 1.11 ms with 12 sessions per bin, 0.76 with 23, 0.60 with 58 and 0.44
-// with 116, the records 0.89-0.93 ms each.  Small calls gain before that (4e6
-// sessions, 11 per bin: 62 against 91 us) but would need a probe of their order.
-static_assert(kLocalMinPerBin == 16, "the line measured above");
-constexpr uint32_t kLocalAlways = 2048;    // bins that always take the local reduce
-// Width from which the window spans kLocalSureSpan whatever its copies
-// (local_shape): up to about +-1 minute of disorder.  With narrower bins a probe
-// looks first: with +-5 s of jitter 4e8 sessions at 4 ms per bin took 13.3 ms
-// with the local reduce, whose window they leave, 1.45 ms with the sliding
-// window; at 10 ms per bin 1.71 against 15.6 ms.
-constexpr uint32_t kLocalSureWidth = 48;
-// Width below which not even +-5 s of jitter fits the window: no probe.
-constexpr uint32_t kLocalMinWidth = 4;
-
-struct Strategy {
-    int reduce;   // R_RECORDS or R_WINDOW, or R_LOCAL when the local reduce is sure
-    bool probe;   // the local reduce runs instead if the sessions' order allows it
-};
-
 static Strategy hist_strategy(const PassParams& p) {
-    if (p.n_bins <= kLocalAlways) return {R_LOCAL, false};
     const int mode = g_reduce.load();
-    if (mode == SINET_REDUCE_WINDOW) return {R_WINDOW, false};
-    if (mode == SINET_REDUCE_RECORDS) return {R_RECORDS, false};
-    const int other = p.n >= kWindowMinSessions ? R_WINDOW : R_RECORDS;
-    if (p.n / p.n_bins < kLocalMinPerBin || p.width < kLocalMinWidth) return {other, false};
-    if (p.width >= kLocalSureWidth) return {R_LOCAL, false};
-    return {other, true};
+    if (mode == SINET_REDUCE_AUTO || p.n_bins <= kLocalAlways) return auto_strategy(p.n, p.n_bins, p.width);
+    return {mode == SINET_REDUCE_WINDOW ? R_WINDOW : R_RECORDS, false};
 }
 
 // Lookups that walk global memory (trie, learned windows, binary searches
@@ -3045,13 +3227,37 @@ static sinet_status run_window(const PassParams& p, uint32_t kind, int accumulat
 
 using LocalFn = void (*)(PassParams, LocalArgs);
 
-static LocalFn pick_local(uint32_t kind, bool vec) {
+template <uint32_t KIND>
+static LocalFn local_fn(bool vec, bool defer) {
+    if (defer) return vec ? k_local<KIND, true, true> : k_local<KIND, false, true>;
+    return vec ? k_local<KIND, true, false> : k_local<KIND, false, false>;
+}
+
+static LocalFn pick_local(uint32_t kind, bool vec, bool defer) {
     switch (kind) {
-        case KK_UNION: return vec ? k_local<KK_UNION, true> : k_local<KK_UNION, false>;
-        case KK_INOUT: return vec ? k_local<KK_INOUT, true> : k_local<KK_INOUT, false>;
-        case KK_LABEL_IN: return vec ? k_local<KK_LABEL_IN, true> : k_local<KK_LABEL_IN, false>;
+        case KK_UNION: return local_fn<KK_UNION>(vec, defer);
+        case KK_INOUT: return local_fn<KK_INOUT>(vec, defer);
+        case KK_LABEL_IN: return local_fn<KK_LABEL_IN>(vec, defer);
         default: return nullptr;
     }
+}
+
+template <uint32_t KIND>
+static void (*aside_fn(bool vec))(PassParams, uint32_t*) {
+    return vec ? k_aside<KIND, true> : k_aside<KIND, false>;
+}
+
+static sinet_status launch_aside(const PassParams& p, uint32_t kind, uint32_t* aside, hipStream_t s) {
+    const bool vec = vector_ok(p, kind, true);
+    const auto fn = kind == KK_UNION ? aside_fn<KK_UNION>(vec)
+                                     : kind == KK_INOUT ? aside_fn<KK_INOUT>(vec) : aside_fn<KK_LABEL_IN>(vec);
+    const size_t lds = kind == KK_LABEL_IN ? 0 : p.t.lds_bytes;
+    const uint32_t grid = device_cu_count() * blocks_per_cu((const void*)fn, kMaxBlock, lds);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kMaxBlock), lds, s, p, aside);
+    const uint32_t blocks = defer_at(aside, p.n, p.n_bins).blocks;
+    const uint32_t slices = std::max(1u, 2 * device_cu_count() / blocks);
+    hipLaunchKernelGGL(k_deferred, dim3(blocks * slices), dim3(kStage2Block), 0, s, p, aside, slices);
+    return check_hip(hipGetLastError(), "runs out of order launch");
 }
 
 // LDS of a workgroup of the local reduce, window and table: one workgroup of
@@ -3067,32 +3273,44 @@ static bool local_fuses(uint32_t kind, const DevTable& t) {
 }
 
 // Bins that its window can hold.
-static uint32_t local_bins(uint32_t kind, const DevTable& t) {
-    const size_t tab = (kind == KK_LABEL_IN ? 0 : t.lds_bytes) + 8;
+static uint32_t local_room(uint32_t kind, const DevTable& t) {
+    const size_t tab = (kind == KK_LABEL_IN ? 0 : t.lds_bytes) + 16;
     return (uint32_t)(((kind == KK_LABEL_IN ? kLocalLdsLabels : kLocalLds) - tab) / 32);
 }
 
-static sinet_status launch_local(const PassParams& p, uint32_t kind, const uint32_t* gate,
-                                 hipStream_t s) {
-    LocalFn fn = pick_local(kind, vector_ok(p, kind, true));
+static LocalShape shape_of(const PassParams& p, uint32_t kind) {
+    return local_shape(p.n, p.n_bins, p.width, local_room(kind, p.t), device_cu_count());
+}
+
+// aside: where runs out of order go (NULL: nowhere).
+static sinet_status launch_local(const PassParams& p, uint32_t kind, const LocalShape& sh,
+                                 const uint32_t* gate, uint32_t* aside, hipStream_t s) {
+    LocalFn fn = pick_local(kind, vector_ok(p, kind, true), aside != nullptr);
     if (!fn) return fail(SINET_ERR_UNSUPPORTED, "no kernel for this lookup kind");
-    const size_t tab = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 8;
-    const uint32_t cus = device_cu_count();
-    const LocalShape sh = local_shape(p.n, p.n_bins, p.width, local_bins(kind, p.t), cus);
-    const LocalArgs a{sh.bins, sh.reps, sh.run, sh.whole ? 1u : 0u, gate};
+    const size_t tab = (kind == KK_LABEL_IN ? 0 : p.t.lds_bytes) + 16;
+    const LocalArgs a{sh.bins, sh.reps, sh.run, sh.whole ? 1u : 0u, gate, aside};
     const size_t lds = tab + (32ull * a.bins << a.reps);
     const uint64_t steps = (p.n + 4 * sh.block - 1) / (4 * sh.block);
-    uint64_t grid = (uint64_t)cus * blocks_per_cu((const void*)fn, (int)sh.block, lds);
+    uint64_t grid = (uint64_t)device_cu_count() * blocks_per_cu((const void*)fn, (int)sh.block, lds);
     if (grid > steps) grid = steps;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(sh.block), lds, s, p, a);
     return check_hip(hipGetLastError(), "local reduce launch");
 }
 
+// Bytes of the runs out of order.
+static size_t defer_bytes(uint64_t n, uint32_t n_bins) {
+    const DeferWs d = defer_at(nullptr, n, n_bins);
+    return (size_t)(d.rec - d.any) * 4 + 4ull * d.steps * kDeferSlots;
+}
+
 // The local reduce: the output cleared, the labels stored first when the
-// lookup does not run inside it (into label_out, or n bytes at `labels`).
+// lookup does not run inside it (into label_out, or n bytes at `labels`), the
+// runs out of order set aside when there is room for them at `aside`.
 static sinet_status run_local_in(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s,
-                                 uint8_t* labels, bool timed) {
-    sinet_status st = accumulate ? SINET_OK : launch_clear(p, 4ull * p.n_bins, s);
+                                 uint8_t* labels, uint32_t* aside, bool timed) {
+    const uint64_t cells = accumulate ? 0 : 4ull * p.n_bins;
+    sinet_status st = launch_clears({{p.count, p.hbytes, p.dropped, (unsigned long long*)aside},
+                                     {cells, cells, !accumulate && p.dropped ? 8ull : 0ull, aside ? 1ull : 0ull}, nullptr}, s);
     PassParams q = p;
     if (st == SINET_OK && !local_fuses(kind, p.t)) {
         PassParams lq = p;
@@ -3105,17 +3323,31 @@ static sinet_status run_local_in(const PassParams& p, uint32_t kind, int accumul
         kind = KK_LABEL_IN;
     }
     if (st != SINET_OK) return st;
-    PhaseScope ph(PH_STAGE1, s, timed);
-    return launch_local(q, kind, nullptr, s);
+    {
+        PhaseScope ph(PH_STAGE1, s, timed);
+        st = launch_local(q, kind, shape_of(q, kind), nullptr, aside, s);
+    }
+    if (st != SINET_OK || !aside) return st;
+    PhaseScope ph(PH_STAGE2, s, timed);
+    return launch_aside(q, kind, aside, s);
 }
 
 static sinet_status run_local(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s) {
+    const bool fused = local_fuses(kind, p.t);
+    const size_t lab = !fused && !p.label_out ? al256(p.n) : 0;
+    size_t aside = !shape_of(p, fused ? kind : (uint32_t)KK_LABEL_IN).whole && local_defers(p.n, p.n_bins)
+                       ? defer_bytes(p.n, p.n_bins) : 0;
     void* ws = nullptr;
-    if (!local_fuses(kind, p.t) && !p.label_out) {
-        const sinet_status st = ws_alloc(&ws, p.n, s);
+    if (aside && ws_alloc(&ws, lab + aside, s) != SINET_OK) {  // no room: only slower out of order
+        (void)hipGetLastError();
+        ws = nullptr;
+        aside = 0;
+    }
+    if (lab && !ws) {
+        const sinet_status st = ws_alloc(&ws, lab, s);
         if (st != SINET_OK) return st;
     }
-    const sinet_status st = run_local_in(p, kind, accumulate, s, (uint8_t*)ws, true);
+    const sinet_status st = run_local_in(p, kind, accumulate, s, (uint8_t*)ws, aside ? (uint32_t*)((char*)ws + lab) : nullptr, true);
     const sinet_status st2 = ws ? ws_free(ws, s) : SINET_OK;
     return st != SINET_OK ? st : st2;
 }
@@ -3130,7 +3362,7 @@ sinet_status run_hist_in(const PassParams& p, uint32_t mode, int accumulate, hip
     if (p.n == 0) return SINET_OK;
     const Strategy strat = hist_strategy(p);
     if (strat.reduce == R_LOCAL)  // 2^25 sessions at most: their labels fit
-        return run_local_in(p, kind, accumulate, s, (uint8_t*)scratch, false);
+        return run_local_in(p, kind, accumulate, s, (uint8_t*)scratch, nullptr, false);
     if (!accumulate) {
         const sinet_status st = launch_clear(p, 0, s);
         if (st != SINET_OK) return st;
@@ -3147,7 +3379,7 @@ sinet_status run_hist_in(const PassParams& p, uint32_t mode, int accumulate, hip
 // neighbouring sessions spread; the kernels of the one not chosen return at
 // once.  The labels are stored first unless both reduces look them up alike
 // (the records with a table the local reduce fuses).
-static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulate, int other,
+static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulate, Reduce other,
                                hipStream_t s) {
     const bool fused = other == R_RECORDS && local_fuses(kind, p.t);
     const bool lookup = !fused && kind != KK_LABEL_IN;
@@ -3158,8 +3390,8 @@ static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulat
     if (st != SINET_OK) return st;
     uint32_t* gate = (uint32_t*)((char*)ws + wsb);
     const uint32_t k2 = fused ? kind : (uint32_t)KK_LABEL_IN;
-    const uint32_t bins = local_bins(k2, p.t);
-    hipLaunchKernelGGL(k_local_probe, dim3(1), dim3(kMaxBlock), 0, s, p, bins / 16 * 9, gate);
+    const LocalShape sh = shape_of(p, k2);
+    hipLaunchKernelGGL(k_local_probe, dim3(1), dim3(kMaxBlock), 0, s, p, sh.bins / 16 * 9, gate);
     st = check_hip(hipGetLastError(), "order probe launch");
     if (st == SINET_OK && !accumulate) st = launch_clear(p, 4ull * p.n_bins, s, gate);
     PassParams q = p;
@@ -3173,7 +3405,7 @@ static sinet_status run_probed(const PassParams& p, uint32_t kind, int accumulat
     }
     if (st == SINET_OK) {
         PhaseScope ph(PH_STAGE1, s);
-        st = launch_local(q, k2, gate, s);
+        st = launch_local(q, k2, sh, gate, nullptr, s);
     }
     if (st == SINET_OK && other == R_WINDOW) {
         st = run_window_in(q, KK_LABEL_IN, accumulate, s, ws, P, true, gate);

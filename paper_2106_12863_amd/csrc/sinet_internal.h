@@ -309,7 +309,6 @@ sinet_status launch_scan_fill(const PartWs& w, hipStream_t s);
 // 64-bit words of the local window of a stage-1 workgroup whose largest table
 // takes `table` bytes of LDS (0: no room)
 uint32_t batch_window_words(size_t table);
-constexpr uint64_t kLocalMinPerBin = 16;        // sessions per bin from which the local reduce pays
 uint32_t batch_stage1_blocks_per_cu(uint32_t kind, size_t lds);
 // lookups that run as their own pass before stage 1
 bool lookup_splits(const DevTable& t);

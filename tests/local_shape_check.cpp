@@ -1,7 +1,7 @@
 // The local reduce's shape (the header the library includes) over sessions,
 // bins, widths and room: the copies fit, a run's counts fit their 17 bits, a
 // moving window keeps the time that its rule promises, and a run's advance
-// leaves most of it to the time jitter.
+// leaves most of it to the time jitter.  Then the reduce that calls take.
 #include <cstdio>
 #include <initializer_list>
 
@@ -32,6 +32,29 @@ int main() {
                         printf("n %llu bins %u width %u cap %u: window %u reps %u run %u block %u\n",
                                (unsigned long long)n, n_bins, width, cap, s.bins, s.reps, s.run, s.block);
                 }
+    // calls: sessions, bins, width; the reduce, probed, runs out of order set aside
+    struct { uint64_t n; uint32_t n_bins, width; Reduce r; bool probe, defers; } routes[] = {
+        {5, 2048, 1, R_LOCAL, false, false},                  // the window holds every bin
+        {4000000, 3000, 1, R_RECORDS, false, false},          // narrower than any jitter
+        {4000000, 3000, 10, R_RECORDS, true, false},
+        {400000000, 360000, 10, R_WINDOW, true, false},
+        {100000000, 43200, 1000, R_LOCAL, false, true},
+        {100000000, 65536, 48, R_LOCAL, false, true},
+        {100000000, 86400, 1000, R_LOCAL, false, false},      // more blocks than a wave scans
+        {60000000, 43200, 1000, R_LOCAL, false, false},       // too short to hide a launch
+        {400000000, 43200, 1000, R_LOCAL, false, false},      // too much room
+        {1600000000, 86400000, 1, R_WINDOW, false, false},
+        {100000000, 86400000, 1, R_RECORDS, false, false},
+    };
+    for (const auto& t : routes) {
+        const Strategy g = auto_strategy(t.n, t.n_bins, t.width);
+        const bool defers = g.reduce == R_LOCAL && t.n_bins > kLocalAlways && local_defers(t.n, t.n_bins);
+        if (g.reduce != t.r || g.probe != t.probe || defers != t.defers) {
+            ++bad;
+            printf("n %llu bins %u width %u: reduce %d probe %d aside %d\n", (unsigned long long)t.n, t.n_bins,
+                   t.width, (int)g.reduce, (int)g.probe, (int)defers);
+        }
+    }
     printf("shapes %llu moving %llu bad %llu\n", seen, moving, bad);
     return bad || !moving ? 1 : 0;
 }

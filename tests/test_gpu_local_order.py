@@ -1,0 +1,82 @@
+"""The local reduce on sessions in and out of order: runs that it sets aside as
+records (seen by the time of their second stage) and, for narrow bins, calls that
+its probe hands to the records; the same exact result as the CPU oracle's,
+accumulated or not, for labels given and looked up, byte counts of every size and
+columns of every alignment."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+#        n, n_bins, width, jitter
+MIN = 90_000_000  # sessions from which runs out of order are set aside
+CASES = [(MIN, 65_536, 48, 5_000),     # the most bins of those calls
+         (MIN + 4_097, 2_601, 500, 5_000),     # the fewest, and a ragged last step
+         (3_000_003, 60_000, 20, 5_000),       # narrow bins
+         (50_003, 2_049, 7, 300)]              # as few sessions and bins as are probed
+
+
+@pytest.mark.parametrize("n,n_bins,width,jitter", CASES)
+@pytest.mark.parametrize("order", ["sorted", "shuffled", "blocks", "half"])
+def test_order_chooses_the_reduce(n, n_bins, width, jitter, order):
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    print("order", n, n_bins, width, order, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + len(order))
+    t = ((torch.arange(n, device="cuda", dtype=torch.float64) + 0.5) * (n_bins * width / n)).to(torch.int64)
+    t += torch.randint(-jitter, jitter + 1, (n,), generator=g, device="cuda")
+    if order == "shuffled":
+        t = t[torch.randperm(n, generator=g, device="cuda")]
+    elif order == "blocks":  # pieces of 500 sessions in any order: neighbours are close
+        m = n // 500
+        t[:m * 500] = t[:m * 500].view(m, 500)[torch.randperm(m, generator=g, device="cuda")].reshape(-1)
+    elif order == "half":
+        t[n // 2:] = t[n // 2:][torch.randperm(n - n // 2, generator=g, device="cuda")]
+    ts = (t.clamp_(0, n_bins * width + 999) + 500).to(torch.int32)
+    by = torch.randint(0, 1 << 62, (n,), generator=g, device="cuda") >> \
+        torch.randint(0, 62, (n,), generator=g, device="cuda") // (1 if n < MIN else 4) * 4
+    ends = [torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda", dtype=torch.int32)
+            for _ in range(2)]
+    rng = np.random.default_rng(3)
+    base, plen = rng.integers(0, 1 << 32, 64).astype(np.uint32), rng.integers(3, 20, 64).astype(np.uint8)
+    tab = sinet.Table(base, plen)
+    lab = sinet.discriminate(tab, *ends)[0]
+    torch.cuda.synchronize()
+    exp = oracle.histogram(sinet.to_host_u32(ts), sinet.to_host_u64(by), lab.cpu().numpy(), 500, width, n_bins)
+
+    def timed(call):
+        sinet.timing_enable(True)
+        out = call()
+        torch.cuda.synchronize()
+        t = sinet.timing_read()
+        sinet.timing_enable(False)
+        return out, t
+
+    def same(out, k):
+        return all(np.array_equal(sinet.to_host_u64(a), e * np.uint64(k)) for a, e in zip(out, exp))
+
+    given, t0 = timed(lambda: sinet.histogram(ts, by, lab, 500, width, n_bins))
+    (lab2, looked), t1 = timed(lambda: sinet.pipeline(tab, ts, *ends, by, 500, width, n_bins))
+    assert torch.equal(lab, lab2) and same(given, 1) and same(looked, 1)
+    sinet.histogram(ts, by, lab, 500, width, n_bins, out=given, accumulate=True)
+    torch.cuda.synchronize()
+    assert same(given, 2)
+    if n_bins > 5_000 and n >= MIN:
+        # 0.3 ms and more where the second stage has records, a launch alone where
+        # not (a window of 2,527 bins or more holds nearly all of 2,601 in any order)
+        for t in (t0, t1):
+            assert (t["stage2_ms"] > 0.1) == (order != "sorted"), (order, t)
+    # columns off 16 bytes, alike and not
+    for cut in ((1, 1, 1, 1, 1), (1, 2, 3, 1, 2)):
+        def off(x, k):
+            y = torch.empty(n + k, dtype=x.dtype, device="cuda")[k:]
+            return y.copy_(x)
+        c = [off(x, k) for x, k in zip((ts, *ends, by, lab), cut)]
+        (lab2, looked) = sinet.pipeline(tab, *c[:4], 500, width, n_bins)
+        given = sinet.histogram(c[0], c[3], c[4], 500, width, n_bins)
+        torch.cuda.synchronize()
+        assert torch.equal(lab, lab2) and same(given, 1) and same(looked, 1), cut
