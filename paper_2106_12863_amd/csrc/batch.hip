@@ -114,22 +114,17 @@ sinet_status prepare(const sinet_stream* st, uint32_t ns, uint64_t item_sessions
         pr.lds_tab[s] = p.t.lds_bytes;
         pr.n_chunks[s] = (p.n + kChunk - 1) / kChunk;
         d.vec = vector_ok(p, p.t.kind, true) ? 1u : 0u;
-        size_t& most = pr.kind_lds[p.t.kind];
-        most = std::max(most, pr.lds_tab[s]);
-    }
-    for (uint32_t s = 0; s < ns; ++s) {
-        const sinet_stream& x = st[s];
-        BatchStreamDev& d = pr.desc[s];
-        const PassParams& p = d.p;
-        choose_local(d, batch_window_words(pr.kind_lds[p.t.kind]), item_sessions);
         // lookups that walk global memory: a lookup pass stores the labels (in
         // the stream's label output, or a plan-owned buffer when it has none),
-        // stage 1 reads them
-        if (!d.local_bins && p.n && lookup_splits(p.t)) {
+        // stage 1 reads them, in the local reduce too.  Searched inside stage 1,
+        // beside the window, 16 streams of 4e6 sessions in ten-minute frames took
+        // 38.4 ms with a PLA (0.69 after a pass), 1.05 with a trie (0.92), 1.99
+        // with an MLP (1.38), 1.51 with the sampled binary search (1.06); of 2e5
+        // sessions 1.85, 0.082, 0.153 and 0.121 ms (0.078, 0.083, 0.128, 0.105).
+        if (p.n && lookup_splits(p.t)) {
             pr.lkind[s] = p.t.kind;
             pr.lds_look[s] = p.t.lds_bytes;
-            BatchStreamDev& l = pr.ldesc[s];
-            l = d;
+            pr.ldesc[s] = d;
             if (!x.label) {
                 pr.tmp_off[s] = pr.tmp_bytes;
                 pr.tmp_bytes += (p.n + 255) & ~255ull;
@@ -140,7 +135,11 @@ sinet_status prepare(const sinet_stream* st, uint32_t ns, uint64_t item_sessions
             d.p.label_in = x.label;  // or the plan buffer, set when the arena exists
             d.p.label_out = nullptr;
         }
+        size_t& most = pr.kind_lds[pr.kind[s]];
+        most = std::max(most, pr.lds_tab[s]);
     }
+    for (uint32_t s = 0; s < ns; ++s)
+        choose_local(pr.desc[s], batch_window_words(pr.kind_lds[pr.kind[s]]), item_sessions);
     uint64_t c = 0;
     uint64_t k = 0;
     for (uint32_t s = 0; s < ns; ++s) {
