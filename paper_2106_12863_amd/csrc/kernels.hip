@@ -1443,14 +1443,10 @@ __device__ __forceinline__ void local_flush(const PassParams& p, const LocalWin&
 // up 0.372 -> 0.382: the room for the records (a gap of 6 us in the stream where
 // it is given back) and the launches that find nothing to do.
 
-// Whether the run's sessions mostly keep to the window: ts is the session that the
-// lanes with `tries` try.  Called by the whole workgroup; s_vote holds a word per
-// wave.
-__device__ __forceinline__ bool local_strays(const PassParams& p, const LocalWin& w, uint32_t ts,
-                                             bool tries, uint32_t* s_vote) {
+// Whether more than an eighth of the bins that the lanes with `counts` bring lie
+// outside the window.  Called by the whole workgroup; s_vote holds a word per wave.
+__device__ __forceinline__ bool local_strays(const LocalWin& w, uint32_t bin, bool counts, uint32_t* s_vote) {
     const uint32_t lane = threadIdx.x & 63u, nw = blockDim.x >> 6;
-    uint32_t bin;
-    const bool counts = in_window(p, ts, bin) && tries;
     const uint32_t in = (uint32_t)__popcll(__ballot(counts));
     const uint32_t miss = (uint32_t)__popcll(__ballot(counts && bin - w.w0 >= w.bins));
     if (lane == 0) s_vote[threadIdx.x >> 6] = miss << 16 | in;
@@ -1493,7 +1489,9 @@ __global__ void __launch_bounds__(kMaxBlock) k_local(PassParams p, LocalArgs a) 
         if constexpr (DEFER) tried = sample(r0);
         if (!a.whole) w.w0 = local_place(local_first(p, r0 * step + 4ull * tid, cur, full(r0)), a.bins, s_min);
         if constexpr (DEFER) {
-            const bool aside = local_strays(p, w, tried, tries, s_vote);
+            uint32_t bin;
+            const bool counts = in_window(p, tried, bin) && tries;
+            const bool aside = local_strays(w, bin, counts, s_vote);
             if (tid < r1 - r0) *glob(defer_at(a.aside, p.n, p.n_bins).on + r0 + tid) = aside ? 1u : 0u;
             if (aside) {  // k_aside's
                 if (tid == 0) *glob(a.aside) = 1u;
@@ -1697,7 +1695,7 @@ __global__ void __launch_bounds__(1024) k_scan_one(const uint32_t* __restrict__ 
 // Group the directory entries by block: segs[seg_off[b] ..] = (first slot,
 // count).  Consumes seg_count back to zero.
 __global__ void k_fill(PartWs w) {
-    if (w.gate && !*glob(w.gate)) return;
+    if ((w.gate && !*glob(w.gate)) || (w.only_aside && !*glob(w.farcount + 2))) return;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < w.n_chunks * kWin;
          q += stride) {
@@ -1991,6 +1989,24 @@ __global__ void __launch_bounds__(kStage2Block) k_stage2(PartWs w, unsigned long
     stage2_run(w, sh, PlainOut{count, hbytes, n_bins, accumulate}, lines ? 1u : kStage2Run);
 }
 
+// A block's accumulators cleared, and added to the output with device atomics
+// (both by the whole workgroup).
+__device__ __forceinline__ void block_clear(Stage2Shared& sh) {
+    for (uint32_t k = threadIdx.x; k < 4 * kBlockBins; k += kStage2Block) {
+        sh.b[k] = 0;
+        sh.c[k] = 0;
+    }
+}
+__device__ __forceinline__ void block_add(const Stage2Shared& sh, unsigned long long* count,
+                                          unsigned long long* hbytes, uint32_t n_bins, uint32_t blk) {
+    for (uint32_t k = threadIdx.x; k < 4 * kBlockBins; k += kStage2Block) {
+        if (!sh.c[k]) continue;
+        const uint64_t x = (uint64_t)(k / kBlockBins) * n_bins + blk * kBlockBins + k % kBlockBins;
+        __hip_atomic_fetch_add(count + x, (unsigned long long)sh.c[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(hbytes + x, sh.b[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // The records of k_local's runs out of order: a workgroup adds up those of one
 // block and a slice of the steps in LDS and then, with device atomics, to the
 // output.  Slices, because a block's records are as many as its share of all
@@ -2002,10 +2018,7 @@ __global__ void __launch_bounds__(kStage2Block) k_deferred(PassParams p, uint32_
     const uint32_t tid = threadIdx.x, blk = blockIdx.x / slices, slice = blockIdx.x - blk * slices;
     const uint32_t t0 = (uint32_t)((uint64_t)w.steps * slice / slices),
                    t1 = (uint32_t)((uint64_t)w.steps * (slice + 1) / slices);
-    for (uint32_t k = tid; k < 4 * kBlockBins; k += kStage2Block) {
-        sh.b[k] = 0;
-        sh.c[k] = 0;
-    }
+    block_clear(sh);
     PartWs recs{};
     recs.rec = w.rec;
     for (uint32_t t = t0; t < t1; t += kSegMax) {
@@ -2020,12 +2033,7 @@ __global__ void __launch_bounds__(kStage2Block) k_deferred(PassParams p, uint32_
         stage2_segments(recs, sh, 0);
         __syncthreads();
     }
-    for (uint32_t k = tid; k < 4 * kBlockBins; k += kStage2Block) {
-        if (!sh.c[k]) continue;
-        const uint64_t x = (uint64_t)(k / kBlockBins) * p.n_bins + blk * kBlockBins + k % kBlockBins;
-        __hip_atomic_fetch_add(p.count + x, (unsigned long long)sh.c[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(p.hbytes + x, sh.b[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    block_add(sh, p.count, p.hbytes, p.n_bins, blk);
 }
 
 __global__ void k_zero(unsigned long long* __restrict__ p, uint64_t n) {
@@ -2112,6 +2120,40 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
+// Which items of the spare streams are out of order (item.w = 1): as a run of
+// k_local, an item is when more than an eighth of 32 of its sessions, evenly spaced,
+// lie outside the window that its first 32 sessions place.  Half a wave per item.
+// (Asked inside stage 1 it cost all items 3 % there, by registers.)
+__global__ void __launch_bounds__(256) k_batch_order(BatchArgs a, uint4* items, PartWs w) {
+    const uint32_t it = (blockIdx.x * 256 + threadIdx.x) / 32, l = threadIdx.x & 31u;
+    const bool half = (threadIdx.x & 32u) != 0;
+    uint32_t first = 0xFFFFFFFFu, bin = 0, bins = 0;
+    bool counts = false, spare = false;
+    if (it < a.n_items) {
+        const uint4 item = items[it];
+        const BatchStreamDev& bs = a.streams[item.x];
+        spare = bs.spare != 0;
+        if (spare) {
+            bins = bs.local_bins;
+            const uint64_t i0 = (uint64_t)item.y * kChunk, i1 = min(bs.p.n, (uint64_t)item.z * kChunk);
+            const uint32_t t0 = *glob(bs.p.ts + min(i0 + l, i1 - 1)), t1 = *glob(bs.p.ts + i0 + (i1 - i0) * l / 32);
+            uint32_t b;
+            if (in_window(bs.p, t0, b)) first = b;
+            counts = in_window(bs.p, t1, bin);
+        }
+    }
+#pragma unroll
+    for (int o = 16; o; o >>= 1) first = min(first, (uint32_t)__shfl_xor((int)first, o));
+    const uint32_t w0 = first != 0xFFFFFFFFu && first > bins / 16u ? first - bins / 16u : 0u;
+    const uint32_t in = (uint32_t)(__ballot(counts) >> (half ? 32 : 0));
+    const uint32_t miss = (uint32_t)(__ballot(counts && bin - w0 >= bins) >> (half ? 32 : 0));
+    if (it < a.n_items && l == 0) {
+        const bool aside = spare && (uint32_t)__popc(miss) * 8u > (uint32_t)__popc(in);
+        *glob(&items[it].w) = aside ? 1u : 0u;
+        if (aside) *glob(w.farcount + 2) = 1u;
+    }
+}
+
 template <uint32_t KIND>
 __device__ __forceinline__ void batch_stage1(const BatchArgs& a, const PartWs& w) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
@@ -2157,7 +2199,7 @@ __device__ __forceinline__ void batch_stage1(const BatchArgs& a, const PartWs& w
         }
         const PassParams& p = bs.p;
         Dropped d{};
-        if (bs.local_bins) {
+        if (bs.local_bins && uniform_u32(item.w) == 0) {  // (k_batch_order: 1 for an item out of order)
             LocalWin w{win, bs.local_bins, bs.reps, 0u};
             const bool vec = bs.vec != 0;
             auto full = [&](uint64_t c) { return vec && (c + 1) * kChunk <= p.n; };
@@ -2213,6 +2255,29 @@ __global__ void __launch_bounds__(kStage2Block) k_batch_stage2(BatchArgs a, Part
     stage2_run(w, sh, BatchOut{&a}, kStage2Run);
 }
 
+// The blocks (stream, block) of the local streams whose items out of order became
+// records: added to what their other items put into the output.
+__global__ void __launch_bounds__(kStage2Block) k_batch_aside(BatchArgs a, PartWs w, const uint2* blocks,
+                                                              uint32_t slices) {
+    __shared__ Stage2Shared sh;
+    if (*glob(w.farcount + 2) == 0) return;
+    const uint32_t slice = blockIdx.x % slices;
+    const uint2 id = blocks[blockIdx.x / slices];
+    const BatchStreamDev& bs = a.streams[id.x];
+    const uint32_t s0 = w.seg_off[bs.block0 + id.y], n = w.seg_off[bs.block0 + id.y + 1] - s0;
+    const uint32_t t0 = s0 + (uint32_t)((uint64_t)n * slice / slices),
+                   t1 = s0 + (uint32_t)((uint64_t)n * (slice + 1) / slices);
+    if (t0 == t1) return;
+    block_clear(sh);
+    for (uint32_t t = t0; t < t1; t += kSegMax) {
+        stage2_describe(w, sh, 0, t, min(t1 - t, (uint32_t)kSegMax));
+        __syncthreads();
+        stage2_segments(w, sh, 0);
+        __syncthreads();
+    }
+    block_add(sh, bs.p.count, bs.p.hbytes, bs.p.n_bins, id.y);
+}
+
 
 // In/out-index lookups fit 128 VGPRs (4 waves per SIMD, two workgroups per CU);
 // the interval kinds keep their registers rather than spill.
@@ -2243,7 +2308,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_batch_far(BatchArgs a, PartWs w) 
         while (lo + 1 < a.n_streams && a.chunk_base[lo + 1] <= g) ++lo;
         const uint32_t si = uniform_u32(lo);
         const BatchStreamDev& bs = a.streams[si];
-        if (bs.local_bins || bs.p.t.kind != KIND) continue;  // another kind group's chunk
+        if (bs.p.t.kind != KIND) continue;  // another kind group's chunk
         PassParams p = bs.p;
         p.label_out = nullptr;
         p.src_inst = nullptr;
@@ -3072,6 +3137,19 @@ sinet_status launch_batch_stage2(const BatchArgs& a, const PartWs& w, uint32_t n
     if (n_blocks == 0) return SINET_OK;
     hipLaunchKernelGGL(k_batch_stage2, dim3(stage2_grid(n_blocks)), dim3(kStage2Block), 0, s, a, w);
     return check_hip(hipGetLastError(), "batch stage-2 launch");
+}
+
+sinet_status launch_batch_order(const BatchArgs& a, const PartWs& w, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_order, dim3((a.n_items + 7) / 8), dim3(256), 0, s, a, const_cast<uint4*>(a.items), w);
+    return check_hip(hipGetLastError(), "batch order launch");
+}
+
+sinet_status launch_batch_aside(const BatchArgs& a, const PartWs& w, const uint2* blocks, uint32_t n_blocks,
+                                hipStream_t s) {
+    if (n_blocks == 0) return SINET_OK;
+    const uint32_t slices = std::max(1u, 2 * device_cu_count() / n_blocks);
+    hipLaunchKernelGGL(k_batch_aside, dim3(n_blocks * slices), dim3(kStage2Block), 0, s, a, w, blocks, slices);
+    return check_hip(hipGetLastError(), "batch items out of order launch");
 }
 
 sinet_status launch_batch_far(uint32_t kind, const BatchArgs& a, const PartWs& w, size_t lds,

@@ -95,7 +95,7 @@ struct PartWs {
     uint32_t* nd;                   // [n_chunks] directory entries per chunk
     uint32_t* farbits;              // [n_chunks * kChunk / 32] far sessions (flagged chunks)
     uint32_t* farlist;              // [n_chunks] chunks holding far sessions
-    uint32_t* farcount;             // [1]
+    uint32_t* farcount;             // [1], next_run, batches: items out of order
     uint32_t* next_run;             // [1] next run of chunks to take (k_stage1)
     uint32_t* seg_count;            // [n_blocks] directory entries per block
     uint32_t* seg_off;              // [n_blocks + 1] exclusive scan of seg_count
@@ -107,6 +107,7 @@ struct PartWs {
     uint32_t run;                   // chunks a stage-1 workgroup takes at a time
     uint32_t keep_dropped;          // the caller clears the dropped counters
     const uint32_t* gate;           // NULL, or a word: zero when another reduce runs instead
+    uint32_t only_aside;            // batches: only items out of order become records
 };
 
 struct FarList {
@@ -179,11 +180,13 @@ struct BatchStreamDev {
     uint32_t local_bins;        // bins of the local reduce's window (0: records)
     uint32_t vec;               // 1: the stream's columns allow 16-byte loads
     uint32_t reps;              // log2 of the window's copies
+    uint32_t spare;             // 1: a local stream with chunks and blocks for items out of order
+    uint32_t pad;
 };
 
 struct BatchArgs {
     const BatchStreamDev* streams;
-    const uint4* items;         // (stream, first chunk, end chunk, -) of one kind group
+    const uint4* items;         // (stream, first chunk, end chunk, out of order) of one kind group
     uint32_t n_items;
     uint32_t n_streams;
     uint32_t* counter;          // work-queue head of the group
@@ -302,6 +305,10 @@ sinet_status launch_batch_stage1(uint32_t kind, const BatchArgs& a, const PartWs
                                  uint32_t grid, hipStream_t s);
 sinet_status launch_batch_stage2(const BatchArgs& a, const PartWs& w, uint32_t n_blocks,
                                  hipStream_t s);
+// asks which items of the group's spare streams are out of order
+sinet_status launch_batch_order(const BatchArgs& a, const PartWs& w, hipStream_t s);
+sinet_status launch_batch_aside(const BatchArgs& a, const PartWs& w, const uint2* blocks, uint32_t n_blocks,
+                                hipStream_t s);
 sinet_status launch_batch_far(uint32_t kind, const BatchArgs& a, const PartWs& w, size_t lds,
                               hipStream_t s);
 sinet_status launch_zero_jobs(const ZeroJob* jobs, uint32_t n_jobs, hipStream_t s);

@@ -59,3 +59,56 @@ def test_coarse_streams_of_searching_tables_equal_oracle(kind):
     made = [_stream(sinet, torch, tab, base, plen, j, n, w, b, "sorted", lab)
             for j, (n, w, b, lab) in enumerate(cuts)]
     _check(sinet, torch, sinet.BatchPlan([m[0] for m in made]), made)
+
+
+@pytest.mark.parametrize("order,records", [("shuffled", False), ("half", True), ("sorted", True)])
+def test_coarse_streams_set_aside_equal_oracle(order, records):
+    """A plan large enough to set items aside, without and with streams of records."""
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    rng = np.random.default_rng(8)
+    base, plen = rng.integers(0, 1 << 32, 64).astype(np.uint32), rng.integers(3, 20, 64).astype(np.uint8)
+    tab = sinet.Table(base, plen)
+    print("batch set aside", order, flush=True)
+    made = [_stream(sinet, torch, tab, base, plen, 80, 15_000_007, 500, 20_000, order, True)]
+    lab, out, exp = made[0][1:]
+    s = made[0][0]
+    extra = [sinet.new_hist(20_000) for _ in range(5)]  # the same sessions again, other outputs
+    streams = [s] + [sinet.BatchStream(tab, s.ts, s.src, s.dst, s.nbytes, 300, 500, 20_000, out=o) for o in extra]
+    made += [_stream(sinet, torch, tab, base, plen, 81, 300_001, 10, 70_000, order, True)] if records else []
+    plan = sinet.BatchPlan(streams[:2] + [m[0] for m in made[1:]] + streams[2:])
+    for _ in range(3):
+        plan.run()
+        torch.cuda.synchronize()
+        assert np.array_equal(lab.cpu().numpy(), exp[0])
+        for o in [out] + extra:
+            for got, e in zip(o, exp[1:]):
+                assert np.array_equal(sinet.to_host_u64(got), e)
+        for _, _, o, e in made[1:]:
+            assert all(np.array_equal(sinet.to_host_u64(a), b) for a, b in zip(o, e[1:]))
+
+
+def test_coarse_streams_out_of_order_equal_oracle():
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    rng = np.random.default_rng(7)
+    made = []
+    for j, (kind, order, n, width, n_bins) in enumerate([
+            ("scan", "shuffled", 400_009, 1_000, 3_000), ("auto", "half", 700_001, 1_000, 3_000),
+            ("trie", "half", 600_011, 1_000, 20_000), ("auto", "shuffled", 1_200_007, 500, 65_536),
+            ("scan", "half", 1_300_001, 500, 70_000),      # more bins than are set aside
+            ("auto", "sorted", 300_001, 1_000, 5_000), ("scan", "shuffled", 50_001, 60_000, 60),
+            ("auto", "shuffled", 200_003, 20, 30_000)]):   # records anyway
+        k = 64 if kind == "scan" else 3_000
+        base, plen = rng.integers(0, 1 << 32, k).astype(np.uint32), rng.integers(5, 29, k).astype(np.uint8)
+        tab = sinet.Table(base, plen, kind=kind, inout_index=kind != "trie")
+        made.append(_stream(sinet, torch, tab, base, plen, 50 + j, n, width, n_bins, order, j % 2 == 0))
+    print("batch out of order", flush=True)
+    for chunk in (None, 2_048, 1 << 18):
+        tune = None
+        if chunk:
+            tune = sinet.Tune()
+            tune.block, tune.chunk, tune.grid = 512, chunk, 0
+        _check(sinet, torch, sinet.BatchPlan([m[0] for m in made], tune), made)
