@@ -172,7 +172,9 @@ typedef struct {
 /* Autotuned launch parameters of the batched persistent kernel. */
 typedef struct {
     uint32_t block;         /* threads per workgroup (64..1024, multiple of 64) */
-    uint32_t chunk;         /* sessions per work item (multiple of 4*block)  */
+    uint32_t chunk;         /* sessions per work item (multiple of 4*block;
+                               items of coarse streams, which are added up in
+                               LDS, hold 129,024 at most)                    */
     uint32_t grid;          /* persistent workgroups (0: one per slot)       */
     uint32_t reserved;
 } sinet_tune;

@@ -189,11 +189,11 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& tune, bool spare,
                         sinet_batch_plan* plan) {
-    // an item of a local stream is one run of its window's 17-bit counts
-    const uint32_t item_chunks = std::min<uint32_t>(std::max<uint32_t>(1, tune.chunk / kChunk),
-                                                    kLocalRun / kChunk);
+    // an item of a local stream is one run of its window's 17-bit counts at most
+    const uint32_t item_chunks = std::max<uint32_t>(1, tune.chunk / kChunk);
+    const uint32_t run_chunks = std::min<uint32_t>(item_chunks, kLocalRun / kChunk);
     Prepared pr;
-    sinet_status rc = prepare(st, ns, (uint64_t)item_chunks * kChunk, spare, pr);
+    sinet_status rc = prepare(st, ns, (uint64_t)run_chunks * kChunk, spare, pr);
     if (rc != SINET_OK) return rc;
 
     // kind groups and their work items
@@ -209,8 +209,9 @@ sinet_status build_plan(const sinet_stream* st, uint32_t ns, const sinet_tune& t
         group_lds[g] = std::max(group_lds[g], pr.lds_tab[s] + 16);
         group_spare[g] |= d.spare;
         if (d.local_bins) group_win[g] = std::max(group_win[g], 4u * d.local_bins << d.reps);
-        for (uint64_t c0 = 0; c0 < pr.n_chunks[s]; c0 += item_chunks) {
-            const uint64_t c1 = std::min<uint64_t>(pr.n_chunks[s], c0 + item_chunks);
+        const uint32_t step = d.local_bins ? run_chunks : item_chunks;
+        for (uint64_t c0 = 0; c0 < pr.n_chunks[s]; c0 += step) {
+            const uint64_t c1 = std::min<uint64_t>(pr.n_chunks[s], c0 + step);
             items[g].push_back(make_uint4(s, (uint32_t)c0, (uint32_t)c1, 0u));
         }
     }
