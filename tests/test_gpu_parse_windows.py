@@ -89,3 +89,11 @@ def test_lists_overflow_and_lines_leave_the_window(what):
     buf = np.frombuffer(b"".join(good[:100] + mid + good[50:]), np.uint8)
     _check(buf)
     _check(buf[3:], off=11)
+
+
+def test_bad_lines_are_counted_over_many_blocks():
+    rng = np.random.default_rng(9)
+    lines = [b"a" * int(k) + b"\n" for k in rng.integers(0, 90, 40_000)]
+    for k in range(0, 40_000, 997):
+        lines[k] = _line(rng)
+    _check(np.frombuffer(b"".join(lines), np.uint8), off=5)
