@@ -15,8 +15,9 @@
 // the delimiters (',' and '\n') are compacted into LDS by rank, so a line, which
 // starts after a delimiter that is a newline, finds the ends of its fields by
 // index.  A lane per line then parses the four fields with four-byte reads and
-// byte dot products.  A line whose fields leave the window (or a window with
-// more delimiters or lines than the lists hold) is parsed from device memory.
+// byte dot products.  A window with more delimiters or lines than the lists hold
+// (lines of less than 130 bytes) is parsed in rounds, a list at a time; the last
+// line, where its fields leave the window, from device memory.
 // The number of newlines before a block comes from the blocks before it: each
 // publishes its own count at once, then the count up to its end, and one wave
 // adds up its predecessors' counts back to the nearest such sum while the
@@ -31,7 +32,9 @@
 // arithmetic; 2.10 with the counts found by the kernel itself; 1.84 ms (2.4
 // TB/s) with the search for them beside the parsing.  Persistent workgroups
 // that fetched their next block early took 4.30 ms: a ticket taken early
-// publishes its count late.
+// publishes its count late.  4e8 bytes of 79-byte lines, 10,000 delimiters a
+// window: 0.87 ms with the lines beyond the lists read from device memory, 0.44 in
+// rounds.
 // The block that holds a newline owns the line after it; the first block owns
 // the first line.
 #include <hip/hip_runtime.h>
@@ -398,12 +401,12 @@ __device__ __forceinline__ uint32_t put_line(const ParseArgs& a, uint64_t l, boo
     return ok ? 0u : 1u;
 }
 
-__global__ void __launch_bounds__(kParseBlock) k_parse(ParseArgs a) {
+__global__ void __launch_bounds__(kParseBlock, 6) k_parse(ParseArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t s_text[kWindow + 16];
     __shared__ uint16_t s_delim[kDelims];             // positions in the window, ascending
     __shared__ uint16_t s_start[kLines], s_rank[kLines];  // per newline: position + 1, its delimiter rank
     __shared__ uint32_t s_wave[kParseBlock / 64];
-    __shared__ uint32_t s_blk, s_own, s_bad;
+    __shared__ uint32_t s_blk, s_own, s_bad, s_end;
     __shared__ uint64_t s_base;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     if (tid == 0) {
@@ -460,69 +463,82 @@ __global__ void __launch_bounds__(kParseBlock) k_parse(ParseArgs a) {
             if (blk + 1 == a.n_blocks) *a.total = upto;
         }
     };
-    if (n_nl > kLines) {
-        // more lines than the list holds (shorter than 32 bytes on average, so
-        // nearly all are bad): each lane parses those after its own newlines
-        place();
-        __syncthreads();
-        uint64_t l = s_base + (before >> 16) + 1;
-        for (uint64_t m = nm; m; m &= m - 1, ++l) {
-            const uint32_t q = 64u * tid + (uint32_t)__builtin_ctzll(m);
-            const uint64_t s = b0 + q + 1;
-            if (tid >= kOwnLanes || s >= a.t.end) continue;
-            uint32_t ts = 0, src = 0, dst = 0;
-            uint64_t nb = 0;
-            const bool ok = line_slow(a, s, ts, src, dst, nb);
-            bad += put_line(a, l, ok, ts, src, dst, nb);
-        }
-        if (blk == 0 && tid == 0) {
-            uint32_t ts = 0, src = 0, dst = 0;
-            uint64_t nb = 0;
-            const bool ok = line_slow(a, a.t.skew, ts, src, dst, nb);
-            bad += put_line(a, 0, ok, ts, src, dst, nb);
-        }
-    } else {
-        uint32_t r = before & 0xFFFFu;
-        if (n_delim > kDelims && r + 64u > kDelims) {  // the list ends in this lane's bytes, or has ended
-            for (uint64_t m = dm; m && r < kDelims; m &= m - 1, ++r)
-                s_delim[r] = (uint16_t)(64u * tid + (uint32_t)__builtin_ctzll(m));
-        } else {
+    // The lines, in rounds: each lists delimiters from rank d_lo and newlines from
+    // number k_lo on and parses the lines whose own are all listed.  Lines of 130
+    // bytes and more take one round.
+    uint32_t line = 0, d_lo = 0, k_lo = 0;  // the round's first line of the block
+    for (bool first = true;; first = false) {
+        const bool more = n_delim - d_lo > kDelims || n_nl - k_lo > kLines;
+        if (!more && first) {
+            uint32_t r = before & 0xFFFFu;
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 for (uint32_t m = (uint32_t)(dm >> (32 * h)); m; m &= m - 1u, ++r)
                     s_delim[r] = (uint16_t)(64u * tid + 32u * h + (uint32_t)__builtin_ctz(m));
-        }
-        uint32_t k = before >> 16;
-        for (uint64_t m = nm; m; m &= m - 1, ++k) {
-            const uint32_t q = (uint32_t)__builtin_ctzll(m);
-            s_start[k] = (uint16_t)(64u * tid + q + 1u);
-            s_rank[k] = (uint16_t)((before & 0xFFFFu) + (uint32_t)__popcll(dm & ((1ull << q) - 1ull)));
+            uint32_t k = before >> 16;
+            for (uint64_t m = nm; m; m &= m - 1, ++k) {
+                const uint32_t q = (uint32_t)__builtin_ctzll(m);
+                s_start[k] = (uint16_t)(64u * tid + q + 1u);
+                s_rank[k] = (uint16_t)((before & 0xFFFFu) + (uint32_t)__popcll(dm & ((1ull << q) - 1ull)));
+            }
+        } else {
+            // places in the lists (those before it wrap around and are above any)
+            uint32_t r = (before & 0xFFFFu) - d_lo, k = (before >> 16) - k_lo;
+            const bool none = (int)r >= (int)kDelims || (int)(r + (mine & 0xFFFFu)) <= 0;
+            for (uint64_t m = none ? 0ull : dm; m; m &= m - 1, ++r)
+                if (r < kDelims) s_delim[r] = (uint16_t)(64u * tid + (uint32_t)__builtin_ctzll(m));
+            for (uint64_t m = nm; m; m &= m - 1, ++k) {
+                const uint32_t q = (uint32_t)__builtin_ctzll(m);
+                if (k >= kLines) continue;
+                s_start[k] = (uint16_t)(64u * tid + q + 1u);
+                s_rank[k] = (uint16_t)((before & 0xFFFFu) + (uint32_t)__popcll(dm & ((1ull << q) - 1ull)));
+            }
         }
         __syncthreads();
-        const uint32_t n_own = s_own, lead = blk == 0 ? 1u : 0u;
+        const uint32_t lead = blk == 0 ? 1u : 0u, n_lines = s_own + lead;
+        // line r0 of the block follows newline r0 - lead of the window, whose delimiter
+        // rank is d0 - 1; its own newline is number nx, of rank dn (n_delim: none)
+        auto rank_of = [&](uint32_t nx) { return nx < n_nl ? (uint32_t)s_rank[nx - k_lo] : n_delim; };
+        uint32_t end = n_lines;  // the round's end: the first line that is not all listed
+        if (more) {
+            if (tid == 0) s_end = n_lines;
+            __syncthreads();
+            for (uint32_t r0 = line + tid; r0 < n_lines; r0 += kParseBlock) {
+                const bool top = r0 < lead;
+                const uint32_t i = r0 - lead, nx = top ? 0u : i + 1u;
+                bool listed = (top || i - k_lo < kLines) && (nx >= n_nl || nx - k_lo < kLines);
+                if (listed) {
+                    const uint32_t d0 = top ? 0u : (uint32_t)s_rank[i - k_lo] + 1u;
+                    const uint32_t last = min(min(d0 + 20u, rank_of(nx)), n_delim - 1u);
+                    listed = d0 >= n_delim || (d0 >= d_lo && last - d_lo < kDelims);
+                }
+                if (!listed) {
+                    atomicMin(&s_end, r0);
+                    break;
+                }
+            }
+            __syncthreads();
+            end = s_end;
+        }
         uint32_t ts = 0, src = 0, dst = 0;
         uint64_t nb = 0;
         bool ok = false;
-        // line r0 of the block into ts .. ok; false when there is none
+        // line r0 into ts .. ok; false when there is none
         auto one = [&](uint32_t r0) -> bool {
-            if (r0 >= n_own + lead) return false;
-            // list entry i is the newline before the line (none: the first line)
+            if (r0 >= end) return false;
             const uint32_t i = r0 - lead;
             const bool top = r0 < lead;
-            const uint32_t s = top ? a.t.skew : (uint32_t)s_start[i];
+            const uint32_t s = top ? a.t.skew : (uint32_t)s_start[i - k_lo];
             if (b0 + s >= a.t.end) return false;  // nothing after the text's last newline
-            const uint32_t d0 = top ? 0u : (uint32_t)s_rank[i] + 1u;  // rank of the line's first delimiter
-            const uint32_t nx = top ? 0u : i + 1u;                    // the next newline's entry
-            const uint32_t dn = nx < n_nl ? (uint32_t)s_rank[nx] : n_delim;
-            const bool seen = nx < n_nl || at_end;  // the line's end is in the window
-            if (d0 + 20u < min(n_delim, kDelims) || (seen && min(dn + 1u, n_delim) <= kDelims)) {
-                // every delimiter the line needs is listed, or its last one is
+            const uint32_t d0 = top ? 0u : (uint32_t)s_rank[i - k_lo] + 1u;
+            const uint32_t nx = top ? 0u : i + 1u, dn = rank_of(nx);
+            if (d0 + 20u < n_delim || nx < n_nl || at_end) {
+                // the line's delimiters are in the window, 21 or to its end
                 ok = dn - d0 >= 20u;  // 20 commas before its newline
                 if (ok) {
-                    const uint32_t c1 = s_delim[d0], c4 = s_delim[d0 + 3], c5 = s_delim[d0 + 4];
-                    const uint32_t c7 = s_delim[d0 + 6], c8 = s_delim[d0 + 7], c20 = s_delim[d0 + 19];
-                    const uint32_t c21 = d0 + 20u < n_delim ? (uint32_t)s_delim[d0 + 20]
-                                                            : (uint32_t)(a.t.end - b0);
+                    const uint16_t* dl = s_delim + (d0 - d_lo);
+                    const uint32_t c1 = dl[0], c4 = dl[3], c5 = dl[4], c7 = dl[6], c8 = dl[7], c20 = dl[19];
+                    const uint32_t c21 = d0 + 20u < n_delim ? (uint32_t)dl[20] : (uint32_t)(a.t.end - b0);
                     const Staged b{s_text};
                     ok = c1 - s == 23u && staged_time(b, s, a.origin, ts) &&
                          staged_ipv4(b, c4 + 1, c5, src) && staged_ipv4(b, c7 + 1, c8, dst) &&
@@ -533,15 +549,25 @@ __global__ void __launch_bounds__(kParseBlock) k_parse(ParseArgs a) {
             }
             return true;
         };
-        // the first kParseBlock lines are parsed while the last wave still finds
-        // the block's line number
-        place();
-        const bool has = one(tid);
-        __syncthreads();
-        const uint64_t l0 = s_base + 1u - lead;
-        if (has) bad += put_line(a, l0 + tid, ok, ts, src, dst, nb);
-        for (uint32_t r0 = tid + kParseBlock; one(r0); r0 += kParseBlock)
-            bad += put_line(a, l0 + r0, ok, ts, src, dst, nb);
+        uint32_t r0 = line + tid;
+        if (first) {
+            // the first kParseBlock lines are parsed while the last wave still finds
+            // the block's line number
+            place();
+            const bool has = one(r0);
+            __syncthreads();
+            if (has) bad += put_line(a, s_base + 1u - lead + r0, ok, ts, src, dst, nb);
+            r0 += kParseBlock;
+        }
+        for (; one(r0); r0 += kParseBlock) bad += put_line(a, s_base + 1u - lead + r0, ok, ts, src, dst, nb);
+        if (end >= n_lines) break;
+        // the next round starts with the line after (whose newline is listed: the line
+        // before it was)
+        line = end;
+        const uint32_t k = end - lead, d = (uint32_t)s_rank[k - k_lo] + 1u;
+        __syncthreads();  // the lists are written again
+        k_lo = k;
+        d_lo = d;
     }
     // one counter for all blocks: a block adds its own once (by waves, text without
     // a good line was bound by it: 2e8 bytes of 40-byte lines 0.77 -> 0.25 ms)
