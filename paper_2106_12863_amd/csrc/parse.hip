@@ -17,7 +17,7 @@
 // index.  A lane per line then parses the four fields with four-byte reads and
 // byte dot products.  A window with more delimiters or lines than the lists hold
 // (lines of less than 130 bytes) is parsed in rounds, a list at a time; the last
-// line, where its fields leave the window, from device memory.
+// line, where its fields leave the window, by one wave from device memory.
 // The number of newlines before a block comes from the blocks before it: each
 // publishes its own count at once, then the count up to its end, and one wave
 // adds up its predecessors' counts back to the nearest such sum while the
@@ -34,7 +34,8 @@
 // that fetched their next block early took 4.30 ms: a ticket taken early
 // publishes its count late.  4e8 bytes of 79-byte lines, 10,000 delimiters a
 // window: 0.87 ms with the lines beyond the lists read from device memory, 0.44 in
-// rounds.
+// rounds.  2e8 bytes of 5,080-byte lines: 5.83 ms with the lines that leave their
+// window read by a lane, byte by byte, 0.22 by a wave.
 // The block that holds a newline owns the line after it; the first block owns
 // the first line.
 #include <hip/hip_runtime.h>
@@ -128,31 +129,6 @@ struct LdsLine {
     }
 };
 
-// Byte access to one line in device memory (lines that leave their window):
-// bytes only, never past the line.
-struct GlobalLine {
-    const uint8_t* p;
-    __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return p[i]; }
-    __device__ __forceinline__ uint32_t upto(uint32_t i, uint32_t e) const { return i < e ? p[i] : 0xFFu; }
-    // the first ',' or '\n' in [c, n), or n
-    __device__ __forceinline__ uint32_t delim(uint32_t c, uint32_t n) const {
-        while (c < n && p[c] != ',' && p[c] != 10) ++c;
-        return c;
-    }
-};
-
-template <class Bytes>
-__device__ __forceinline__ bool dec(const Bytes& b, uint32_t at, int n, int32_t& v) {
-    int32_t x = 0;
-    for (int i = 0; i < n; ++i) {
-        const uint32_t c = b[at + i] - '0';
-        if (c > 9u) return false;
-        x = x * 10 + c;
-    }
-    v = x;
-    return true;
-}
-
 // The date and time of day as milliseconds from the origin day's midnight;
 // false for an impossible one or one outside [0, 2^32 - 1).
 __device__ __forceinline__ bool time_of(int32_t y, int32_t mo, int32_t d, int32_t h, int32_t mi, int32_t se,
@@ -171,50 +147,8 @@ __device__ __forceinline__ bool time_of(int32_t y, int32_t mo, int32_t d, int32_
     return true;
 }
 
-template <class Bytes>
-__device__ __forceinline__ bool capture_time(const Bytes& b, uint32_t s, uint32_t e, int64_t origin, uint32_t& ts) {
-    if (e - s != 23) return false;
-    if (b[s + 4] != '/' || b[s + 7] != '/' || b[s + 10] != ' ' || b[s + 13] != ':' ||
-        b[s + 16] != ':' || b[s + 19] != '.')
-        return false;
-    int32_t y, mo, d, h, mi, se, ms;
-    if (!dec(b, s, 4, y) || !dec(b, s + 5, 2, mo) || !dec(b, s + 8, 2, d) || !dec(b, s + 11, 2, h) ||
-        !dec(b, s + 14, 2, mi) || !dec(b, s + 17, 2, se) || !dec(b, s + 20, 3, ms))
-        return false;
-    return time_of(y, mo, d, h, mi, se, ms, origin, ts);
-}
-
-template <class Bytes>
-__device__ __forceinline__ bool ipv4(const Bytes& b, uint32_t s, uint32_t e, uint32_t& a) {
-    if (e - s < 7u || e - s > 15u) return false;  // "1.2.3.4" to "255.255.255.255"
-    constexpr uint32_t kDot = (uint32_t)('.' - '0');
-    uint32_t v = 0, i = s;
-#pragma unroll
-    for (int part = 0; part < 4; ++part) {
-        // the octet is the digits at i (a fourth one makes it bad); the byte
-        // after them must be '.' for parts 0-2 and the field's end for part 3
-        const uint32_t d0 = b.upto(i, e) - '0', d1 = b.upto(i + 1, e) - '0';
-        const uint32_t d2 = b.upto(i + 2, e) - '0', d3 = b.upto(i + 3, e) - '0';
-        if (d0 > 9u) return false;
-        const uint32_t nd = d1 > 9u ? 1u : d2 > 9u ? 2u : d3 > 9u ? 3u : 4u;
-        if (nd > 3u) return false;
-        const uint32_t o = nd == 1u ? d0 : nd == 2u ? d0 * 10 + d1 : d0 * 100 + d1 * 10 + d2;
-        if (o > 255u) return false;
-        const uint32_t next = nd == 1u ? d1 : nd == 2u ? d2 : d3;
-        v = (v << 8) | o;
-        i += nd;
-        if (part < 3) {
-            if (next != kDot) return false;
-            ++i;
-        }
-    }
-    if (i != e) return false;
-    a = v;
-    return true;
-}
-
-template <class Bytes>
-__device__ __forceinline__ bool count_u64(const Bytes& b, uint32_t s, uint32_t e, uint64_t& out) {
+// 1 to 20 decimal digits in [s, e), at most 2^64 - 1.
+__device__ __forceinline__ bool count_u64(const LdsLine& b, uint32_t s, uint32_t e, uint64_t& out) {
     if (e <= s || e - s > 20) return false;
     // 19 digits stay below 10^19 < 2^64 - 1, so only a 20th digit can
     // overflow; the digits before it are taken four at a time
@@ -242,25 +176,6 @@ __device__ __forceinline__ bool count_u64(const Bytes& b, uint32_t s, uint32_t e
     return true;
 }
 
-// Parse the line of b that ends at its first newline or at n; false for a bad
-// line.
-__device__ __forceinline__ bool parse_line(const GlobalLine& b, uint32_t n, int64_t origin, uint32_t& ts,
-                                           uint32_t& src, uint32_t& dst, uint64_t& nbytes) {
-    uint32_t s = 0;
-    for (int f = 1; f <= 21; ++f) {
-        // a capture time is 23 bytes: a longer first field is not read on
-        const uint32_t c = b.delim(s, f == 1 ? min(n, 24u) : n);
-        // field f is [s, c)
-        if (f == 1 && !capture_time(b, s, c, origin, ts)) return false;
-        if (f == 5 && !ipv4(b, s, c, src)) return false;
-        if (f == 8 && !ipv4(b, s, c, dst)) return false;
-        if (f == 21) return count_u64(b, s, c, nbytes);
-        if (c >= n || b[c] == 10) return false;  // the line ended before field 21
-        s = c + 1;
-    }
-    return false;
-}
-
 // One line of the window, parsed from the staged text and its delimiters.
 // Reads of up to three bytes before a field stay inside the line, of up to
 // three after one inside the staging (16 bytes of slack).
@@ -276,7 +191,7 @@ struct Staged {
 // Nonzero when a byte of x (digits less '0' by exclusive or) is above 9.
 __device__ __forceinline__ uint32_t not_digits(uint32_t x) { return (x | (x + 0x76767676u)) & 0x80808080u; }
 
-// Field 1 at s, 23 bytes: same rules as capture_time.
+// Field 1 at s, 23 bytes: "YYYY/MM/DD hh:mm:ss.mmm".
 __device__ __forceinline__ bool staged_time(const Staged& b, uint32_t s, int64_t origin, uint32_t& ts) {
     constexpr uint32_t z = 0x30303030u;
     const uint32_t w0 = b.word(s), w1 = b.word(s + 4), w2 = b.word(s + 8), w3 = b.word(s + 12),
@@ -305,7 +220,7 @@ __device__ __forceinline__ uint32_t last_digits(const Staged& b, uint32_t end, u
            __builtin_amdgcn_udot4(x, 0x010A0000u, 0u, false);
 }
 
-// A dotted quad in [s, e): same rules as ipv4.
+// A dotted quad in [s, e): four octets of one to three digits, 0 to 255.
 __device__ __forceinline__ bool staged_ipv4(const Staged& b, uint32_t s, uint32_t e, uint32_t& a) {
     const uint32_t n = e - s;
     if (n < 7u || n > 15u) return false;
@@ -328,7 +243,7 @@ __device__ __forceinline__ bool staged_ipv4(const Staged& b, uint32_t s, uint32_
     return bad == 0u;
 }
 
-// 1 to 20 decimal digits in [s, e): same rules as count_u64.
+// The same as count_u64, four digits at a time where none can overflow.
 __device__ __forceinline__ bool staged_count(const Staged& b, uint32_t s, uint32_t e, uint64_t& out) {
     const uint32_t n = e - s;
     if (n < 1u || n > 20u) return false;
@@ -383,12 +298,73 @@ __device__ __forceinline__ uint64_t newlines_before(const ParseArgs& a, uint32_t
     return sum;
 }
 
-// The line from position s on, from device memory.
-__device__ __forceinline__ bool line_slow(const ParseArgs& a, uint64_t s, uint32_t& ts, uint32_t& src,
-                                          uint32_t& dst, uint64_t& nb) {
-    const uint64_t n = a.t.end - s;
-    return parse_line(GlobalLine{a.t.base + s}, n < 0xFFFFFFFFull ? (uint32_t)n : 0xFFFFFFFEu, a.origin, ts,
-                      src, dst, nb);
+// A line that leaves its window, from position s on, by one wave: 1,024 bytes a
+// step, the next ones loaded meanwhile.  A lane ranks its 16 bytes' delimiters and
+// notes the ends of the fields that are needed; then the fields are copied to LDS
+// (buf, 96 bytes) and every lane parses them.
+__device__ __forceinline__ bool line_far(const ParseArgs& a, uint64_t s, uint32_t lane, uint64_t* ends,
+                                         uint8_t* buf, uint32_t& ts, uint32_t& src, uint32_t& dst,
+                                         uint64_t& nb) {
+    constexpr uint32_t kEnds[7] = {1, 4, 5, 7, 8, 20, 21};  // delimiters of the line, by number
+    uint64_t x = (s & ~15ull) + 16u * lane;
+    uint4 v = group16(a.t, x);
+    uint32_t seen = 0;  // delimiters before this step
+    for (;; x += 1024) {
+        const uint4 next = group16(a.t, x + 1024);
+        uint32_t nl = chars16<10>(v), dl = nl | chars16<','>(v);
+        if (x < s) {  // the first step's first group: bytes before the line
+            nl &= 0xFFFFu << (uint32_t)(s - x);
+            dl &= 0xFFFFu << (uint32_t)(s - x);
+        }
+        const uint32_t c = (uint32_t)__popc(dl);
+        uint32_t before = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)before, o);
+            if (lane >= (uint32_t)o) before += y;
+        }
+        uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)before, 63);  // of the line
+        before -= c;
+        const uint64_t has = __ballot(nl != 0u);
+        if (has)  // up to the line's own newline
+            upto = (uint32_t)__builtin_amdgcn_readlane((int)(before + (uint32_t)__popc(dl & ((nl & (0u - nl)) * 2u - 1u))),
+                                                       __builtin_ctzll(has));
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            uint32_t j = kEnds[k] - seen - before;  // the lane's j-th delimiter, wrapped when below
+            if (j - 1u >= c || kEnds[k] - seen > upto) continue;
+            uint32_t m = dl;
+            for (; j > 1; --j) m &= m - 1u;
+            ends[k] = x + (uint32_t)__builtin_ctz(m);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        const bool start = seen == 0;
+        seen += upto;
+        // a first field of other than 23 bytes: bad, however long the line is
+        if (start && (seen == 0 || ends[0] - s != 23u)) return false;
+        if (has || seen >= 21u) break;
+        if (x - 16u * lane + 1024 >= a.t.end) {  // the text ends with this line
+            if (seen == 20u && lane == 0) ends[6] = a.t.end;
+            ++seen;  // as a newline would
+            break;
+        }
+        v = next;
+    }
+    if (seen < 21u) return false;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const uint64_t f[4] = {s, ends[1] + 1, ends[3] + 1, ends[5] + 1};
+    const uint64_t n1 = ends[2] - f[1], n2 = ends[4] - f[2], n3 = ends[6] - f[3];
+    if (n1 > 15u || n2 > 15u || n3 > 20u) return false;
+    // each field with three bytes before it and three behind in its own part
+    constexpr uint32_t kAt[4] = {4, 32, 52, 72};
+    const uint32_t n[4] = {23u, (uint32_t)n1, (uint32_t)n2, (uint32_t)n3};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (lane < n[k]) buf[kAt[k] + lane] = *glob(a.t.base + f[k] + lane);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const Staged b{buf};
+    return staged_time(b, kAt[0], a.origin, ts) && staged_ipv4(b, kAt[1], kAt[1] + n[1], src) &&
+           staged_ipv4(b, kAt[2], kAt[2] + n[2], dst) && staged_count(b, kAt[3], kAt[3] + n[3], nb);
 }
 
 __device__ __forceinline__ uint32_t put_line(const ParseArgs& a, uint64_t l, bool ok, uint32_t ts,
@@ -403,14 +379,14 @@ __device__ __forceinline__ uint32_t put_line(const ParseArgs& a, uint64_t l, boo
 
 __global__ void __launch_bounds__(kParseBlock, 6) k_parse(ParseArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t s_text[kWindow + 16];
-    __shared__ uint16_t s_delim[kDelims];             // positions in the window, ascending
+    __shared__ __attribute__((aligned(16))) uint16_t s_delim[kDelims];  // positions in the window, ascending
     __shared__ uint16_t s_start[kLines], s_rank[kLines];  // per newline: position + 1, its delimiter rank
     __shared__ uint32_t s_wave[kParseBlock / 64];
-    __shared__ uint32_t s_blk, s_own, s_bad, s_end;
-    __shared__ uint64_t s_base;
+    __shared__ uint32_t s_blk, s_own, s_bad, s_end, s_far;
+    __shared__ uint64_t s_base, s_ends[7];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     if (tid == 0) {
-        s_bad = 0;
+        s_bad = s_far = 0;
         s_blk = atomicAdd(a.ticket, 1u);
     }
     __syncthreads();
@@ -544,8 +520,9 @@ __global__ void __launch_bounds__(kParseBlock, 6) k_parse(ParseArgs a) {
                          staged_ipv4(b, c4 + 1, c5, src) && staged_ipv4(b, c7 + 1, c8, dst) &&
                          staged_count(b, c20 + 1, c21, nb);
                 }
-            } else {
-                ok = line_slow(a, b0 + s, ts, src, dst, nb);
+            } else {  // the block's last line leaves the window: below
+                s_far = s + 1u;
+                return false;
             }
             return true;
         };
@@ -568,6 +545,16 @@ __global__ void __launch_bounds__(kParseBlock, 6) k_parse(ParseArgs a) {
         __syncthreads();  // the lists are written again
         k_lo = k;
         d_lo = d;
+    }
+    if (!at_end && n_nl == s_own) {  // no newline behind the block's own in the window
+        __syncthreads();
+        if (wave == 0 && s_far) {
+            uint32_t ts = 0, src = 0, dst = 0;
+            uint64_t nb = 0;
+            const bool ok = line_far(a, b0 + s_far - 1u, lane, s_ends, reinterpret_cast<uint8_t*>(s_delim), ts, src, dst, nb);
+            // (the block's last line)
+            if (lane == 0) bad += put_line(a, s_base + s_own, ok, ts, src, dst, nb);
+        }
     }
     // one counter for all blocks: a block adds its own once (by waves, text without
     // a good line was bound by it: 2e8 bytes of 40-byte lines 0.77 -> 0.25 ms)

@@ -97,3 +97,27 @@ def test_bad_lines_are_counted_over_many_blocks():
     for k in range(0, 40_000, 997):
         lines[k] = _line(rng)
     _check(np.frombuffer(b"".join(lines), np.uint8), off=5)
+
+
+@pytest.mark.parametrize("at", [1, 2, 5, 9, 20, 21, 22, 24])
+def test_one_line_beyond_its_window(at):
+    """A last line that leaves its window by a field of every length around a step
+    of the search (1,024 bytes), with and without a newline, cut after field 21,
+    20 or 3, or with one field too long to be good."""
+    rng = np.random.default_rng(at)
+    head = _fill(rng, OWN - 150, []).tobytes()
+    lines = []
+    for n in (1_200, 2_040, 2_047, 2_048, 2_049, 5_000, 40_000):
+        line = _line(rng, n + int(rng.integers(0, 16)), at)
+        f = line[:-1].split(b",")
+        lines += [line, b",".join(f[:21]) + b"\n", b",".join(f[:20]) + b"\n", b",".join(f[:3]) + b"\n",
+                  b",".join(f[:20] + [b"18446744073709551615"] + f[21:]) + b"\n",
+                  b",".join(f[:20] + [b"18446744073709551616"]) + b"\n"]
+    for k, line in enumerate(lines):
+        off = k % 16
+        if k % 3 == 0:
+            _check(np.frombuffer(head + line + _line(rng), np.uint8), off)
+        elif k % 3 == 1:
+            _check(np.frombuffer(head + line, np.uint8), off)
+        else:
+            _check(np.frombuffer(head + line[:-1], np.uint8), off)
