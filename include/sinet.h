@@ -197,10 +197,14 @@ const char* sinet_version(void);
  * index when it fits in LDS (a 2-bit state per /16 block plus the sorted
  * 16-bit offsets of the boundaries of the union of all prefixes inside the
  * /16 blocks that such a boundary cuts); label-only queries are answered from
- * it (a SCAN table's by a search over that union's boundaries).  Every table also gets an institution index (the /16 blocks that any
- * prefix touches, and small sorted groups of the boundaries inside them), which
- * answers institution ids; the kind's search serves positions.  kind may be
- * OR-ed with SINET_TABLE_NO_INOUT_INDEX.  base: IPv4
+ * it (a SCAN table's by a search over that union's boundaries).  A table also
+ * gets an institution index (the /16 blocks that any prefix touches, and small
+ * sorted groups of the boundaries inside them: 32 bytes per seven boundaries, or
+ * 16 per six where there are more than 4,095 institutions or ids from 2^20 on),
+ * which answers institution ids; where its records and samples do not fit LDS
+ * (about 70,000 blocks and groups), tries, PLAs of windows and searches of less
+ * than 2^19 boundaries in deep groups serve them themselves.  The kind's search
+ * serves positions.  kind may be OR-ed with SINET_TABLE_NO_INOUT_INDEX.  base: IPv4
  * address, host bits allowed (they are masked off as Algorithm 1 masks the
  * CIDR base); len: prefix length Z in 0..32; inst: institution id of the row
  * (any value except SINET_NO_INST), or NULL for the row index.  The longest

@@ -367,7 +367,18 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
         un.resize((size_t)1 << un_steps, 0xFFFFFFFFu);
     }
     InstIndex ix;
-    if (want_io) build_inst_index(t->B, t->owner, id.data(), ix);
+    bool want_inst = want_io;
+    if (want_inst) {
+        build_inst_index(t->B, t->owner, id.data(), ix);
+        InstDev x{};
+        x.groups = ix.groups.data();  // (the sizes decide)
+        x.n_first = (uint32_t)ix.first.size();
+        x.n_sample = (uint32_t)ix.sample.size();
+        x.n_dict = ix.coded ? (uint32_t)ix.MI.size() : 0u;
+        x.steps = ix.steps;
+        want_inst = inst_pays(x, kind, false, m);  // a PLA's windows are known later
+        if (!want_inst) ix = InstIndex{};
+    }
     std::vector<uint32_t> trie;
     if (kind == SINET_LOOKUP_TRIE) build_trie(t->B, trie);
     const bool learned = kind == SINET_LOOKUP_LEARNED_PLA || kind == SINET_LOOKUP_LEARNED_MLP;
@@ -460,7 +471,7 @@ sinet_status sinet_table_create(const uint32_t* base, const uint8_t* len, const 
         d.un_in0 = un_in0;
     }
     t->inst = InstDev{};
-    if (want_io) {
+    if (want_inst) {
         t->inst.groups = (const uint32_t*)(a + oIg);
         t->inst.first = (const uint32_t*)(a + oIf);
         t->inst.sample = (const uint16_t*)(a + oIs);
@@ -648,7 +659,7 @@ sinet_status sinet_discriminate(const sinet_table* t, const uint32_t* src, const
     if (n == 0) return SINET_OK;
     if (!src || !dst) return fail(SINET_ERR_INVALID_ARG, "src or dst is NULL");
     if (!label && !src_inst && !dst_inst) return SINET_OK;
-    if ((src_inst || dst_inst) && t->inst.groups)
+    if ((src_inst || dst_inst) && inst_pays(t->inst, t->dev.kind, t->dev.pla_window != 0, t->dev.m))
         return run_inst(t->inst, src, dst, n, label, src_inst, dst_inst, stream);
     PassParams p;
     memset(&p, 0, sizeof(p));

@@ -166,17 +166,39 @@ __global__ void __launch_bounds__(kInstBlock) k_inst(InstArgs a) {
     }
 }
 
+// LDS of a workgroup with the records and samples in it, or 0 when they do not fit.
+size_t inst_lds(const InstDev& x) {
+    const size_t lds = 4ull * (kInstGroups + x.n_dict) + 2ull * (x.n_first + x.n_sample);
+    return lds <= kInstLdsMax && x.n_sample <= 65536 ? lds : 0;
+}
+
 }  // namespace
+
+// Where the records and samples fit LDS the index is the faster one for every
+// kind.  Where each step of the search reads L2 instead, it depends (5e7 sessions,
+// both ids and the label):
+//   a trie (at most three reads) and a PLA whose windows are 16 boundaries are
+//   faster themselves: 400,000 clustered prefixes 3.12 ms by the index, 1.65 by the
+//   trie, 1e6 3.80 and 2.67; 100,000 random /24 1.80, 1.76 and 1.25 by the PLA;
+//   the other searches lose where the index takes few steps (70,000 random /24, two:
+//   1.70 against 2.01 ms; 1e6, four: 2.96 against 8.41) or the table is large
+//   (600,000 clustered prefixes, 726,000 boundaries, eight steps: 3.45 against 3.97;
+//   1e6 3.83 against 4.99), else they win (400,000, 485,000 boundaries, eight: 3.12
+//   against 2.72).
+bool inst_pays(const InstDev& x, uint32_t kind, bool window, uint32_t m) {
+    if (!x.groups) return false;
+    if (inst_lds(x)) return true;
+    if (kind == SINET_LOOKUP_TRIE || (kind == SINET_LOOKUP_LEARNED_PLA && window)) return false;
+    return x.steps <= 4 || m >= (1u << 19);
+}
 
 sinet_status run_inst(const InstDev& x, const uint32_t* src, const uint32_t* dst, uint64_t n,
                       uint8_t* label, uint32_t* src_inst, uint32_t* dst_inst, hipStream_t s) {
     const InstArgs a{x, src, dst, label, src_inst, dst_inst, n};
     const bool vec = (((uintptr_t)src | (uintptr_t)dst | (uintptr_t)src_inst | (uintptr_t)dst_inst) & 15u) == 0 &&
                      ((uintptr_t)label & 3u) == 0;
-    const size_t base = 4ull * (kInstGroups + x.n_dict);
-    size_t lds = base + 2ull * (x.n_first + x.n_sample);
-    const bool in_lds = lds <= kInstLdsMax && x.n_sample <= 65536;
-    if (!in_lds) lds = base;
+    const bool in_lds = inst_lds(x) != 0;
+    const size_t lds = in_lds ? inst_lds(x) : 4ull * (kInstGroups + x.n_dict);
     auto pick = [&](auto coded) {
         constexpr bool C = decltype(coded)::value;
         return in_lds ? (vec ? k_inst<C, true, true> : k_inst<C, true, false>)

@@ -287,7 +287,10 @@ uint32_t device_cu_count();
 int blocks_per_cu(const void* fn, int block, size_t lds);
 uint64_t div_magic(uint32_t width);
 
-// Institution ids (and labels) through the institution index (inst.hip).
+// Institution ids (and labels) through the institution index (inst.hip); whether
+// that is faster than the kind's own search (window: a PLA's bound fits one) over
+// m boundaries.
+bool inst_pays(const InstDev& x, uint32_t kind, bool window, uint32_t m);
 sinet_status run_inst(const InstDev& x, const uint32_t* src, const uint32_t* dst, uint64_t n,
                       uint8_t* label, uint32_t* src_inst, uint32_t* dst_inst, hipStream_t s);
 

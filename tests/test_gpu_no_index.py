@@ -57,6 +57,32 @@ def test_institutions_by_the_kinds_search(kind):
                     assert np.array_equal(g.cpu().numpy().view(e.dtype), e), (n, want)
 
 
+@pytest.mark.parametrize("kind", ["bsearch", "trie", "pla", "mlp"])
+@pytest.mark.parametrize("ids,deep", [(900, False), (1 << 30, False), (900, True)])
+def test_institutions_of_tables_beyond_lds(kind, ids, deep):
+    """Default tables whose index does not fit LDS: some kinds search themselves."""
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    rng = np.random.default_rng(ids % 1000)
+    base = (rng.integers(0, 1 << 24, 70_000) << 8).astype(np.uint32)
+    plen = np.full(70_000, 24, np.uint8)
+    if deep:  # 600,000 hosts in 2,000 blocks: many groups in a block
+        base = ((rng.integers(0, 2_000, 600_000) * 32 << 16) + rng.integers(0, 1 << 16, 600_000)).astype(np.uint32)
+        base, plen = base[:250_000], np.full(250_000, 32, np.uint8)
+    inst = rng.integers(0, ids, len(base)).astype(np.uint32)
+    tab = sinet.Table(base, plen, inst, kind=kind)
+    if kind in ("pla", "mlp"):
+        tab.train(steps=30 if kind == "mlp" else 0)
+    n = 200_003
+    print("institutions beyond LDS", kind, ids, flush=True)
+    a = _addresses(rng, base, n)
+    got = sinet.discriminate(tab, *(sinet.to_device_u32(x) for x in a), True, True, True)
+    torch.cuda.synchronize()
+    for g, e in zip(got, oracle.classify(base, plen, a[0], a[1], inst)):
+        assert np.array_equal(g.cpu().numpy().view(e.dtype), e)
+
+
 @pytest.mark.parametrize("n,width,n_bins", [(3, 1, 5_000), (300_007, 1, 5_000), (300_007, 50, 100),
                                             (400_003, 60, 4_000), (400_003, 9, 4_000)])
 def test_scan_labels_by_the_row_scan(n, width, n_bins):
