@@ -63,14 +63,16 @@ inline void build_inst_index(const std::vector<uint32_t>& B, const std::vector<u
         }
     }
     // codes in order of first use (0: outside), for ids that a small array maps
-    std::vector<uint16_t> code_of(kInstIdMax, 0);
+    uint32_t max_id = 0;
+    for (const uint32_t v : ix.MI)
+        if (v != kInstNone && v > max_id) max_id = v;
+    ix.coded = max_id < kInstIdMax;
+    std::vector<uint16_t> code_of(ix.coded ? max_id + 1 : 0, 0);
     std::vector<uint32_t> dict{kInstNone};
-    ix.coded = true;
     for (size_t j = 0; j < ix.MI.size() && ix.coded; ++j) {
         const uint32_t v = ix.MI[j];
         if (v == kInstNone) continue;
-        ix.coded = v < kInstIdMax;
-        if (!ix.coded || code_of[v]) continue;
+        if (code_of[v]) continue;
         ix.coded = dict.size() < kInstDictMax;
         code_of[v] = (uint16_t)dict.size();
         dict.push_back(v);
