@@ -3410,9 +3410,13 @@ static sinet_status run_local_in(const PassParams& p, uint32_t kind, int accumul
     return launch_aside(q, kind, aside, s);
 }
 
+// Sessions whose labels wait in the workspace at a time, so that calls on a nearly
+// full device need little of it.
+constexpr uint64_t kLocalLabels = 1ull << 28;
+
 static sinet_status run_local(const PassParams& p, uint32_t kind, int accumulate, hipStream_t s) {
     const bool fused = local_fuses(kind, p.t);
-    const size_t lab = !fused && !p.label_out ? al256(p.n) : 0;
+    const size_t lab = !fused && !p.label_out ? al256(std::min(p.n, kLocalLabels)) : 0;
     size_t aside = !shape_of(p, fused ? kind : (uint32_t)KK_LABEL_IN).whole && local_defers(p.n, p.n_bins)
                        ? defer_bytes(p.n, p.n_bins) : 0;
     void* ws = nullptr;
@@ -3425,7 +3429,13 @@ static sinet_status run_local(const PassParams& p, uint32_t kind, int accumulate
         const sinet_status st = ws_alloc(&ws, lab, s);
         if (st != SINET_OK) return st;
     }
-    const sinet_status st = run_local_in(p, kind, accumulate, s, (uint8_t*)ws, aside ? (uint32_t*)((char*)ws + lab) : nullptr, true);
+    static_assert(kLocalLabels >= kWindowMinSessions, "calls that set runs aside are one piece");
+    sinet_status st = SINET_OK;
+    for (uint64_t lo = 0; st == SINET_OK && lo < p.n; lo += lab ? kLocalLabels : p.n) {
+        PassParams q = advance(p, lo);
+        if (lab) q.n = std::min(q.n, kLocalLabels);
+        st = run_local_in(q, kind, accumulate || lo, s, (uint8_t*)ws, aside ? (uint32_t*)((char*)ws + lab) : nullptr, true);
+    }
     const sinet_status st2 = ws ? ws_free(ws, s) : SINET_OK;
     return st != SINET_OK ? st : st2;
 }

@@ -156,3 +156,33 @@ def test_batch_with_coarse_streams_equals_oracle(chunk):
             assert lab is None or np.array_equal(lab.cpu().numpy(), elab), j
             for got, e in zip(out, (ec, eb, ed)):
                 assert np.array_equal(sinet.to_host_u64(got), e), j
+
+
+def test_labels_in_pieces():
+    """More sessions than the workspace holds labels of, by a table whose lookups
+    are a pass of their own: equal to the histogram of the labels given."""
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    n, width, n_bins = (1 << 28) + 4_099, 60_000, 1_440
+    rng = np.random.default_rng(5)
+    base, plen = rng.integers(0, 1 << 32, 900).astype(np.uint32), rng.integers(6, 29, 900).astype(np.uint8)
+    tab = sinet.Table(base, plen, kind="trie", inout_index=False)
+    print("labels in pieces", n, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    ts = torch.linspace(0, n_bins * width - 1, n, device="cuda", dtype=torch.float64).to(torch.int32)
+    src, dst = (torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda", dtype=torch.int32)
+                for _ in range(2))
+    by = torch.randint(0, 1 << 31, (n,), generator=g, device="cuda")
+    lab = sinet.discriminate(tab, src, dst)[0]
+    given = sinet.histogram(ts, by, lab, 60_000, width, n_bins)
+    none, looked = sinet.pipeline(tab, ts, src, dst, by, 60_000, width, n_bins, label=False)
+    torch.cuda.synchronize()
+    assert none is None and int(given[0].sum()) + int(given[2][:, 0].sum()) == n
+    for a, b in zip(given, looked):
+        assert torch.equal(a, b)
+    sinet.pipeline(tab, ts, src, dst, by, 60_000, width, n_bins, label=False, out=looked, accumulate=True)
+    torch.cuda.synchronize()
+    for a, b in zip(given, looked):
+        assert torch.equal(a * 2, b)
