@@ -3108,11 +3108,13 @@ sinet_status launch_batch_lookup(uint32_t kind, const BatchArgs& a, size_t lds, 
 }
 
 // Two workgroups per CU where the table leaves 8 KB or more for the window
-// then, else one; at most 32 KB.
-uint32_t batch_window_words(size_t table) {
+// then, else one; at most 32 KB.  two: what two leave, however little.
+uint32_t batch_window_words(size_t table, bool two) {
     const size_t used = kStage1StaticLds + sizeof(BatchStreamDev) + 256 + table;
-    for (const size_t lds : {(size_t)80 * 1024, (size_t)160 * 1024})
-        if (lds >= used + 8 * 1024) return (uint32_t)((lds - used < 32 * 1024 ? lds - used : 32 * 1024) / 8);
+    for (const size_t lds : {(size_t)80 * 1024, (size_t)160 * 1024}) {
+        if (lds >= used + (two ? 0 : 8 * 1024)) return (uint32_t)((lds - used < 32 * 1024 ? lds - used : 32 * 1024) / 8);
+        if (two) break;
+    }
     return 0;
 }
 

@@ -318,7 +318,7 @@ sinet_status launch_zero_jobs(const ZeroJob* jobs, uint32_t n_jobs, hipStream_t 
 sinet_status launch_scan_fill(const PartWs& w, hipStream_t s);
 // 64-bit words of the local window of a stage-1 workgroup whose largest table
 // takes `table` bytes of LDS (0: no room)
-uint32_t batch_window_words(size_t table);
+uint32_t batch_window_words(size_t table, bool two);
 uint32_t batch_stage1_blocks_per_cu(uint32_t kind, size_t lds);
 // lookups that run as their own pass before stage 1
 bool lookup_splits(const DevTable& t);
