@@ -186,10 +186,16 @@ __device__ __forceinline__ void win_flush(const WinArgs& a, const WinPiece& g, u
     }
 }
 
-// First event of piece q: room for 1/15 of the sessions before it (a piece of m
-// sessions has at most m/32 carries and m/32 + m/1024 wraps) and a few each.
+// First event of piece q: room for 1/15 of the sessions before it and a few each.
+// A piece of m sessions carries out of byte fields at most m (kRingMaxBytes - 1) /
+// 2^27 times and wraps words at most m (2^27 + kRingMaxBytes - 1) / 2^32 times
+// (every ring word starts at 0), so its list needs no test of its end.
+constexpr uint64_t kEventShare = 15;
+static_assert(kEventShare * ((kRingMaxBytes - 1) * (1ull << (32 - kCountShift)) +
+                             ((1ull << kCountShift) + kRingMaxBytes - 1)) <= (1ull << 32),
+              "a piece's carries and wraps fit its share of the events");
 __device__ __host__ __forceinline__ uint64_t piece_events(uint64_t begin, uint32_t q) {
-    return begin / 15 + 8ull * q;
+    return begin / kEventShare + 8ull * q;
 }
 
 // Carry / wrap events of one add: only a bin with more than 32 sessions of one
