@@ -3345,18 +3345,20 @@ static sinet_status launch_aside(const PassParams& p, uint32_t kind, uint32_t* a
 constexpr size_t kLocalLds = 156 * 1024;
 constexpr size_t kLocalLdsLabels = 79 * 1024;
 
-// Label lookups that the local reduce runs itself; the others store their
-// labels in a pass of their own first.
-static bool local_fuses(uint32_t kind, const DevTable& t) {
-    return kind == KK_LABEL_IN || kind == KK_UNION ||
-           (kind == KK_INOUT && t.lds_bytes <= 92 * 1024);
-}
-
 // Bins that its window can hold.
 static uint32_t local_room(uint32_t kind, const DevTable& t) {
     const size_t tab = (kind == KK_LABEL_IN ? 0 : t.lds_bytes) + 16;
-    return (uint32_t)(((kind == KK_LABEL_IN ? kLocalLdsLabels : kLocalLds) - tab) / 32);
+    const size_t lds = kind == KK_LABEL_IN ? kLocalLdsLabels : kLocalLds;
+    return lds > tab ? (uint32_t)((lds - tab) / 32) : 0u;
 }
+
+// Label lookups that the local reduce runs itself, which leave its window room for
+// the bins that always take it, whatever the order of the sessions; the others
+// store their labels in a pass of their own first.
+static bool local_fuses(uint32_t kind, const DevTable& t) {
+    return kind == KK_LABEL_IN || ((kind == KK_UNION || kind == KK_INOUT) && local_room(kind, t) >= kLocalAlways);
+}
+static_assert((kLocalLdsLabels - 16) / 32 >= kLocalAlways, "labels given leave that room too");
 
 static LocalShape shape_of(const PassParams& p, uint32_t kind) {
     return local_shape(p.n, p.n_bins, p.width, local_room(kind, p.t), device_cu_count());
