@@ -509,8 +509,8 @@ sinet_status sinet_timing_read(sinet_timing* out);
  *            sessions in order to within a minute or so.  Out of order, from 9e7
  *            to 2^28 sessions and up to 65,536 bins, it sets them aside as
  *            records (at most 5.2 bytes of workspace per session; without that
- *            room it does not) and takes about twice the time; other calls take
- *            up to twice the time of RECORDS then.
+ *            room, or under graph capture, it does not) and takes about twice
+ *            the time; other calls take up to twice the time of RECORDS then.
  * Process-wide; takes effect for calls made after it returns.
  * Errors: INVALID_ARG (unknown mode). */
 typedef enum {

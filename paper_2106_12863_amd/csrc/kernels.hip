@@ -3423,6 +3423,13 @@ static sinet_status run_local(const PassParams& p, uint32_t kind, int accumulate
     const size_t lab = !fused && !p.label_out ? al256(std::min(p.n, kLocalLabels)) : 0;
     size_t aside = !shape_of(p, fused ? kind : (uint32_t)KK_LABEL_IN).whole && local_defers(p.n, p.n_bins)
                        ? defer_bytes(p.n, p.n_bins) : 0;
+    if (aside) {  // a captured call must not come to need an allocation for it
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            aside = 0;
+        }
+    }
     void* ws = nullptr;
     if (aside && ws_alloc(&ws, lab + aside, s) != SINET_OK) {  // no room: only slower out of order
         (void)hipGetLastError();

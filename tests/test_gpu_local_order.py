@@ -80,3 +80,39 @@ def test_order_chooses_the_reduce(n, n_bins, width, jitter, order):
         given = sinet.histogram(c[0], c[3], c[4], 500, width, n_bins)
         torch.cuda.synchronize()
         assert torch.equal(lab, lab2) and same(given, 1) and same(looked, 1), cut
+
+
+def test_captured_calls_take_no_workspace():
+    """A call that would set runs aside, captured into a graph with nothing but its
+    outputs: every replay, eager calls in between, equals the eager call."""
+    import torch
+
+    import paper_2106_12863_amd as sinet
+    n, n_bins, width = MIN, 65_536, 48
+    print("capture", n, n_bins, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    ts = torch.randint(0, n_bins * width, (n,), generator=g, device="cuda", dtype=torch.int32)
+    by = torch.randint(0, 1 << 40, (n,), generator=g, device="cuda")
+    lab = torch.randint(0, 4, (n,), generator=g, device="cuda", dtype=torch.uint8)
+    eager = sinet.histogram(ts, by, lab, 0, width, n_bins)
+    out = sinet.new_hist(n_bins)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        sinet.histogram(ts, by, lab, 0, width, n_bins, out=out)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sinet.histogram(ts, by, lab, 0, width, n_bins, out=out)
+    for rep in range(3):
+        for x in out:
+            x.fill_(7 + rep)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(out, eager)), rep
+        assert all(torch.equal(a, b) for a, b in
+                   zip(sinet.histogram(ts, by, lab, 0, width, n_bins), eager)), rep
+    assert free - torch.cuda.mem_get_info()[0] < n  # no record room was taken for the graph
