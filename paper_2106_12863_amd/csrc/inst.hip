@@ -5,14 +5,15 @@
 // rate of a large copy); every address in a /16 block with a record also costs
 // one random read of an L2-resident table (two without codes).  Random 4- or
 // 16-byte reads of a 1-4 MB table run at 2.65e11 reads/s on the device, of a
-// 16 MB one at 0.8e11, and that rate, not latency, is what is left: deferring
-// the institution reads by an iteration, 24 or 32 waves per CU instead of 16, or
-// a common address for the lanes without a record changed nothing (0.89-0.95
-// ms).  So everything but the leaf is kept in LDS, and with few distinct
-// institutions the leaf itself holds their codes.  1e8 sessions against
-// 200,000 prefixes, both ids and the label: 4.08 ms by the binary search over
-// the intervals (14 LDS steps, 4 dependent global reads, then the owner and its
-// id), 0.89 ms with an index into MI in the leaf, 0.75 ms with codes.
+// 16 MB one at 0.8e11, and that rate, not latency, is most of what is left (vector
+// issue is busy 67 % of the time, LDS with conflicts 38 %): deferring the
+// institution reads by an iteration, 24 or 32 waves per CU instead of 16, or a
+// common address for the lanes without a record changed nothing (0.89-0.95 ms).
+// So everything but the leaf is kept in LDS, and with few distinct institutions
+// the leaf itself holds their codes.  1e8 sessions against 200,000 prefixes, both
+// ids and the label: 4.08 ms by the binary search over the intervals (14 LDS
+// steps, 4 dependent global reads, then the owner and its id), 0.89 ms with an
+// index into MI in the leaf, 0.75 ms with codes.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

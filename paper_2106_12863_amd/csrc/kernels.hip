@@ -342,8 +342,7 @@ __device__ __forceinline__ unsigned long long pla_round(const DevTable& t, const
     const uint32_t sg = s0 + upper_last(v.knot + s0, s1 - s0 + 1, x);
     const int pp = clamp_pos(pla_eval(v.knot[sg], v.c[sg], v.g[sg], x), t.m);
     const uint32_t wb = (uint32_t)max(pp - e, 0) & ~3u;
-    // every window load, and the boundary after each window for the bracket
-    // check, is issued before any is used
+    // every window load is issued before any is used
     const uint32_t me = lane & 1u;
     uint32_t xx[2], bb[2], c[2];
     uint4 w[2][2];
@@ -1259,7 +1258,7 @@ __global__ void __launch_bounds__(kStage1Block, 4) k_stage1(PassParams p, PartWs
 // needs no barrier; runs do, two each.  Measured against the records (whose
 // stage 2 has one workgroup per 1,024 bins, and whose counters a few blocks
 // contend for) and, from 2^28 sessions on, the sliding window (whose 5-bit
-// counts overflow into one event list): 1e8 sessions of a day into 86,400
+// counts overflowed into one event list then): 1e8 sessions of a day into 86,400
 // one-second bins, lookups included, 1.78 -> 0.38 ms (5.3 TB/s); into 1,440
 // minutes 89.7 -> 0.37 ms; 4e8 labelled sessions into 86,400 seconds 63.4 ->
 // 0.91 ms (5.7 TB/s), into 144 ten-minute frames (before: 32-bit count and
@@ -2114,7 +2113,7 @@ __global__ void __launch_bounds__(256) k_clear(ClearArgs c) {
 // take the local reduce instead, an item being a run: their records made a few
 // blocks very long, which stage 2 ended on, and their private histograms held a
 // CU to one workgroup.  64 streams (3e8 sessions, a third in 1-s bins): stage 1
-// 3.20 -> 1.91 ms, stage 2 5.72 -> 4.16 ms, the whole batch 9.27 -> 6.31 ms.
+// 3.20 -> 1.78 ms, stage 2 5.72 -> 3.96 ms, the whole batch 9.27 -> 5.7 to 6.0 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
