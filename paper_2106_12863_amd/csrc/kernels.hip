@@ -1440,7 +1440,12 @@ __device__ __forceinline__ void local_flush(const PassParams& p, const LocalWin&
 // records 4.80, whose stage 2 has one workgroup per block), into 6,000 8.6 -> 0.53
 // (7.40); looked up, into 43,200 8.63 -> 0.79.  In order 0.240 -> 0.250 ms, looked
 // up 0.372 -> 0.382: the room for the records (a gap of 6 us in the stream where
-// it is given back) and the launches that find nothing to do.
+// it is given back) and the launches that find nothing to do.  The first call
+// after memory was freed otherwise (a table destroyed) maps that room again, 66 us
+// for 1e8 sessions, 150 to 200 for 2e8; taking it while k_local runs, with the flags
+// of the runs in an allocation of their own, saved that but cost every call a second
+// gap (2e8 looked up 886 -> 895 us), and so did a k_aside that found the runs
+// out of order itself (10 us, the samples' reads).
 
 // Whether more than an eighth of the bins that the lanes with `counts` bring lie
 // outside the window.  Called by the whole workgroup; s_vote holds a word per wave.

@@ -3,6 +3,10 @@ records (seen by the time of their second stage) and, for narrow bins, calls tha
 its probe hands to the records; the same exact result as the CPU oracle's,
 accumulated or not, for labels given and looked up, byte counts of every size and
 columns of every alignment."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -116,3 +120,35 @@ def test_captured_calls_take_no_workspace():
         assert all(torch.equal(a, b) for a, b in
                    zip(sinet.histogram(ts, by, lab, 0, width, n_bins), eager)), rep
     assert free - torch.cuda.mem_get_info()[0] < n  # no record room was taken for the graph
+
+
+NO_ROOM = """
+import torch, paper_2106_12863_amd as sinet
+n, n_bins, width, step = 260_000_000, 65_536, 48, 50_000_000
+g = torch.Generator(device="cuda"); g.manual_seed(3)
+ts = torch.randint(0, n_bins * width, (n,), generator=g, device="cuda", dtype=torch.int32)
+by = torch.randint(0, 1 << 40, (n,), generator=g, device="cuda")
+lab = torch.randint(0, 4, (n,), generator=g, device="cuda", dtype=torch.uint8)
+want, out = sinet.new_hist(n_bins), sinet.new_hist(n_bins)
+for k, lo in enumerate(range(0, n, step)):  # too few sessions a call to be set aside
+    sinet.histogram(ts[lo:lo + step], by[lo:lo + step], lab[lo:lo + step], 0, width, n_bins, out=want,
+                    accumulate=k > 0)
+torch.cuda.synchronize()
+fill = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+print("free", torch.cuda.mem_get_info()[0], flush=True)
+sinet.timing_enable(True)
+sinet.histogram(ts, by, lab, 0, width, n_bins, out=out)
+torch.cuda.synchronize()
+print("ms", sinet.timing_read(), flush=True)
+assert all(torch.equal(a, b) for a, b in zip(out, want))
+print("equal", flush=True)
+"""
+
+
+def test_no_room_for_records():
+    """With 1 GiB free the records of 2.6e8 shuffled sessions (1.3 GB) have no room: no run
+    is set aside, with the same result."""
+    print("no room", flush=True)
+    r = subprocess.run([sys.executable, "-c", NO_ROOM], capture_output=True, text=True, timeout=100,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0 and "equal" in r.stdout, r.stdout + r.stderr
